@@ -183,23 +183,28 @@ qsg_status make_layout(const qsg_group_desc* d, uint32_t n, const qsg_run_config
     return QSG_OK;
 }
 
-// Which specialised class list covers every class of this slot that is not
-// accepted outright (threshold below 2^32-1): 0, 1, 2, or 3 for the generic
-// fifteen-class update.  The lists match the kernels' Classes<R>.
-const int kRegimeLists[3][7][2] = {
-    {{0, 0}, {1, 0}, {2, 0}, {3, 0}, {4, 0}, {0, 1}, {1, 1}},
-    {{0, 0}, {1, 0}, {2, 0}, {3, 0}, {0, 1}, {1, 1}, {0, 2}},
-    {{0, 0}, {1, 0}, {2, 0}, {0, 1}, {1, 1}, {0, 2}, {1, 2}},
+// The seven classes (n_s, n_t) of each regime whose flip can raise the
+// energy, and the code the colour pass numbers each with (class_code).
+struct RegimeClass {
+    uint32_t ns, nt, code;
+};
+const RegimeClass kRegimeClasses[3][7] = {
+    {{0, 0, 0}, {1, 0, 1}, {2, 0, 2}, {3, 0, 3}, {4, 0, 4}, {0, 1, 5}, {1, 1, 6}},
+    {{0, 0, 0}, {1, 0, 1}, {2, 0, 2}, {3, 0, 3}, {0, 1, 4}, {1, 1, 5}, {0, 2, 6}},
+    {{0, 0, 4}, {1, 0, 5}, {2, 0, 6}, {0, 1, 0}, {1, 1, 1}, {0, 2, 2}, {1, 2, 3}},
 };
 
+// The regime whose list covers every class of this slot that is not accepted
+// outright (threshold below 2^32-1).  Couplings k > 0, kp >= 0 always fall in
+// one of the three: dE > 0 needs n_s < 2 + kp/k at n_t = 0, n_s < 2 at n_t =
+// 1 and n_s < 2 - kp/k at n_t = 2.  3: none (no ladder gives it).
 uint32_t class_regime(const uint32_t* thr15) {
     for (uint32_t r = 0; r < 3; ++r) {
         bool covered = true;
-        for (int c = 0; c < 15 && covered; ++c) {
+        for (uint32_t c = 0; c < 15 && covered; ++c) {
             if (thr15[c] == 0xFFFFFFFFu) continue;
             bool in = false;
-            for (int i = 0; i < 7; ++i)
-                in |= (kRegimeLists[r][i][0] * 3 + kRegimeLists[r][i][1] == c);
+            for (const RegimeClass& k : kRegimeClasses[r]) in |= k.ns * 3 + k.nt == c;
             covered = in;
         }
         if (covered) return r;
@@ -207,21 +212,16 @@ uint32_t class_regime(const uint32_t* thr15) {
     return 3;
 }
 
-// Level picks of a slot in regime r < 3: per comparison level (bit 31 - b of
-// the thresholds, b = 0..31) the set of the regime's seven classes whose
-// threshold bit is 1, or its complement with bit 7 set when that is smaller,
-// so the colour pass ORs at most three class masks per level.
-void level_picks(const uint32_t* thr15, uint32_t r, uint32_t* out8) {
-    for (int w = 0; w < 8; ++w) out8[w] = 0;
-    if (r > 2) return;
-    for (int b = 0; b < 32; ++b) {
-        uint32_t set = 0;
-        for (int i = 0; i < 7; ++i) {
-            const int c = kRegimeLists[r][i][0] * 3 + kRegimeLists[r][i][1];
-            set |= ((thr15[c] >> (31 - b)) & 1u) << i;
-        }
-        const uint32_t pick = __builtin_popcount(set) > 3 ? ((~set & 0x7Fu) | 0x80u) : set;
-        out8[b >> 2] |= pick << (8 * (b & 3));
+// Handler entries of a slot in regime r < 3: per comparison level (bit 31 - b
+// of the thresholds, b = 0..31) the truth table of the threshold bit over the
+// class codes.
+void level_entries(const uint32_t* thr15, uint32_t r, uint32_t* out16) {
+    for (int b = 0; b < 32; b += 2) {
+        uint32_t table[2] = {0, 0};
+        for (const RegimeClass& k : kRegimeClasses[r])
+            for (int h = 0; h < 2; ++h)
+                table[h] |= ((thr15[k.ns * 3 + k.nt] >> (31 - b - h)) & 1u) << k.code;
+        out16[b >> 1] = qsg::level_entry(table[0]) | qsg::level_entry(table[1]) << 16;
     }
 }
 
@@ -428,7 +428,7 @@ void for_state_regions(const qsg_ctx* c, F f) {
 
 namespace {
 // Build a group's tables with the host builder of its ladder kind and upload
-// them (thresholds, regime, level picks, exchange tables).
+// them (thresholds, regime, level entries, exchange tables).
 qsg_status set_ladder(qsg_ctx* c, uint32_t group, const double* values, uint32_t kind) {
     if (qsg_status st = check_ctx(c)) return st;
     if (group >= c->desc.size()) return fail(c, QSG_E_INVALID, "group %u out of range", group);
@@ -452,8 +452,9 @@ qsg_status set_ladder(qsg_ctx* c, uint32_t group, const double* values, uint32_t
     for (uint32_t i = 0; i < N; ++i) {
         for (int k = 0; k < 15; ++k) thr[i * qsg::kThrStride + k] = thr15[i * 15 + k];
         const uint32_t r = class_regime(&thr15[i * 15]);
+        if (r > 2) return fail(c, QSG_E_UNSUPPORTED, "slot %u: thresholds fit no class regime", i);
         thr[i * qsg::kThrStride + 15] = r;
-        level_picks(&thr15[i * 15], r, &thr[i * qsg::kThrStride + qsg::kLevelPicks]);
+        level_entries(&thr15[i * 15], r, &thr[i * qsg::kThrStride + qsg::kLevelEntries]);
     }
     for (uint32_t i = 0; i < pairs; ++i) eq32[i] = eq[i];
     hipStream_t s = c->stream;

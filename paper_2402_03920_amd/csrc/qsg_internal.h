@@ -23,12 +23,17 @@ constexpr int kCntStride = 64 + 64 + 32;  // int32 per slot
 // Per-slot measurement sums: Bsp[64], Bt[64], q[32], q^2[32] as int64.
 constexpr int kSumStride = 192;
 // Per-slot table: [0, 15) thresholds of the fifteen classes, [15] the class
-// regime, [16, 24) the level picks (one byte per comparison level, most
-// significant first, four to a word): for the seven classes of regimes 0-2,
-// bits 0-6 mark the classes whose threshold has a 1 at that level, or, when
-// more than three do, bits 0-6 mark those with a 0 and bit 7 is set.
+// regime, [16, 32) the handler entries of the 32 comparison levels, most
+// significant first, two 16-bit entries to a word (the word of Philox block
+// q).  A level's truth table (7 bits) has bit c set when the threshold of
+// class code c has a 1 at that level; table i's handler starts kHandlerSkip +
+// i * kHandlerBytes after the address the colour pass jumps from.
 constexpr int kThrStride = 32;
-constexpr int kLevelPicks = 16;
+constexpr int kLevelEntries = 16;
+constexpr uint32_t kHandlerBytes = 32;
+constexpr uint32_t kHandlerSkip = 12;
+constexpr uint32_t kEntryMask = 127 * kHandlerBytes | kHandlerSkip;
+constexpr uint32_t level_entry(uint32_t table) { return kHandlerSkip + table * kHandlerBytes; }
 // Histogram of the unsatisfied time bonds u = (V - Bt)/2 per slot, taken at
 // every PT step before the exchanges: bin = u * kHistBins / (V + 1).
 constexpr int kHistBins = 1024;

@@ -34,9 +34,9 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// In the colour pass only counter word 0 (the site) differs between lanes,
-// so the first two rounds group their xors to keep the block-uniform parts
-// on the scalar unit: round 0 has c.y, c.z, c.w uniform, round 1 c.x, c.y.
+// Where only counter word 0 differs between lanes, the first two rounds group
+// their xors to keep the uniform parts on the scalar unit: round 0 has c.y,
+// c.z, c.w uniform, round 1 c.x, c.y.
 __device__ __forceinline__ uint4 philox(uint4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
@@ -51,6 +51,45 @@ __device__ __forceinline__ uint4 philox(uint4 c, uint32_t k0, uint32_t k1) {
             c = make_uint4(xor3(h1, c.y, k0), (uint32_t)p1, xor3(h0, c.w, k1), (uint32_t)p0);
         k0 += kW0;
         k1 += kW1;
+    }
+    return c;
+}
+
+// The same block in two parts for the colour pass, where counter word 0 (the
+// site) differs between lanes and words 1-3 (sweep, slot and block, group)
+// are block-uniform.  What only the site, the group and the key decide is
+// kept per word over its blocks (philox_site: round 0's product of the site
+// and round 1's product of its high half); per block (philox_block) the
+// uniform products of the first two rounds run on the scalar unit, which
+// leaves 2 + 8 * 4 vector instructions.
+struct PhiloxSite {
+    uint32_t lo0;       // low half of round 0's product of the site
+    uint32_t lo1, hi1;  // round 1's product of (its high half ^ group ^ key)
+};
+
+__device__ __forceinline__ PhiloxSite philox_site(uint32_t s, uint32_t gid, uint32_t k1) {
+    const uint64_t p = (uint64_t)s * kM0;
+    const uint64_t q = (uint64_t)((uint32_t)(p >> 32) ^ (gid ^ k1)) * kM1;
+    return {(uint32_t)p, (uint32_t)q, (uint32_t)(q >> 32)};
+}
+
+__device__ __forceinline__ uint4 philox_block(const PhiloxSite& ps, uint32_t t, uint32_t gq,
+                                              uint32_t k0, uint32_t k1) {
+    const uint64_t u = (uint64_t)gq * kM1;                                // round 0
+    const uint64_t v = (uint64_t)((uint32_t)(u >> 32) ^ t ^ k0) * kM0;    // round 1
+    uint4 c = make_uint4(ps.hi1 ^ ((uint32_t)u ^ (k0 + kW0)), ps.lo1,
+                         ps.lo0 ^ ((uint32_t)(v >> 32) ^ (k1 + kW1)), (uint32_t)v);
+#pragma unroll
+    for (int r = 2; r < 10; ++r) {
+        k0 += r == 2 ? 2 * kW0 : kW0;
+        k1 += r == 2 ? 2 * kW1 : kW1;
+        const uint64_t p0 = (uint64_t)c.x * kM0;
+        const uint64_t p1 = (uint64_t)c.z * kM1;
+        const uint32_t h0 = (uint32_t)(p0 >> 32), h1 = (uint32_t)(p1 >> 32);
+        if (r == 2)  // c.w is uniform
+            c = make_uint4(xor3(h1, c.y, k0), (uint32_t)p1, h0 ^ (c.w ^ k1), (uint32_t)p0);
+        else
+            c = make_uint4(xor3(h1, c.y, k0), (uint32_t)p1, xor3(h0, c.w, k1), (uint32_t)p0);
     }
     return c;
 }
@@ -80,49 +119,17 @@ __device__ __forceinline__ uint32_t fast_div(uint32_t x, Divisor d) {
     return d.m ? (__umulhi(x, d.m) >> d.s) : (x >> d.s);
 }
 
-// Classes (n_s, n_t) whose flip can raise the energy (dE > 0), for the three
-// orderings of the two couplings; every other class has dE <= 0 and is
-// always accepted.  Regime 0: kp > 2k, 1: k < kp <= 2k, 2: kp <= k.
-template <int R> struct Classes;
-template <> struct Classes<0> {
-    static constexpr int n = 7;
-    static constexpr int ns[7] = {0, 1, 2, 3, 4, 0, 1};
-    static constexpr int nt[7] = {0, 0, 0, 0, 0, 1, 1};
-};
-template <> struct Classes<1> {
-    static constexpr int n = 7;
-    static constexpr int ns[7] = {0, 1, 2, 3, 0, 1, 0};
-    static constexpr int nt[7] = {0, 0, 0, 0, 1, 1, 2};
-};
-template <> struct Classes<2> {
-    static constexpr int n = 7;
-    static constexpr int ns[7] = {0, 1, 2, 0, 1, 0, 1};
-    static constexpr int nt[7] = {0, 0, 0, 1, 1, 2, 2};
-};
-template <> struct Classes<3> {  // any table: all fifteen classes
-    static constexpr int n = 15;
-    static constexpr int ns[15] = {0, 0, 0, 1, 1, 1, 2, 2, 2, 3, 3, 3, 4, 4, 4};
-    static constexpr int nt[15] = {0, 1, 2, 0, 1, 2, 0, 1, 2, 0, 1, 2, 0, 1, 2};
-};
-
-__device__ __forceinline__ uint64_t all_if(uint32_t v, uint32_t bit) {
-    return 0ull - (uint64_t)((v >> bit) & 1u);  // block-uniform 0 or ~0
-}
-
 // Three-input bitwise operation of gfx950 (v_bitop3_b32); the immediate is
 // the truth table f(0xF0, 0xCC, 0xAA) of the operand order (a, b, c).
 #define BITOP3(a, b, c, table) __builtin_amdgcn_bitop3_b32((a), (b), (c), (table))
-constexpr int kAndOr = 0xEA;      // (a & b) | c
-constexpr int kAndAndNot = 0x40;  // a & b & ~c
 constexpr int kAndXnor = 0x90;    // a & ~(b ^ c)
 constexpr int kXor3 = 0x96;       // a ^ b ^ c
 constexpr int kMajority = 0xE8;   // at least two of a, b, c
 constexpr int kXorAnd = 0x78;     // a ^ (b & c)
+constexpr int kXorAndNot = 0xB4;  // a ^ (b & ~c)
 constexpr int kSelect = 0xCA;     // a ? b : c (bitwise)
 constexpr int kAnd3 = 0x80;       // a & b & c
-constexpr int kAndNotAnd = 0x20;  // a & ~b & c
-constexpr int kNor3 = 0x01;       // ~(a | b | c)
-constexpr int kEqEq = 0x81;       // a == b and a == c
+constexpr int kNotEq3 = 0x7E;     // not (a == b and a == c)
 constexpr int kNeNe = 0x18;       // a != b and a != c
 
 template <int T>
@@ -131,34 +138,27 @@ __device__ __forceinline__ uint64_t bop3(uint64_t a, uint64_t b, uint64_t c) {
                  BITOP3((uint32_t)(a >> 32), (uint32_t)(b >> 32), (uint32_t)(c >> 32), T));
 }
 
-// Per-word state of the comparison: the class planes it needs (bit-sliced
-// n_s = s2 s1 s0 and one-hot planes of n_t = 0, 1, 2), the lanes accepted so
-// far and the lanes still undecided.
-struct WordState {
+// A word under update: site, centre word, the class code of every lane as
+// three bit planes (code = p2 p1 p0, see class_code) and the lanes the
+// comparison still has to decide (at first those whose flip can raise the
+// energy).
+struct Word {
     uint32_t s;  // flat site index (RNG counter word 0)
-    uint64_t w;  // centre word before the update
-    uint64_t s0, s1, s2, nt0, nt1, nt2;
-    uint64_t acc, und;
+    uint64_t w;  // centre word, accepted lanes already flipped
+    uint64_t p0, p1, p2;
+    uint64_t und;
 };
 
-// LDS of a colour-pass block.  At the start of a call every thread writes
-// its word's site, centre word and class planes to its own slot (the n_t = 1
-// plane is not stored: the three n_t planes are one-hot), so they need not
-// stay in registers through the comparison.  Words still undecided after
-// the first levels are queued as (owner thread, accepted, undecided lanes)
-// and finished by as few waves as possible, reading the rest from the
-// owner's slot.  Two pairs of counters alternate between consecutive calls
-// of a block: a slow thread may still be reading the previous call's count
-// after a fast one has cleared the counters for the next call.
+// LDS of a colour-pass block: the words still undecided after the first
+// levels, packed by all threads of the block and finished by as few waves as
+// possible.  Two pairs of counters alternate between consecutive calls of a
+// block: a slow thread may still be reading the previous call's count after
+// a fast one has cleared the counters for the next call.
 struct SweepQueue {
     uint32_t count[4];
-    // per-thread slots
     uint32_t s[kSweepBlock];
-    uint64_t w[kSweepBlock], s0[kSweepBlock], s1[kSweepBlock], s2[kSweepBlock];
-    uint64_t nt0[kSweepBlock], nt2[kSweepBlock];
-    // queue entries
-    uint32_t owner[kSweepBlock];
-    uint64_t acc[kSweepBlock], und[kSweepBlock];
+    uint64_t w[kSweepBlock], p0[kSweepBlock], p1[kSweepBlock], p2[kSweepBlock];
+    uint64_t und[kSweepBlock];
 };
 
 
@@ -182,13 +182,72 @@ __device__ __forceinline__ void store64(uint64_t* base, uint32_t i, uint64_t v) 
         base[i] = v;
 }
 
-// Site (x, y, tau): its six neighbours and four couplings, the unsatisfied
-// bonds and their bit-sliced counts.
+// Unsatisfied space bonds u = w ^ neighbour ^ coupling of a word, counted per
+// lane: n_s = s2 s1 s0, a full adder over u1..u3, then u4 added to its sum.
+struct SpaceCount {
+    uint64_t s0, s1, s2;
+};
+__device__ __forceinline__ SpaceCount count_space(uint64_t w, uint64_t nxp, uint64_t nxm,
+                                                  uint64_t nyp, uint64_t nym, uint64_t jxp,
+                                                  uint64_t jxm, uint64_t jyp, uint64_t jym) {
+    const uint64_t u1 = bop3<kXor3>(w, nxp, jxp), u2 = bop3<kXor3>(w, nxm, jxm);
+    const uint64_t u3 = bop3<kXor3>(w, nyp, jyp), u4 = bop3<kXor3>(w, nym, jym);
+    const uint64_t sum = bop3<kXor3>(u1, u2, u3), carry = bop3<kMajority>(u1, u2, u3);
+    return {sum ^ u4, bop3<kXorAnd>(carry, sum, u4), bop3<kAnd3>(carry, sum, u4)};
+}
+
+// Class codes.  A flip can raise the energy (dE > 0) in at most seven of the
+// fifteen classes (n_s, n_t), and which seven depends only on the ordering of
+// the two couplings (the regime; every other class is accepted outright):
+//   regime 0 (kp > 2k):        n_t = 0: n_s = 0..4;  n_t = 1: n_s = 0, 1
+//   regime 1 (k < kp <= 2k):   n_t = 0: n_s = 0..3;  n_t = 1: n_s = 0, 1;  n_t = 2: n_s = 0
+//   regime 2 (kp <= k):        n_t = 0: n_s = 0..2;  n_t = 1, 2: n_s = 0, 1
+// Three planes number the seven classes 0..6 (kClassCode of the host lists
+// the same codes), so that any function of the class, such as the threshold
+// bits of one level, is one three-input operation on them.  und: the lanes
+// in one of the seven classes; the codes of the others are not used.
+__device__ __forceinline__ Word class_code(uint32_t regime, uint32_t s, uint64_t w,
+                                           const SpaceCount& n, uint64_t above, uint64_t below) {
+    Word r;
+    r.s = s;
+    r.w = w;
+    const uint64_t nt1 = above ^ below;
+    const uint64_t some = bop3<kNotEq3>(w, above, below);  // n_t > 0
+    if (regime == 0) {  // n_t = 0: n_s; n_t = 1: 5 + n_s
+        asm volatile("");  // a block-uniform branch, not a select of both sides
+        r.p0 = n.s0 ^ nt1;
+        r.p1 = bop3<kSelect>(nt1, n.s0, n.s1);
+        r.p2 = n.s2 | nt1;
+        r.und = bop3<0x04>(n.s2, nt1, n.s1) | ~some;  // n_t = 1: n_s < 2
+    } else {
+        const uint64_t nt2 = bop3<kNeNe>(w, above, below);
+        r.p0 = n.s0;
+        r.p1 = n.s1 | nt2;
+        if (regime == 1) {  // n_t = 0: n_s; n_t = 1: 4 + n_s; n_t = 2: 6
+            asm volatile("");
+            r.p2 = some;
+            r.und = bop3<0x0B>(n.s2, some, bop3<0x07>(n.s1, nt2, n.s0));
+        } else {            // n_t = 0: 4 + n_s; n_t = 1: n_s; n_t = 2: 2 + n_s
+            r.p2 = ~some;
+            r.und = bop3<0x1F>(n.s1, n.s0, some) & ~n.s2;
+        }
+    }
+    return r;
+}
+
+
+// Load the neighbourhood of colour-c word `idx` of a slot.  Colour-c words of
+// a slot are numbered plane by plane, row by row: idx = tau*(L*L/2) +
+// y*(L/2) + xh, x = 2*xh + ((c + y + tau) & 1).
 template <bool kGlobal>
-__device__ __forceinline__ WordState load_site(const GroupDev& G, const uint64_t* __restrict__ S,
-                                               uint32_t x, uint32_t y, uint32_t tau) {
+__device__ __forceinline__ Word load_word(const GroupDev& G, const uint64_t* __restrict__ S,
+                                          uint32_t regime, uint32_t colour, uint32_t idx) {
     const uint32_t L = G.L;
     const uint32_t P = L * L;
+    const uint32_t tau = fast_div(idx, G.div_half_plane);
+    const uint32_t rem = idx - tau * (P >> 1);
+    const uint32_t y = fast_div(rem, G.div_half_row);
+    const uint32_t x = 2 * (rem - y * (L >> 1)) + ((colour + y + tau) & 1u);
     const uint32_t xp = (x + 1 == L) ? 0 : x + 1;
     const uint32_t xm = (x == 0) ? L - 1 : x - 1;
     const uint32_t yp = (y + 1 == L) ? 0 : y + 1;
@@ -197,281 +256,188 @@ __device__ __forceinline__ WordState load_site(const GroupDev& G, const uint64_t
     const uint32_t tm = (tau == 0) ? G.Ltau - 1 : tau - 1;
     const uint32_t row = y * L;
     const uint32_t plane = tau * P;
-
-    WordState st;
-    st.s = plane + row + x;
-    const uint64_t w = load64<kGlobal>(S, st.s);
-    const uint64_t nxp = load64<kGlobal>(S, plane + row + xp);
-    const uint64_t nxm = load64<kGlobal>(S, plane + row + xm);
-    const uint64_t nyp = load64<kGlobal>(S, plane + yp * L + x);
-    const uint64_t nym = load64<kGlobal>(S, plane + ym * L + x);
-    const uint64_t ntp_raw = load64<kGlobal>(S, tp * P + row + x);
-    const uint64_t ntm_raw = load64<kGlobal>(S, tm * P + row + x);
-    const uint64_t jxp = load64<true>(G.Jx, row + x);
-    const uint64_t jxm = load64<true>(G.Jx, row + xm);  // the -x bond is the +x bond of x-1
-    const uint64_t jyp = load64<true>(G.Jy, row + x);
-    const uint64_t jym = load64<true>(G.Jy, ym * L + x);
-
-    // unsatisfied space bonds u = w ^ neighbour ^ coupling and their count
-    // n_s = s2 s1 s0: a full adder over u1..u3, then u4 added to its sum
-    const uint64_t u1 = bop3<kXor3>(w, nxp, jxp), u2 = bop3<kXor3>(w, nxm, jxm);
-    const uint64_t u3 = bop3<kXor3>(w, nyp, jyp), u4 = bop3<kXor3>(w, nym, jym);
-    const uint64_t sum = bop3<kXor3>(u1, u2, u3), carry = bop3<kMajority>(u1, u2, u3);
-    st.w = w;
-    st.s0 = sum ^ u4;
-    st.s1 = bop3<kXorAnd>(carry, sum, u4);
-    st.s2 = bop3<kAnd3>(carry, sum, u4);
-    // unsatisfied time bonds n_t as one-hot planes; on an antiperiodic prism
-    // the bond that wraps round tau counts with the opposite sign, which is
-    // the neighbour's word inverted
-    uint64_t ntp = ntp_raw, ntm = ntm_raw;
+    const uint32_t site = plane + row + x;
+    const uint64_t w = load64<kGlobal>(S, site);
+    const SpaceCount n = count_space(
+        w, load64<kGlobal>(S, plane + row + xp), load64<kGlobal>(S, plane + row + xm),
+        load64<kGlobal>(S, plane + yp * L + x), load64<kGlobal>(S, plane + ym * L + x),
+        load64<true>(G.Jx, row + x), load64<true>(G.Jx, row + xm),  // -x bond: the +x bond of x-1
+        load64<true>(G.Jy, row + x), load64<true>(G.Jy, ym * L + x));
+    uint64_t above = load64<kGlobal>(S, tp * P + row + x);
+    uint64_t below = load64<kGlobal>(S, tm * P + row + x);
+    // on an antiperiodic prism the bond that wraps round tau counts with the
+    // opposite sign, which is the neighbour's word inverted
     if (G.anti) {
         asm volatile("");  // a block-uniform branch: periodic groups skip this
-        if (tau + 1 == G.Ltau) ntp = ~ntp;
-        if (tau == 0) ntm = ~ntm;
+        if (tau + 1 == G.Ltau) above = ~above;
+        if (tau == 0) below = ~below;
     }
-    st.nt0 = bop3<kEqEq>(w, ntp, ntm);
-    st.nt1 = ntp ^ ntm;
-    st.nt2 = bop3<kNeNe>(w, ntp, ntm);
-    st.acc = 0;
-    st.und = 0;
-    return st;
+    return class_code(regime, site, w, n, above, below);
 }
 
-// Load the neighbourhood of colour-c word `idx` of a slot and count
-// unsatisfied bonds.  Colour-c words of a slot are numbered plane by plane,
-// row by row: idx = tau*(L*L/2) + y*(L/2) + xh, x = 2*xh + ((c + y + tau) & 1).
-template <bool kGlobal>
-__device__ __forceinline__ WordState load_word(const GroupDev& G, const uint64_t* __restrict__ S,
-                                               uint32_t colour, uint32_t idx) {
-    const uint32_t half_plane = (G.L * G.L) >> 1;
-    const uint32_t half_row = G.L >> 1;
-    const uint32_t tau = fast_div(idx, G.div_half_plane);
-    const uint32_t rem = idx - tau * half_plane;
-    const uint32_t y = fast_div(rem, G.div_half_row);
-    const uint32_t x = 2 * (rem - y * half_row) + ((colour + y + tau) & 1u);
-    return load_site<kGlobal>(G, S, x, y, tau);
+// Threshold plane T of one level: bit j = the level's threshold bit of lane
+// j's class, a function of the three code planes and so one v_bitop3 per
+// 32-lane half.  That instruction takes its truth table as an immediate
+// while the table differs from slot to slot and level to level, so there is
+// one handler per table (128: code 7 does not occur) and the level jumps to
+// its own: the two operations and a branch to the end, kHandlerBytes apart.
+// Combining one-hot class masks under uniform branches instead took seven
+// vector and fourteen scalar instructions a level and held fourteen registers
+// of masks: 3089 vector instructions a wave of eight words and 5.6 waves a
+// SIMD, now 2432 and 7.5, 783 -> 621 us a pass on 2 x 48 slots of 24 x 24 x
+// 2048.  (Handlers that also hold the comparison, 64 bytes each, took 3 %
+// longer: more instruction fetches.)  `entry`: byte offset of the handler from the instruction after
+// s_getpc (the host stores it per slot and level, see level_entry); masked
+// so that no value can leave the handlers.
+__device__ __forceinline__ uint64_t threshold_plane(uint32_t entry, const Word& r) {
+    static_assert(kHandlerBytes == 32 && kHandlerSkip == 12, "handlers below are laid out so");
+    uint32_t T_lo, T_hi;
+    asm("s_getpc_b64 vcc\n"
+        "s_add_u32 vcc_lo, vcc_lo, %[e]\n"
+        "s_addc_u32 vcc_hi, vcc_hi, 0\n"
+        "s_setpc_b64 vcc\n"
+        ".set .Lqsg_t%=, 0\n"
+        ".rept 128\n"
+        "v_bitop3_b32 %[tl], %[cl], %[bl], %[al] bitop3:.Lqsg_t%=\n"
+        "v_bitop3_b32 %[th], %[ch], %[bh], %[ah] bitop3:.Lqsg_t%=\n"
+        "s_branch .Lqsg_end%=\n"
+        "s_nop 0\n"
+        "s_nop 0\n"
+        "s_nop 0\n"
+        ".set .Lqsg_t%=, .Lqsg_t%= + 1\n"
+        ".endr\n"
+        ".Lqsg_end%=:\n"
+        : [tl] "=&v"(T_lo), [th] "=&v"(T_hi)
+        : [e] "s"(entry & kEntryMask), [al] "v"((uint32_t)r.p0), [ah] "v"((uint32_t)(r.p0 >> 32)),
+          [bl] "v"((uint32_t)r.p1), [bh] "v"((uint32_t)(r.p1 >> 32)), [cl] "v"((uint32_t)r.p2),
+          [ch] "v"((uint32_t)(r.p2 >> 32))
+        : "vcc", "scc");
+    return lo_hi(T_lo, T_hi);
 }
-
-// One-hot masks of the listed classes and the slot's thresholds for them.
-template <int R>
-__device__ __forceinline__ void class_masks(const WordState& st, const uint32_t* __restrict__ thr,
-                                            uint64_t (&M)[Classes<R>::n],
-                                            uint32_t (&th)[Classes<R>::n]) {
-    using C = Classes<R>;
-    const uint64_t NT[3] = {st.nt0, st.nt1, st.nt2};
-    const uint64_t ns0 = bop3<kNor3>(st.s2, st.s1, st.s0);
-#pragma unroll
-    for (int i = 0; i < C::n; ++i) {
-        th[i] = __builtin_amdgcn_readfirstlane(thr[C::ns[i] * 3 + C::nt[i]]);
-        const uint64_t nt = NT[C::nt[i]];
-        // n_s <= 4, so s0 & ~s1 means 1, s1 & ~s0 means 2, s1 & s0 means 3
-        switch (C::ns[i]) {
-            case 0: M[i] = ns0 & nt; break;
-            case 1: M[i] = bop3<kAndNotAnd>(st.s0, st.s1, nt); break;
-            case 2: M[i] = bop3<kAndNotAnd>(st.s1, st.s0, nt); break;
-            case 3: M[i] = bop3<kAnd3>(st.s1, st.s0, nt); break;
-            default: M[i] = st.s2 & nt; break;
-        }
-        if (R == 3) M[i] &= ~all_if(th[i] == 0xFFFFFFFFu ? 1u : 0u, 0);
-    }
-}
-
 
 // Compare the lanes' bit-sliced Philox numbers with their class thresholds,
 // most significant level first, for blocks q0 <= q < q1 while any lane of
 // the wave is undecided.  Block q (counter (s, t, g<<4 | q, gid)) carries
 // levels 2q and 2q+1.  Per level, on each 32-bit half, with T the plane of
 // the lanes' threshold bits and W the level of the random numbers:
-//   acc |= und & T & ~W   (r has 0 where thr has 1: r < thr, accepted)
+//   acc = und ? T : acc   (a lane decided here has T != W: accepted iff T = 1)
 //   und &= ~(T ^ W)       (still equal so far).
-// Regimes 0-2 build T from the slot's level pick: a block-uniform branch per
-// class skips the classes outside it, so at most three masks are combined;
-// the class masks are disjoint, so T = inv ^ (xor of the picked masks), with
-// inv = ~0 for a complemented pick, is exact on every lane still undecided.
-// Regime 3 (any table) ORs all fifteen masks, each ANDed with its bit.
-template <int R>
+// So acc holds the decision of every lane once it has left und; on lanes
+// still in und it is meaningless.
 __device__ __forceinline__ void compare_levels(const GroupDev& G, uint32_t g, uint32_t t,
-                                               uint32_t s, const uint64_t (&M)[Classes<R>::n],
-                                               const uint32_t (&th)[Classes<R>::n],
-                                               const uint32_t* thr, uint32_t q0,
-                                               uint32_t q1, uint64_t& acc, uint64_t& und,
-                                               uint32_t unchecked = 0) {
-    using C = Classes<R>;
-    uint32_t acc_lo = (uint32_t)acc, acc_hi = (uint32_t)(acc >> 32);
-    uint32_t und_lo = (uint32_t)und, und_hi = (uint32_t)(und >> 32);
-    // the slot's level picks (two bytes per block, see kLevelPicks), read
-    // through the constant address space: block-uniform scalar loads (the
-    // table is not written during a launch)
+                                               const uint32_t* entries, const Word& r, uint32_t q0,
+                                               uint32_t q1, uint64_t& acc, uint64_t& und) {
+    // the slot's handler entries (two levels to a word), read through the
+    // constant address space: block-uniform scalar loads (the table is not
+    // written during a launch)
     typedef const uint32_t __attribute__((address_space(4)))* ConstU32;
-    const ConstU32 pk = (ConstU32)(thr);
+    const ConstU32 en = (ConstU32)(entries);
+    const PhiloxSite ps = philox_site(r.s, G.gid, G.key1);
 #pragma unroll 1
     for (uint32_t q = q0; q < q1; ++q) {
-        // every lane of the wave decided: stop (not checked for the first
-        // `unchecked` blocks, where that almost never happens; a block run
-        // on decided lanes changes nothing)
-        if (q >= q0 + unchecked && !__any((und_lo | und_hi) != 0)) break;
-        const uint4 o = philox(make_uint4(s, t, (g << 4) | q, G.gid), G.key0, G.key1);
-        const uint32_t lev_lo[2] = {o.x, o.z};
-        const uint32_t lev_hi[2] = {o.y, o.w};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            uint32_t T_lo = 0, T_hi = 0;
-            if (R < 3) {
-                const uint32_t pick = (pk[kLevelPicks + (q >> 1)] >> (16 * (q & 1u) + 8 * h)) & 0xFFu;
-                T_lo = T_hi = 0u - (pick >> 7);
-#pragma unroll
-                for (int i = 0; i < C::n; ++i) {
-                    if (pick & (1u << i)) {
-                        asm volatile("");  // keep the uniform branch: no select of both sides
-                        T_lo ^= (uint32_t)M[i];
-                        T_hi ^= (uint32_t)(M[i] >> 32);
-                    }
-                }
-            } else {
-                const uint32_t bit = 31u - (2u * q + (uint32_t)h);
-#pragma unroll
-                for (int i = 0; i < C::n; ++i) {
-                    const uint32_t B = 0u - ((th[i] >> bit) & 1u);  // block-uniform 0 or ~0
-                    T_lo = BITOP3((uint32_t)M[i], B, T_lo, kAndOr);
-                    T_hi = BITOP3((uint32_t)(M[i] >> 32), B, T_hi, kAndOr);
-                }
-            }
-            acc_lo |= BITOP3(und_lo, T_lo, lev_lo[h], kAndAndNot);
-            acc_hi |= BITOP3(und_hi, T_hi, lev_hi[h], kAndAndNot);
-            und_lo = BITOP3(und_lo, T_lo, lev_lo[h], kAndXnor);
-            und_hi = BITOP3(und_hi, T_hi, lev_hi[h], kAndXnor);
-        }
+        if (!__any(und != 0)) break;  // every lane of the wave decided
+        const uint32_t e = en[q];
+        const uint4 o = philox_block(ps, t, (g << 4) | q, G.key0, G.key1);
+        uint64_t T = threshold_plane(e, r);
+        acc = bop3<kSelect>(und, T, acc);
+        und = bop3<kAndXnor>(und, T, lo_hi(o.x, o.y));
+        T = threshold_plane(e >> 16, r);
+        acc = bop3<kSelect>(und, T, acc);
+        und = bop3<kAndXnor>(und, T, lo_hi(o.z, o.w));
     }
-    acc = lo_hi(acc_lo, acc_hi);
-    und = lo_hi(und_lo, und_hi);
 }
 
-__device__ __forceinline__ void put_slot(SweepQueue& Q, uint32_t o, const WordState& st) {
-    Q.s[o] = st.s;
-    Q.w[o] = st.w;
-    Q.s0[o] = st.s0;
-    Q.s1[o] = st.s1;
-    Q.s2[o] = st.s2;
-    Q.nt0[o] = st.nt0;
-    Q.nt2[o] = st.nt2;
-}
-
-__device__ __forceinline__ void push_word(SweepQueue& Q, uint32_t k, uint32_t owner, uint64_t acc,
+// Queue a word: w with the lanes accepted so far flipped.
+__device__ __forceinline__ void push_word(SweepQueue& Q, uint32_t k, const Word& r, uint64_t w,
                                           uint64_t und) {
-    Q.owner[k] = owner;
-    Q.acc[k] = acc;
+    Q.s[k] = r.s;
+    Q.w[k] = w;
+    Q.p0[k] = r.p0;
+    Q.p1[k] = r.p1;
+    Q.p2[k] = r.p2;
     Q.und[k] = und;
 }
 
-// Entry k of the queue with its owner's slot.
-__device__ __forceinline__ WordState pop_word(const SweepQueue& Q, uint32_t k, uint32_t& owner) {
-    WordState r;
-    const uint32_t o = Q.owner[k];
-    owner = o;
-    r.s = Q.s[o];
-    r.w = Q.w[o];
-    r.s0 = Q.s0[o];
-    r.s1 = Q.s1[o];
-    r.s2 = Q.s2[o];
-    r.nt0 = Q.nt0[o];
-    r.nt2 = Q.nt2[o];
-    r.nt1 = ~(r.nt0 | r.nt2);
-    r.acc = Q.acc[k];
-    r.und = Q.und[k];
-    return r;
-}
-
-// The comparison of one word from level block q to the end (16 blocks, all
-// 32 bits), then its update.
-template <int R, bool kGlobal>
-__device__ __forceinline__ void finish_word(const GroupDev& G, uint64_t* __restrict__ S, uint32_t g,
-                                            uint32_t t, WordState r, uint32_t q) {
-    using C = Classes<R>;
-    const uint32_t* __restrict__ thr = G.thr + g * kThrStride;
-    uint64_t M[C::n];
-    uint32_t th[C::n];
-    class_masks<R>(r, thr, M, th);
-    compare_levels<R>(G, g, t, r.s, M, th, thr, q, 16, r.acc, r.und);
-    r.acc |= r.und;  // equal on all 32 bits: r == thr, accepted
-    if (r.acc) store64<kGlobal>(S, r.s, r.w ^ r.acc);
+__device__ __forceinline__ Word pop_word(const SweepQueue& Q, uint32_t k) {
+    return {Q.s[k], Q.w[k], Q.p0[k], Q.p1[k], Q.p2[k], Q.und[k]};
 }
 
 // The colour-pass update of one word per thread of the block: the first
-// q_split Philox blocks of levels for every word; then, while the words with
-// undecided lanes fill more than one wave, they are packed into the first
-// waves of the block and given one more block; the last ones (at most one
-// wave) are finished there.  Far fewer waves run the long tail of levels.
-// Every thread of the block calls this (it synchronises); `valid` is false
-// for threads without a word (st is then unused).  Packing counters: one
-// pair per call parity (see SweepQueue); within a call, round j writes
+// G.q_split Philox blocks of levels for every word; then, while the words
+// with undecided lanes fill more than one wave, they are packed into the
+// first waves of the block and given one more block; the last ones (at most
+// one wave) are finished there.  Far fewer waves run the long tail of
+// levels.  Every thread of the block calls this (it synchronises); `valid`
+// is false for threads without a word (r is then unused).  Packing counters:
+// one pair per call parity (see SweepQueue); within a call, round j writes
 // counter j & 1, which round j - 1 cleared after every thread had read its
 // previous value.
-template <int R, bool kGlobal>
+template <bool kGlobal>
 __device__ __forceinline__ void sweep_words(const GroupDev& G, uint64_t* __restrict__ S, uint32_t g,
-                                            uint32_t t, WordState st, bool valid, uint32_t q_split,
-                                            SweepQueue& Q, uint32_t parity) {
-    using C = Classes<R>;
-    const uint32_t* __restrict__ thr = G.thr + g * kThrStride;
+                                            uint32_t t, const Word& r, bool valid, SweepQueue& Q,
+                                            uint32_t parity) {
+    const uint32_t* entries = G.thr + g * kThrStride + kLevelEntries;
     uint32_t* cnt = Q.count + 2 * (parity & 1u);
     if (threadIdx.x == 0) {
         cnt[0] = 0;
         cnt[1] = 0;
     }
     __syncthreads();
-    uint64_t M[C::n];
-    uint32_t th[C::n];
     if (valid) {
-        put_slot(Q, threadIdx.x, st);
-        class_masks<R>(st, thr, M, th);
-        uint64_t live = 0;
-#pragma unroll
-        for (int i = 0; i < C::n; ++i) live |= M[i];
-        st.acc = ~live;  // lanes outside the listed classes: dE <= 0, accepted
-        st.und = live;
-        compare_levels<R>(G, g, t, st.s, M, th, thr, 0, q_split, st.acc, st.und, 0);
-        if (st.und != 0)
-            push_word(Q, atomicAdd(&cnt[0], 1u), threadIdx.x, st.acc, st.und);
-        else if (st.acc)
-            store64<kGlobal>(S, st.s, st.w ^ st.acc);
+        uint64_t acc = ~r.und;  // lanes outside the seven classes: dE <= 0, accepted
+        uint64_t und = r.und;
+        compare_levels(G, g, t, entries, r, 0, G.q_split, acc, und);
+        const uint64_t w = bop3<kXorAndNot>(r.w, acc, und);
+        if (und != 0)
+            push_word(Q, atomicAdd(&cnt[0], 1u), r, w, und);
+        else
+            store64<kGlobal>(S, r.s, w);
     }
     __syncthreads();
     uint32_t n = __builtin_amdgcn_readfirstlane(cnt[0]);
-    uint32_t q = q_split;
+    uint32_t q = G.q_split;
 #pragma unroll 1
-    for (uint32_t j = 1; n > kWaveSize && q + 1 < 16; ++j, ++q) {
+    for (uint32_t j = 1; n != 0; ++j) {
+        // the last words are finished where they sit in the queue: all 32
+        // bits, and a lane equal on every one of them has r == thr, accepted
+        const bool last = n <= kWaveSize || q + 1 >= 16;
+        const uint32_t q1 = last ? 16 : q + 1;
         const bool have = threadIdx.x < n;
-        WordState r;
-        uint32_t owner = 0;
-        if (have) r = pop_word(Q, threadIdx.x, owner);
-        __syncthreads();  // every entry and count read before any is rewritten
-        if (threadIdx.x == 0) cnt[(j + 1) & 1u] = 0;
-        if (have) {
-            class_masks<R>(r, thr, M, th);
-            compare_levels<R>(G, g, t, r.s, M, th, thr, q, q + 1, r.acc, r.und);
-            if (r.und != 0)
-                push_word(Q, atomicAdd(&cnt[j & 1u], 1u), owner, r.acc, r.und);
-            else if (r.acc)
-                store64<kGlobal>(S, r.s, r.w ^ r.acc);
+        Word e;
+        if (have) e = pop_word(Q, threadIdx.x);
+        if (!last) {
+            __syncthreads();  // every entry and count read before any is rewritten
+            if (threadIdx.x == 0) cnt[(j + 1) & 1u] = 0;
         }
+        if (have) {
+            uint64_t acc = 0, und = e.und;
+            compare_levels(G, g, t, entries, e, q, q1, acc, und);
+            const uint64_t w = bop3<kXorAndNot>(e.w, acc, und);
+            if (last)
+                store64<kGlobal>(S, e.s, w ^ und);
+            else if (und != 0)
+                push_word(Q, atomicAdd(&cnt[j & 1u], 1u), e, w, und);
+            else
+                store64<kGlobal>(S, e.s, w);
+        }
+        if (last) break;
         __syncthreads();
         n = __builtin_amdgcn_readfirstlane(cnt[j & 1u]);
-    }
-    // the last words are finished where they sit in the queue
-    if (threadIdx.x < n) {
-        uint32_t owner;
-        finish_word<R, kGlobal>(G, S, g, t, pop_word(Q, threadIdx.x, owner), q);
+        q = q1;
     }
 }
 
 // One word per thread, numbered as in load_word (the fused chunk kernel).
-template <int R, bool kGlobal>
+// S: the slot's spins (global memory, or a copy in LDS).  parity: alternate
+// 0/1 between consecutive calls in one block.
+template <bool kGlobal>
 __device__ __forceinline__ void sweep_block(const GroupDev& G, uint64_t* __restrict__ S, uint32_t g,
                                             uint32_t colour, uint32_t t, uint32_t idx, bool valid,
-                                            uint32_t q_split, SweepQueue& Q, uint32_t parity) {
-    WordState st{};
-    if (valid) st = load_word<kGlobal>(G, S, colour, idx);
-    sweep_words<R, kGlobal>(G, S, g, t, st, valid, q_split, Q, parity);
+                                            SweepQueue& Q, uint32_t parity) {
+    const uint32_t regime = __builtin_amdgcn_readfirstlane(G.thr[g * kThrStride + 15]);
+    Word r{};
+    if (valid) r = load_word<kGlobal>(G, S, regime, colour, idx);
+    sweep_words<kGlobal>(G, S, g, t, r, valid, Q, parity);
 }
 
 // Column walk: thread `item` of a slot owns column (x, y) = item mod L^2 of
@@ -479,9 +445,9 @@ __device__ __forceinline__ void sweep_block(const GroupDev& G, uint64_t* __restr
 // colour-c sites there are tau = tau0 + par, tau0 + par + 2, ..., with
 // par = (c + x + y) & 1, one per step.  Offsets of the centre and its four
 // space neighbours are fixed for the walk and the slot base advances by two
-// planes per step (a block-uniform address on the scalar unit), the four
-// couplings are loaded once, and the word below the centre is the previous
-// step's word above it, so a step costs six loads and no index arithmetic.
+// planes per step (a block-uniform address on the scalar unit), the word
+// below the centre is the previous step's word above it, so a step costs six
+// spin loads, four coupling loads (cache hits) and no index arithmetic.
 // Only the first step's lower neighbour and the last step's upper one can
 // wrap round tau.
 __device__ __forceinline__ uint64_t load_at(const uint64_t* base, uint32_t byte_off) {
@@ -499,10 +465,11 @@ __device__ __forceinline__ T* scalar_ptr(T* p) {
     return (T*)(uintptr_t)lo_hi(lo, hi);
 }
 
-template <int R>
 __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restrict__ S, uint32_t g,
-                                           uint32_t colour, uint32_t t, uint32_t item, bool valid,
-                                           SweepQueue& Q) {
+                                           uint32_t colour, uint32_t t, uint32_t item,
+                                           uint32_t n_items, SweepQueue& Q) {
+    const bool valid = item < n_items;
+    const uint32_t regime = __builtin_amdgcn_readfirstlane(G.thr[g * kThrStride + 15]);
     const uint32_t L = G.L, P = L * L, Ltau = G.Ltau;
     const uint32_t steps = G.tile >> 1;
     uint32_t tile = 0, col = 0;
@@ -546,11 +513,9 @@ __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restri
         // offset addressing), not 64-bit addresses hoisted out of it
         asm volatile("" : "+v"(o_c), "+v"(o_xp), "+v"(o_xm), "+v"(o_yp), "+v"(o_ym), "+v"(o_tp));
         asm volatile("" : "+v"(j_c), "+v"(j_xm), "+v"(j_ym));
-        WordState st;
+        Word r;
         if (valid) {
             const uint64_t w = load_at(Sk, o_c);
-            const uint64_t nxp = load_at(Sk, o_xp), nxm = load_at(Sk, o_xm);
-            const uint64_t nyp = load_at(Sk, o_yp), nym = load_at(Sk, o_ym);
             uint64_t above;
             if (k + 1 == steps && tau0 + 2 * k + 1 == Ltau) {  // top slice: wraps to slice 0
                 above = load64<true>(S, row + x);
@@ -558,59 +523,15 @@ __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restri
             } else {
                 above = load_at(Sk, o_tp);
             }
-            st.s = site0 + 2 * k * P;
-            const uint64_t jxp = load_at(Jx, j_c);
-            const uint64_t jxm = load_at(Jx, j_xm);  // the -x bond is the +x bond of x-1
-            const uint64_t jyp = load_at(Jy, j_c);
-            const uint64_t jym = load_at(Jy, j_ym);
-            const uint64_t u1 = bop3<kXor3>(w, nxp, jxp), u2 = bop3<kXor3>(w, nxm, jxm);
-            const uint64_t u3 = bop3<kXor3>(w, nyp, jyp), u4 = bop3<kXor3>(w, nym, jym);
-            const uint64_t sum = bop3<kXor3>(u1, u2, u3), carry = bop3<kMajority>(u1, u2, u3);
-            st.w = w;
-            st.s0 = sum ^ u4;
-            st.s1 = bop3<kXorAnd>(carry, sum, u4);
-            st.s2 = bop3<kAnd3>(carry, sum, u4);
-            st.nt0 = bop3<kEqEq>(w, above, below);
-            st.nt1 = above ^ below;
-            st.nt2 = bop3<kNeNe>(w, above, below);
+            const SpaceCount n =
+                count_space(w, load_at(Sk, o_xp), load_at(Sk, o_xm), load_at(Sk, o_yp),
+                            load_at(Sk, o_ym), load_at(Jx, j_c),
+                            load_at(Jx, j_xm),  // the -x bond is the +x bond of x-1
+                            load_at(Jy, j_c), load_at(Jy, j_ym));
+            r = class_code(regime, site0 + 2 * k * P, w, n, above, below);
             below = above;
         }
-        sweep_words<R, true>(G, S, g, t, st, valid, G.q_split, Q, k);
-    }
-}
-// S: the slot's spins (global memory, or a copy in LDS).
-// parity: alternate 0/1 between consecutive calls in one block.
-template <bool kGlobal>
-__device__ __forceinline__ void sweep_block_any(const GroupDev& G, uint64_t* S, uint32_t g,
-                                                uint32_t colour, uint32_t t, uint32_t idx,
-                                                bool valid, uint32_t q_split, SweepQueue& Q,
-                                                uint32_t parity) {
-    switch (__builtin_amdgcn_readfirstlane(G.thr[g * kThrStride + 15])) {  // slot g's regime
-        case 0: sweep_block<0, kGlobal>(G, S, g, colour, t, idx, valid, q_split, Q, parity); break;
-        case 1: sweep_block<1, kGlobal>(G, S, g, colour, t, idx, valid, q_split, Q, parity); break;
-        case 2: sweep_block<2, kGlobal>(G, S, g, colour, t, idx, valid, q_split, Q, parity); break;
-        default: sweep_block<3, kGlobal>(G, S, g, colour, t, idx, valid, q_split, Q, parity); break;
-    }
-}
-
-// Slots whose tables fit none of the three seven-class regimes (never the
-// case for the tables of either ladder kind, whose couplings are positive)
-// take the fifteen-class update one word per thread, without the walk's
-// registers: thread `item` updates colour-c words item, item + n, ... with
-// n = V / tile threads per slot.
-__device__ __forceinline__ void walk_block_any(const GroupDev& G, uint64_t* S, uint32_t g,
-                                               uint32_t colour, uint32_t t, uint32_t item,
-                                               uint32_t n_items, SweepQueue& Q) {
-    const bool valid = item < n_items;
-    switch (__builtin_amdgcn_readfirstlane(G.thr[g * kThrStride + 15])) {  // slot g's regime
-        case 0: walk_block<0>(G, S, g, colour, t, item, valid, Q); break;
-        case 1: walk_block<1>(G, S, g, colour, t, item, valid, Q); break;
-        case 2: walk_block<2>(G, S, g, colour, t, item, valid, Q); break;
-        default:
-#pragma unroll 1
-            for (uint32_t k = 0; k < (G.tile >> 1); ++k)
-                sweep_block<3, true>(G, S, g, colour, t, item + k * n_items, valid, G.q_split, Q, k);
-            break;
+        sweep_words<true>(G, S, g, t, r, valid, Q, k);
     }
 }
 
@@ -632,7 +553,7 @@ k_half_sweep(const GroupDev G, uint32_t colour, const uint32_t* __restrict__ ctr
     const uint32_t b = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const uint32_t g = fast_div(b, G.div_blocks);  // b / gridDim.x on the scalar unit
     const uint32_t item = (b - g * gridDim.x) * kSweepBlock + threadIdx.x;
-    walk_block_any(G, G.spins + (size_t)g * G.V, g, colour, t, item, G.V >> __builtin_ctz(G.tile), Q);
+    walk_block(G, G.spins + (size_t)g * G.V, g, colour, t, item, G.V >> __builtin_ctz(G.tile), Q);
 }
 
 __device__ __forceinline__ uint32_t find_group(const uint32_t* __restrict__ prefix,
@@ -723,7 +644,7 @@ k_half_sweep_batched(const BatchPlan plan, uint32_t colour, const uint32_t* __re
     const uint32_t nb = sweep_blocks_per_slot(G.V, G.tile);
     const uint32_t g = fast_div(local, G.div_blocks);  // local / nb on the scalar unit
     const uint32_t item = (local - g * nb) * kSweepBlock + threadIdx.x;
-    walk_block_any(G, G.spins + (size_t)g * G.V, g, colour, t, item, G.V >> __builtin_ctz(G.tile), Q);
+    walk_block(G, G.spins + (size_t)g * G.V, g, colour, t, item, G.V >> __builtin_ctz(G.tile), Q);
 }
 
 // ---------------------------------------------------------------------------
@@ -754,7 +675,7 @@ k_chunk_fused(const BatchPlan slots, const uint32_t* __restrict__ ctr, uint32_t 
         for (uint32_t colour = 0; colour < 2; ++colour) {
             for (uint32_t base = 0; base < half; base += kSweepBlock) {
                 const uint32_t idx = base + threadIdx.x;
-                sweep_block_any<false>(G, S, g, colour, t0 + it, idx, idx < half, G.q_split, Q, call++);
+                sweep_block<false>(G, S, g, colour, t0 + it, idx, idx < half, Q, call++);
             }
             __syncthreads();  // the next colour reads what this one wrote
         }
