@@ -161,6 +161,10 @@ struct SweepQueue {
     uint64_t und[kSweepBlock];
 };
 
+// The four couplings of every thread's column (column walk).
+struct WalkCouplings {
+    uint64_t xp[kSweepBlock], xm[kSweepBlock], yp[kSweepBlock], ym[kSweepBlock];
+};
 
 // Spin and coupling words are addressed as base + 32-bit byte offset, so
 // global accesses keep the base in SGPRs and only the offset in a VGPR.  The
@@ -445,9 +449,11 @@ __device__ __forceinline__ void sweep_block(const GroupDev& G, uint64_t* __restr
 // colour-c sites there are tau = tau0 + par, tau0 + par + 2, ..., with
 // par = (c + x + y) & 1, one per step.  Offsets of the centre and its four
 // space neighbours are fixed for the walk and the slot base advances by two
-// planes per step (a block-uniform address on the scalar unit), the word
-// below the centre is the previous step's word above it, so a step costs six
-// spin loads, four coupling loads (cache hits) and no index arithmetic.
+// planes per step (a block-uniform address on the scalar unit), the four
+// couplings are loaded once into the thread's LDS slot (re-read from global
+// memory every step, they cost 5 % of the pass), and the word below the
+// centre is the previous step's word above it, so a step costs six loads and
+// no index arithmetic.
 // Only the first step's lower neighbour and the last step's upper one can
 // wrap round tau.
 __device__ __forceinline__ uint64_t load_at(const uint64_t* base, uint32_t byte_off) {
@@ -467,7 +473,7 @@ __device__ __forceinline__ T* scalar_ptr(T* p) {
 
 __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restrict__ S, uint32_t g,
                                            uint32_t colour, uint32_t t, uint32_t item,
-                                           uint32_t n_items, SweepQueue& Q) {
+                                           uint32_t n_items, SweepQueue& Q, WalkCouplings& J) {
     const bool valid = item < n_items;
     const uint32_t regime = __builtin_amdgcn_readfirstlane(G.thr[g * kThrStride + 15]);
     const uint32_t L = G.L, P = L * L, Ltau = G.Ltau;
@@ -491,8 +497,7 @@ __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restri
     uint32_t o_xp = (plane0 + row + xp) * 8u, o_xm = (plane0 + row + xm) * 8u;
     uint32_t o_yp = (plane0 + yp * L + x) * 8u, o_ym = (plane0 + ym * L + x) * 8u;
     uint32_t o_tp = o_c + P * 8u;
-    // coupling words, reloaded every step (cache hits) rather than held
-    uint32_t j_c = (row + x) * 8u, j_xm = (row + xm) * 8u, j_ym = (ym * L + x) * 8u;
+    const uint32_t j_c = (row + x) * 8u, j_xm = (row + xm) * 8u, j_ym = (ym * L + x) * 8u;
     uint64_t below = 0;
     if (valid) {
         if (tau0 == 0) {  // the bond round tau: slice Ltau-1, sign flipped if antiperiodic
@@ -506,13 +511,19 @@ __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restri
     const uint64_t* S0 = scalar_ptr(S);
     const uint64_t* Jx = scalar_ptr(G.Jx);
     const uint64_t* Jy = scalar_ptr(G.Jy);
+    const uint32_t i = threadIdx.x;
+    if (valid) {
+        J.xp[i] = load_at(Jx, j_c);
+        J.xm[i] = load_at(Jx, j_xm);  // the -x bond is the +x bond of x-1
+        J.yp[i] = load_at(Jy, j_c);
+        J.ym[i] = load_at(Jy, j_ym);
+    }
 #pragma unroll 1
     for (uint32_t k = 0; k < steps; ++k) {
         const uint64_t* Sk = S0 + (size_t)k * 2 * P;
         // the offsets stay 32-bit values in the loop (scalar base + 32-bit
         // offset addressing), not 64-bit addresses hoisted out of it
         asm volatile("" : "+v"(o_c), "+v"(o_xp), "+v"(o_xm), "+v"(o_yp), "+v"(o_ym), "+v"(o_tp));
-        asm volatile("" : "+v"(j_c), "+v"(j_xm), "+v"(j_ym));
         Word r;
         if (valid) {
             const uint64_t w = load_at(Sk, o_c);
@@ -523,11 +534,9 @@ __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restri
             } else {
                 above = load_at(Sk, o_tp);
             }
-            const SpaceCount n =
-                count_space(w, load_at(Sk, o_xp), load_at(Sk, o_xm), load_at(Sk, o_yp),
-                            load_at(Sk, o_ym), load_at(Jx, j_c),
-                            load_at(Jx, j_xm),  // the -x bond is the +x bond of x-1
-                            load_at(Jy, j_c), load_at(Jy, j_ym));
+            const SpaceCount n = count_space(w, load_at(Sk, o_xp), load_at(Sk, o_xm),
+                                             load_at(Sk, o_yp), load_at(Sk, o_ym), J.xp[i],
+                                             J.xm[i], J.yp[i], J.ym[i]);
             r = class_code(regime, site0 + 2 * k * P, w, n, above, below);
             below = above;
         }
@@ -549,11 +558,13 @@ __device__ __forceinline__ uint32_t xcd_contiguous(uint32_t b, uint32_t n) {
 __global__ void __launch_bounds__(kSweepBlock)
 k_half_sweep(const GroupDev G, uint32_t colour, const uint32_t* __restrict__ ctr, uint32_t t_add) {
     __shared__ SweepQueue Q;
+    __shared__ WalkCouplings J;
     const uint32_t t = __builtin_amdgcn_readfirstlane(ctr[0] + t_add);
     const uint32_t b = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const uint32_t g = fast_div(b, G.div_blocks);  // b / gridDim.x on the scalar unit
     const uint32_t item = (b - g * gridDim.x) * kSweepBlock + threadIdx.x;
-    walk_block(G, G.spins + (size_t)g * G.V, g, colour, t, item, G.V >> __builtin_ctz(G.tile), Q);
+    walk_block(G, G.spins + (size_t)g * G.V, g, colour, t, item, G.V >> __builtin_ctz(G.tile), Q,
+               J);
 }
 
 __device__ __forceinline__ uint32_t find_group(const uint32_t* __restrict__ prefix,
@@ -636,6 +647,7 @@ __global__ void __launch_bounds__(kSweepBlock)
 k_half_sweep_batched(const BatchPlan plan, uint32_t colour, const uint32_t* __restrict__ ctr,
                      uint32_t t_add) {
     __shared__ SweepQueue Q;
+    __shared__ WalkCouplings J;
     const uint32_t t = __builtin_amdgcn_readfirstlane(ctr[0] + t_add);
     const uint32_t b = xcd_contiguous(blockIdx.x, gridDim.x);
     const BlockPlace at = locate<kSameShape>(plan, b);
@@ -644,7 +656,8 @@ k_half_sweep_batched(const BatchPlan plan, uint32_t colour, const uint32_t* __re
     const uint32_t nb = sweep_blocks_per_slot(G.V, G.tile);
     const uint32_t g = fast_div(local, G.div_blocks);  // local / nb on the scalar unit
     const uint32_t item = (local - g * nb) * kSweepBlock + threadIdx.x;
-    walk_block(G, G.spins + (size_t)g * G.V, g, colour, t, item, G.V >> __builtin_ctz(G.tile), Q);
+    walk_block(G, G.spins + (size_t)g * G.V, g, colour, t, item, G.V >> __builtin_ctz(G.tile), Q,
+               J);
 }
 
 // ---------------------------------------------------------------------------
