@@ -547,11 +547,16 @@ __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restri
 // Blocks are dealt to the eight XCDs round-robin (block b runs on XCD b % 8).
 // Renumber them so that every XCD receives one contiguous run of logical
 // blocks: neighbouring tau-planes then meet in the same L2.  A bijection of
-// [0, n); only the speed depends on the dispatch order.
-__device__ __forceinline__ uint32_t xcd_contiguous(uint32_t b, uint32_t n) {
+// [0, n); only the speed depends on the dispatch order.  `backwards` runs
+// each XCD through its blocks from the last to the first: the blue pass does,
+// so that it begins with the words the red pass left in the caches (3 % less
+// time per pass on ensembles of 0.5 to 0.9 GB).
+__device__ __forceinline__ uint32_t xcd_contiguous(uint32_t b, uint32_t n, bool backwards = false) {
     constexpr uint32_t kXcd = 8;
     const uint32_t q = n / kXcd, r = n % kXcd;
-    const uint32_t x = b % kXcd, i = b / kXcd;
+    const uint32_t x = b % kXcd;
+    uint32_t i = b / kXcd;
+    if (backwards) i = q + (x < r ? 1 : 0) - 1 - i;
     return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
@@ -560,7 +565,8 @@ k_half_sweep(const GroupDev G, uint32_t colour, const uint32_t* __restrict__ ctr
     __shared__ SweepQueue Q;
     __shared__ WalkCouplings J;
     const uint32_t t = __builtin_amdgcn_readfirstlane(ctr[0] + t_add);
-    const uint32_t b = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+    const uint32_t b = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y,
+                                      colour != 0);
     const uint32_t g = fast_div(b, G.div_blocks);  // b / gridDim.x on the scalar unit
     const uint32_t item = (b - g * gridDim.x) * kSweepBlock + threadIdx.x;
     walk_block(G, G.spins + (size_t)g * G.V, g, colour, t, item, G.V >> __builtin_ctz(G.tile), Q,
@@ -649,7 +655,7 @@ k_half_sweep_batched(const BatchPlan plan, uint32_t colour, const uint32_t* __re
     __shared__ SweepQueue Q;
     __shared__ WalkCouplings J;
     const uint32_t t = __builtin_amdgcn_readfirstlane(ctr[0] + t_add);
-    const uint32_t b = xcd_contiguous(blockIdx.x, gridDim.x);
+    const uint32_t b = xcd_contiguous(blockIdx.x, gridDim.x, colour != 0);
     const BlockPlace at = locate<kSameShape>(plan, b);
     const GroupDev G = group_record<kSameShape>(plan, at.gi);
     const uint32_t local = __builtin_amdgcn_readfirstlane(at.local);
