@@ -448,7 +448,7 @@ def mlp_bench(args):
         rows.append(row)
     print(json.dumps({"metric": "ladder network kernels", "unit": "us per call",
                       "higher_is_better": False, "reps": reps, "rows": rows,
-                      "note": "one thread per output, FP32 accumulation; latency-bound at "
+                      "note": "one launch per pass, FP32 accumulation; latency-bound at "
                               "these sizes (a training step is a handful of launches)"}),
           flush=True)
 

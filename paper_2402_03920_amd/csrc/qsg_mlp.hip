@@ -8,9 +8,13 @@
 // FP32; bias, GELU, loss and Adam are FP32.  Without it the same kernels run
 // in FP32 throughout.
 //
-// The matrices are at most [B x 128] x [128 x 128]: latency-bound, so each
-// kernel is a plain one-thread-per-output loop with coalesced weight reads;
-// everything is deterministic (no float atomics).
+// The matrices are at most [B x 128] x [128 x 128]: what costs time is the
+// latency of launches and of the weight reads, not arithmetic.  So a pass is
+// one launch whose blocks keep all weights in registers, read up front, and
+// take a few samples at a time through all layers.  The sums of the forward
+// pass and of the data gradients run over the inputs in order, because with
+// BF16 operands a last-bit difference in one layer is rounded to another
+// operand in the next.  Everything is deterministic (no float atomics).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -54,99 +58,378 @@ __host__ __device__ inline Layer layer(int l) {
     return Layer{K[l], N[l], off, off + (size_t)K[l] * N[l]};
 }
 
-// out[b][n] = act(sum_k x[b][k] * W[k][n] + bias[n]); pre keeps the sum.
-__global__ void k_linear_fwd(const float* __restrict__ X, int B, const float* __restrict__ Wf,
-                             const uint16_t* __restrict__ Wh, const float* __restrict__ bias,
-                             int K, int N, float* __restrict__ pre, float* __restrict__ out,
-                             int act) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B * N) return;
-    const int b = i / N, n = i - b * N;
-    const float* x = X + (size_t)b * K;
-    float acc = 0.0f;
-    if (Wh) {
-        for (int k = 0; k < K; ++k) acc = fmaf(bf16_round(x[k]), bf16_to_f32(Wh[(size_t)k * N + n]), acc);
-    } else {
-        for (int k = 0; k < K; ++k) acc = fmaf(x[k], Wf[(size_t)k * N + n], acc);
+// Operand of a product: rounded to bfloat16 when the BF16 copy is in use.
+template <bool kHalf>
+__device__ __forceinline__ float operand(float x) {
+    return kHalf ? bf16_round(x) : x;
+}
+
+// Weight number i of the FP32 master or of the BF16 copy.
+template <bool kHalf>
+__device__ __forceinline__ float weight(const float* __restrict__ pf,
+                                        const uint16_t* __restrict__ ph, size_t i) {
+    return kHalf ? bf16_to_f32(ph[i]) : pf[i];
+}
+
+// A block is three groups of 128 threads; each thread keeps the 128 weights
+// of one output of one layer in registers, so that all weight reads of the
+// network are in flight together and are read once per block (one launch per
+// layer, each reading its weights in its own dependent loop, took 12 us a
+// layer; the whole pass now takes 8.5 us up to 512 samples and 11 at 1024,
+// before 42 to 47).  Blocks then loop over tiles of S samples: one as long as every
+// sample can have a block of its own on a CU (256 of them), then 2, 4 and 8,
+// which share the barriers between layers.
+constexpr int kGroup = kMlpHidden;
+constexpr int kGroups = 3;
+constexpr int kMlpBlocks = 256;
+constexpr int kMaxTile = 8;
+
+inline int tile_samples(int B) {
+    int s = 1;
+    while (s < kMaxTile && B > s * kMlpBlocks) s *= 2;
+    return s;
+}
+
+// a0 = sum_k v0[k] w[k], a1 = sum_k v1[k] w[k] (v0, v1 in LDS), in order of k.
+__device__ __forceinline__ void dot2(const float* v0, const float* v1,
+                                     const float (&w)[kMlpHidden], float& a0, float& a1) {
+    a0 = a1 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kMlpHidden; k += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(v0 + k);
+        const float4 y = *reinterpret_cast<const float4*>(v1 + k);
+        a0 = fmaf(x.x, w[k], a0);
+        a1 = fmaf(y.x, w[k], a1);
+        a0 = fmaf(x.y, w[k + 1], a0);
+        a1 = fmaf(y.y, w[k + 1], a1);
+        a0 = fmaf(x.z, w[k + 2], a0);
+        a1 = fmaf(y.z, w[k + 2], a1);
+        a0 = fmaf(x.w, w[k + 3], a0);
+        a1 = fmaf(y.w, w[k + 3], a1);
+        // not all of v ahead in registers: the weights need them
+        if (k % 32 == 28) asm volatile("" : "+v"(a0), "+v"(a1) : : "memory");
     }
-    acc += bias[n];
-    if (pre) pre[i] = acc;
-    out[i] = act ? gelu(acc) : acc;
 }
 
-// dpre = dy * gelu'(pre)
-__global__ void k_gelu_bwd(const float* __restrict__ dy, const float* __restrict__ pre,
-                           float* __restrict__ dpre, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dpre[i] = dy[i] * gelu_grad(pre[i]);
-}
-
-// dX[b][k] = sum_n dpre[b][n] * W[k][n]
-__global__ void k_linear_bwd_data(const float* __restrict__ dpre, int B, const float* __restrict__ Wf,
-                                  const uint16_t* __restrict__ Wh, int K, int N,
-                                  float* __restrict__ dX) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B * K) return;
-    const int b = i / K, k = i - b * K;
-    const float* d = dpre + (size_t)b * N;
-    float acc = 0.0f;
-    if (Wh) {
-        for (int n = 0; n < N; ++n) acc = fmaf(bf16_round(d[n]), bf16_to_f32(Wh[(size_t)k * N + n]), acc);
-    } else {
-        for (int n = 0; n < N; ++n) acc = fmaf(d[n], Wf[(size_t)k * N + n], acc);
-    }
-    dX[i] = acc;
-}
-
-// dW[k][n] = sum_b x[b][k] * dpre[b][n]; db[n] = sum_b dpre[b][n]
-__global__ void k_linear_bwd_weight(const float* __restrict__ X, const float* __restrict__ dpre,
-                                    int B, int K, int N, int rounded, float* __restrict__ dW,
-                                    float* __restrict__ db) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < K * N) {
-        const int k = i / N, n = i - k * N;
-        float acc = 0.0f;
-        for (int b = 0; b < B; ++b) {
-            const float x = X[(size_t)b * K + k];
-            const float d = dpre[(size_t)b * N + n];
-            acc = rounded ? fmaf(bf16_round(x), bf16_round(d), acc) : fmaf(x, d, acc);
+// Forward pass, S samples a tile.  Group 0 does layer 1, group 1 layer 2,
+// group 2 layers 0 and 3 (output n & 31 of every fourth sample).
+template <bool kHalf>
+__global__ void __launch_bounds__(kGroups * kGroup)
+k_forward(const float* __restrict__ X, int B, int S, const float* __restrict__ pf,
+          const uint16_t* __restrict__ ph, float* __restrict__ ws, float* __restrict__ out) {
+    __shared__ __align__(16) float h[3][kMaxTile][kMlpHidden];  // operands of layers 1, 2, 3
+    __shared__ float xin[kMaxTile][kMlpIn];
+    const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kGroup);
+    const int n = (int)threadIdx.x % kGroup;
+    const Layer L = layer(group + 1);
+    const int col = group == 2 ? n % kMlpOut : n;
+    float w[kMlpHidden], w0[kMlpIn];
+#pragma unroll
+    for (int k = 0; k < kMlpIn; ++k) w0[k] = weight<kHalf>(pf, ph, layer(0).w_off + k * kMlpHidden + n);
+#pragma unroll
+    for (int k = 0; k < kMlpHidden; ++k)
+        w[k] = weight<kHalf>(pf, ph, L.w_off + (size_t)k * L.N + col);
+    const float bias = pf[L.b_off + col], bias0 = pf[layer(0).b_off + n];
+    const int tiles = (B + S - 1) / S;
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int b0 = tile * S, left = min(S, B - b0);
+        if ((int)threadIdx.x < left * kMlpIn)
+            xin[threadIdx.x / kMlpIn][threadIdx.x % kMlpIn] =
+                operand<kHalf>(X[(size_t)b0 * kMlpIn + threadIdx.x]);
+        __syncthreads();
+        auto put = [&](int l, int s, float pre) {  // a hidden layer's result of sample s
+            const float act = gelu(pre);
+            h[l][s][n] = operand<kHalf>(act);
+            ws[mlp_ws_pre(l, B) + (size_t)(b0 + s) * kMlpHidden + n] = pre;
+            ws[mlp_ws_act(l, B) + (size_t)(b0 + s) * kMlpHidden + n] = act;
+        };
+        if (group == 2) {
+#pragma unroll 1
+            for (int s = 0; s < left; ++s) {
+                float acc = 0.0f;
+#pragma unroll
+                for (int k = 0; k < kMlpIn; ++k) acc = fmaf(xin[s][k], w0[k], acc);
+                put(0, s, acc + bias0);
+            }
         }
-        dW[i] = acc;
-    } else if (i < K * N + N) {
-        const int n = i - K * N;
-        float acc = 0.0f;
-        for (int b = 0; b < B; ++b) acc += dpre[(size_t)b * N + n];
-        db[n] = acc;
+        __syncthreads();
+#pragma unroll 1
+        for (int l = 1; l < 3; ++l) {
+            if (group == l - 1) {
+#pragma unroll 1
+                for (int s = 0; s < left; s += 2) {
+                    const int s1 = min(s + 1, left - 1);
+                    float a0, a1;
+                    dot2(h[l - 1][s], h[l - 1][s1], w, a0, a1);
+                    put(l, s, a0 + bias);
+                    if (s1 > s) put(l, s1, a1 + bias);
+                }
+            }
+            __syncthreads();
+        }
+        if (group == 2) {
+            const int s0 = n / kMlpOut, s1 = s0 + kMlpHidden / kMlpOut;
+            float a0, a1;
+            if (s0 < left) {
+                dot2(h[2][s0], h[2][s1 < left ? s1 : s0], w, a0, a1);
+                out[(size_t)(b0 + s0) * kMlpOut + col] = a0 + bias;
+                if (s1 < left) out[(size_t)(b0 + s1) * kMlpOut + col] = a1 + bias;
+            }
+        }
+        // the next tile's first writes are to xin and h[0], which no thread
+        // reads past the last barrier
     }
+}
+
+// Gradients of the pre-activations of the hidden layers: gpre_l[k] =
+// (sum_n g_{l+1}[n] W_{l+1}[k][n]) gelu'(pre_l[k]), from the output's
+// gradient down.  Group 0 does layer 2, group 1 layer 1, group 2 layer 0,
+// each thread with its row of the weights in registers.  Layer 2's stay in
+// the block (the weight gradients form them again: the caller's scratch
+// holds two of the three).
+template <bool kHalf>
+__global__ void __launch_bounds__(kGroups * kGroup)
+k_backward_data(const float* __restrict__ dout, int B, int S, const float* __restrict__ pf,
+                const uint16_t* __restrict__ ph, const float* __restrict__ ws,
+                float* __restrict__ gpre1, float* __restrict__ gpre0) {
+    __shared__ __align__(16) float g3[kMaxTile][kMlpOut];
+    __shared__ __align__(16) float g[2][kMaxTile][kMlpHidden];  // operands of layers 2 and 1
+    __shared__ float slope[kGroups][kMaxTile][kMlpHidden];      // gelu'(pre) of the group's layer
+    const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kGroup);
+    const int k = (int)threadIdx.x % kGroup;
+    const int l = 2 - group;
+    const Layer L = layer(l + 1);
+    float w[kMlpHidden];  // group 0: its row has 32
+    if (group == 0) {
+#pragma unroll
+        for (int n = 0; n < kMlpOut; ++n) w[n] = weight<kHalf>(pf, ph, L.w_off + (size_t)k * kMlpOut + n);
+    } else {
+#pragma unroll
+        for (int n = 0; n < kMlpHidden; ++n)
+            w[n] = weight<kHalf>(pf, ph, L.w_off + (size_t)k * kMlpHidden + n);
+    }
+    float* gout = group == 1 ? gpre1 : gpre0;
+    const int tiles = (B + S - 1) / S;
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int b0 = tile * S, left = min(S, B - b0);
+        if ((int)threadIdx.x < left * kMlpOut)
+            g3[threadIdx.x / kMlpOut][threadIdx.x % kMlpOut] =
+                operand<kHalf>(dout[(size_t)b0 * kMlpOut + threadIdx.x]);
+#pragma unroll 1
+        for (int s = 0; s < left; ++s)
+            slope[group][s][k] = gelu_grad(ws[mlp_ws_pre(l, B) + (size_t)(b0 + s) * kMlpHidden + k]);
+        __syncthreads();
+        if (group == 0) {
+#pragma unroll 1
+            for (int s = 0; s < left; ++s) {
+                float acc = 0.0f;
+#pragma unroll
+                for (int n = 0; n < kMlpOut; ++n) acc = fmaf(g3[s][n], w[n], acc);
+                g[0][s][k] = operand<kHalf>(acc * slope[0][s][k]);
+            }
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int step = 0; step < 2; ++step) {
+            if (group == step + 1) {
+                auto put = [&](int s, float sum) {
+                    const float v = sum * slope[group][s][k];
+                    if (step == 0) g[1][s][k] = operand<kHalf>(v);
+                    gout[(size_t)(b0 + s) * kMlpHidden + k] = v;
+                };
+#pragma unroll 1
+                for (int s = 0; s < left; s += 2) {
+                    const int s1 = min(s + 1, left - 1);
+                    float a0, a1;
+                    dot2(g[step][s], g[step][s1], w, a0, a1);
+                    put(s, a0);
+                    if (s1 > s) put(s1, a1);
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// Weight and bias gradients of all layers in one launch: dW[k][n] = sum_b
+// x[b][k] g[b][n], db[n] = sum_b g[b][n].  A block of 16 waves forms a 32 x
+// 32 tile of one layer's dW over all samples, 128 samples at a time staged in
+// LDS: each wave takes 8 of them, each lane a 4 x 4 piece of the tile, and
+// the waves' sums are added in order at the end.  What costs time is the
+// latency of a round of reads, so a round is large and a thread has its reads
+// in flight together: 16 us at 321 samples, 26 with rounds of 32.  (A thread
+// per output that walked the batch alone, layer by layer with the data
+// gradients between, made a training step of 321 samples 490 us; now 42.)
+constexpr int kDwTile = 32;
+constexpr int kDwWaves = 16;
+constexpr int kDwThreads = 64 * kDwWaves;
+constexpr int kDwRows = 4;                                       // staged per thread
+constexpr int kDwChunk = kDwRows * kDwThreads / kDwTile;         // samples per round
+constexpr int kDwPerWave = kDwChunk / kDwWaves;
+// blocks of layer l: (K / 32 rounded up) x (N / 32)
+constexpr int dw_blocks(int l) {
+    return l == 0 ? kMlpHidden / kDwTile
+         : l < 3  ? (kMlpHidden / kDwTile) * (kMlpHidden / kDwTile)
+                  : (kMlpHidden / kDwTile) * (kMlpOut / kDwTile);
+}
+constexpr int kDwBlocks = dw_blocks(0) + dw_blocks(1) + dw_blocks(2) + dw_blocks(3);
+
+template <bool kHalf>
+__global__ void __launch_bounds__(kDwThreads)
+k_backward_weight(const float* __restrict__ X, const float* __restrict__ dout, int B,
+                  const float* __restrict__ pf, const uint16_t* __restrict__ ph,
+                  const float* __restrict__ ws, const float* __restrict__ gpre1,
+                  const float* __restrict__ gpre0, float* __restrict__ grads) {
+    // the staged samples, then the waves' sums
+    __shared__ __align__(16) float lds[kDwWaves * kDwTile * kDwTile];
+    static_assert(3 * kDwChunk <= kDwWaves * kDwTile, "the operands fit");
+    float(*xs)[kDwTile] = reinterpret_cast<float(*)[kDwTile]>(lds);
+    float(*gs)[kDwTile] = xs + kDwChunk;
+    float(*ds)[kDwTile] = gs + kDwChunk;  // layer 2: the output's gradients
+    __shared__ float bpart[kDwTile][kDwTile];
+    int block = blockIdx.x, l = 0;
+    while (block >= dw_blocks(l)) block -= dw_blocks(l++);
+    const Layer L = layer(l);
+    const int ntiles = L.N / kDwTile;
+    const int k0 = block / ntiles * kDwTile, n0 = block % ntiles * kDwTile;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int row = t >> 5, c = t & 31;  // staging: sample `row` of the 32, column c
+    const float* x = l == 0 ? X : ws + mlp_ws_act(l - 1, B);
+    const float* g = l == 3 ? dout : l == 1 ? gpre1 : gpre0;
+    float w3[kMlpOut];  // layer 2: this column's row of the output weights
+    if (l == 2) {
+#pragma unroll
+        for (int n = 0; n < kMlpOut; ++n)
+            w3[n] = weight<kHalf>(pf, ph, layer(3).w_off + (size_t)(n0 + c) * kMlpOut + n);
+    }
+    const int ky = lane >> 3, nx = lane & 7;
+    float acc[4][4] = {};
+    float db = 0.0f;
+    for (int b0 = 0; b0 < B; b0 += kDwChunk) {
+        float xv[kDwRows], gv[kDwRows];
+#pragma unroll
+        for (int i = 0; i < kDwRows; ++i) {
+            const int b = b0 + row + kDwTile * i;
+            xv[i] = gv[i] = 0.0f;
+            if (b >= B) continue;
+            if (k0 + c < L.K) xv[i] = x[(size_t)b * L.K + k0 + c];
+            if (l == 2)
+                gv[i] = ws[mlp_ws_pre(2, B) + (size_t)b * kMlpHidden + n0 + c];
+            else
+                gv[i] = g[(size_t)b * L.N + n0 + c];
+        }
+        if (l == 2) {  // gv holds gelu's argument: form the gradient from the output's
+            static_assert(kMlpOut == kDwTile, "one output column per staging column");
+#pragma unroll
+            for (int i = 0; i < kDwRows; ++i) {
+                const int b = b0 + row + kDwTile * i;
+                ds[row + kDwTile * i][c] =
+                    b < B ? operand<kHalf>(dout[(size_t)b * kMlpOut + c]) : 0.0f;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kDwRows; ++i) {
+                float s = 0.0f;
+#pragma unroll
+                for (int n = 0; n < kMlpOut; n += 4) {
+                    const float4 v = *reinterpret_cast<const float4*>(&ds[row + kDwTile * i][n]);
+                    s = fmaf(v.x, w3[n], s);
+                    s = fmaf(v.y, w3[n + 1], s);
+                    s = fmaf(v.z, w3[n + 2], s);
+                    s = fmaf(v.w, w3[n + 3], s);
+                }
+                gv[i] = s * gelu_grad(gv[i]);
+                asm volatile("" : "+v"(gv[i]) : : "memory");  // one row's reads at a time
+            }
+        }
+        __syncthreads();  // the previous round's samples are used up
+#pragma unroll
+        for (int i = 0; i < kDwRows; ++i) {
+            xs[row + kDwTile * i][c] = operand<kHalf>(xv[i]);
+            gs[row + kDwTile * i][c] = operand<kHalf>(gv[i]);
+            db += gv[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kDwPerWave; ++i) {
+            const float4 a = *reinterpret_cast<const float4*>(&xs[kDwPerWave * wave + i][4 * ky]);
+            const float4 d = *reinterpret_cast<const float4*>(&gs[kDwPerWave * wave + i][4 * nx]);
+            const float av[4] = {a.x, a.y, a.z, a.w}, dv[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[p][q] = fmaf(av[p], dv[q], acc[p][q]);
+        }
+    }
+    __syncthreads();  // the staging buffers become the waves' sums
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+        *reinterpret_cast<float4*>(&lds[(wave * kDwTile + 4 * ky + p) * kDwTile + 4 * nx]) =
+            make_float4(acc[p][0], acc[p][1], acc[p][2], acc[p][3]);
+    bpart[row][c] = db;
+    __syncthreads();
+    float sum = 0.0f;
+#pragma unroll
+    for (int v = 0; v < kDwWaves; ++v) sum += lds[v * kDwTile * kDwTile + t];
+    if (k0 + row < L.K) grads[L.w_off + (size_t)(k0 + row) * L.N + n0 + c] = sum;
+    if (k0 == 0 && t < kDwTile) {
+        float s = 0.0f;
+#pragma unroll
+        for (int v = 0; v < kDwTile; ++v) s += bpart[v][t];
+        grads[L.b_off + n0 + t] = s;
+    }
+}
+
+// Loss and decode take 32 threads per sample (a half wave): thread l its
+// logit's exponentials and logarithms; the sums run over the logits in order
+// in every thread, from LDS.
+constexpr int kRowSamples = 8;  // samples per block of 256 threads
+
+__device__ __forceinline__ float row_max(float v) {
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 32));
+    return v;
 }
 
 // Per sample: KL(t || softmax(z[:31])) + (z[31] - logL)^2 and its gradient,
 // scaled by 1/B (mean over the batch).
-__global__ void k_loss(const float* __restrict__ z, const float* __restrict__ t,
-                       const float* __restrict__ logL, int B, float* __restrict__ dz,
-                       float* __restrict__ loss) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const float* zb = z + (size_t)b * kMlpOut;
-    const float* tb = t + (size_t)b * kMlpInc;
-    float m = zb[0];
-    for (int l = 1; l < kMlpInc; ++l) m = fmaxf(m, zb[l]);
+__global__ void __launch_bounds__(32 * kRowSamples)
+k_loss(const float* __restrict__ z, const float* __restrict__ t, const float* __restrict__ logL,
+       int B, float* __restrict__ dz, float* __restrict__ loss) {
+    __shared__ float es[kRowSamples][kMlpOut], ts[kRowSamples][kMlpOut], as[kRowSamples][kMlpOut];
+    const int r = threadIdx.x >> 5, l = threadIdx.x & 31;
+    const int b = blockIdx.x * kRowSamples + r;
+    const bool head = l == kMlpInc;  // the barrier head
+    float zl = 0.0f, tl = 0.0f;
+    if (b < B) {
+        zl = z[(size_t)b * kMlpOut + l];
+        if (!head) tl = t[(size_t)b * kMlpInc + l];
+    }
+    const float m = row_max(head ? -INFINITY : zl);
+    es[r][l] = expf(zl - m);
+    ts[r][l] = tl;
+    __syncthreads();
     float se = 0.0f, tsum = 0.0f;
-    for (int l = 0; l < kMlpInc; ++l) {
-        se += expf(zb[l] - m);
-        tsum += tb[l];
+#pragma unroll
+    for (int i = 0; i < kMlpInc; ++i) {
+        se += es[r][i];
+        tsum += ts[r][i];
     }
     const float lse = m + logf(se);
-    float kl = 0.0f;
     const float inv_b = 1.0f / (float)B;
-    for (int l = 0; l < kMlpInc; ++l) {
-        const float s = expf(zb[l] - lse);
-        if (tb[l] > 0.0f) kl += tb[l] * (logf(tb[l]) - (zb[l] - lse));
-        dz[(size_t)b * kMlpOut + l] = (s * tsum - tb[l]) * inv_b;
+    const float d = head && b < B ? zl - logL[b] : 0.0f;
+    if (b < B)
+        dz[(size_t)b * kMlpOut + l] =
+            head ? 2.0f * d * inv_b : (expf(zl - lse) * tsum - tl) * inv_b;
+    as[r][l] = tl > 0.0f ? logf(tl) - (zl - lse) : 0.0f;
+    __syncthreads();
+    if (head && b < B) {
+        float kl = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kMlpInc; ++i)
+            if (ts[r][i] > 0.0f) kl = fmaf(ts[r][i], as[r][i], kl);
+        loss[b] = kl + d * d;
     }
-    const float d = zb[kMlpInc] - logL[b];
-    dz[(size_t)b * kMlpOut + kMlpInc] = 2.0f * d * inv_b;
-    loss[b] = kl + d * d;
 }
 
 __global__ void k_adam(float* __restrict__ p, uint16_t* __restrict__ ph, const float* __restrict__ g,
@@ -170,80 +453,95 @@ __global__ void k_to_bf16(const float* __restrict__ p, uint16_t* __restrict__ ph
 }
 
 // Ladder from the 31 increment logits: log G_i = log Gmin + (log Gmax -
-// log Gmin) * cumulative softmax; ends pinned exactly; predicted acceptance
-// 1 - exp(z31)/31.
-__global__ void k_decode(const float* __restrict__ z, const double* __restrict__ gmin,
-                         const double* __restrict__ gmax, int B, double* __restrict__ ladder,
-                         float* __restrict__ acc_pred) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const float* zb = z + (size_t)b * kMlpOut;
-    double m = zb[0];
-    for (int l = 1; l < kMlpInc; ++l) m = fmax(m, (double)zb[l]);
+// log Gmin) * cumulative softmax, non-decreasing, ends pinned exactly;
+// predicted acceptance 1 - exp(z31)/31.  Thread l forms point l + 1.
+__global__ void __launch_bounds__(32 * kRowSamples)
+k_decode(const float* __restrict__ z, const double* __restrict__ gmin,
+         const double* __restrict__ gmax, int B, double* __restrict__ ladder,
+         float* __restrict__ acc_pred) {
+    __shared__ double es[kRowSamples][kMlpOut];
+    const int r = threadIdx.x >> 5, l = threadIdx.x & 31;
+    const int b = blockIdx.x * kRowSamples + r;
+    const bool head = l == kMlpInc;
+    const float zl = b < B ? z[(size_t)b * kMlpOut + l] : 0.0f;
+    const double m = row_max(head ? -INFINITY : zl);
+    es[r][l] = exp((double)zl - m);
+    __syncthreads();
     double se = 0.0;
-    for (int l = 0; l < kMlpInc; ++l) se += exp((double)zb[l] - m);
-    const double lo = log(gmin[b]), hi = log(gmax[b]);
+#pragma unroll
+    for (int i = 0; i < kMlpInc; ++i) se += es[r][i];
     double c = 0.0;
-    double* out = ladder + (size_t)b * kMlpLadder;
-    out[0] = gmin[b];
-    for (int l = 0; l < kMlpInc - 1; ++l) {
-        c += exp((double)zb[l] - m) / se;
-        double gv = exp(lo + (hi - lo) * c);
-        if (gv < out[l]) gv = out[l];
-        out[l + 1] = gv;
+#pragma unroll
+    for (int i = 0; i < kMlpInc; ++i)
+        if (i <= l) c += es[r][i] / se;
+    const double first = b < B ? gmin[b] : 1.0, last = b < B ? gmax[b] : 1.0;
+    const double lo = log(first), hi = log(last);
+    double v = exp(lo + (hi - lo) * c);  // (comparisons that leave a NaN in place)
+    if (v < first) v = first;
+    if (v > last) v = last;
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1) {  // running maximum over the points
+        const double below = __shfl_up(v, off, 32);
+        if (l >= off && below > v) v = below;
     }
-    out[kMlpLadder - 1] = gmax[b];
-    if (out[kMlpLadder - 2] > gmax[b]) out[kMlpLadder - 2] = gmax[b];
-    if (acc_pred) acc_pred[b] = 1.0f - expf(zb[kMlpInc]) / (float)kMlpInc;
+    if (b >= B) return;
+    double* out = ladder + (size_t)b * kMlpLadder;
+    if (head) {
+        out[0] = first;
+        if (acc_pred) acc_pred[b] = 1.0f - expf(zl) / (float)kMlpInc;
+    } else {
+        out[l + 1] = l == kMlpInc - 1 ? last : v;
+    }
 }
 
 inline unsigned blocks(long n, int t) { return (unsigned)((n + t - 1) / t); }
 
 }  // namespace
 
+namespace {
+
+template <bool kHalf>
+void launch_forward(const float* pf, const uint16_t* ph, const float* x, int B, float* out,
+                    float* ws, hipStream_t s) {
+    const int S = tile_samples(B);
+    hipLaunchKernelGGL(k_forward<kHalf>, dim3(min((B + S - 1) / S, kMlpBlocks)),
+                       dim3(kGroups * kGroup), 0, s, x, B, S, pf, ph, ws, out);
+}
+
+template <bool kHalf>
+void launch_backward(const float* pf, const uint16_t* ph, const float* x, const float* ws,
+                     const float* dout, int B, float* grads, float* gpre1, float* gpre0,
+                     hipStream_t s) {
+    const int S = tile_samples(B);
+    hipLaunchKernelGGL(k_backward_data<kHalf>, dim3(min((B + S - 1) / S, kMlpBlocks)),
+                       dim3(kGroups * kGroup), 0, s, dout, B, S, pf, ph, ws, gpre1, gpre0);
+    hipLaunchKernelGGL(k_backward_weight<kHalf>, dim3(kDwBlocks), dim3(kDwThreads), 0, s, x, dout, B,
+                       pf, ph, ws, gpre1, gpre0, grads);
+}
+
+}  // namespace
+
 hipError_t mlp_forward(const float* pf, const uint16_t* ph, const float* x, int B, float* out,
                        float* ws, hipStream_t s) {
-    const float* in = x;
-    for (int l = 0; l < 4; ++l) {
-        const Layer L = layer(l);
-        float* pre = ws + mlp_ws_pre(l, B);
-        float* act = (l < 3) ? ws + mlp_ws_act(l, B) : out;
-        hipLaunchKernelGGL(k_linear_fwd, dim3(blocks((long)B * L.N, 128)), dim3(128), 0, s, in, B,
-                           pf + L.w_off, ph ? ph + L.w_off : nullptr, pf + L.b_off, L.K, L.N, pre,
-                           act, l < 3 ? 1 : 0);
-        in = act;
-    }
+    if (ph) launch_forward<true>(pf, ph, x, B, out, ws, s);
+    else launch_forward<false>(pf, ph, x, B, out, ws, s);
     return hipGetLastError();
 }
 
 hipError_t mlp_backward(const float* pf, const uint16_t* ph, const float* x, const float* ws,
                         const float* dout, int B, float* grads, float* scratch, hipStream_t s) {
-    // scratch: gact [B][128] (gradient w.r.t. a hidden activation) and
-    // gpre [B][128] (gradient w.r.t. a hidden pre-activation)
-    float* gact = scratch;
-    float* gpre_buf = scratch + (size_t)B * kMlpHidden;
-    for (int l = 3; l >= 0; --l) {
-        const Layer L = layer(l);
-        const float* gpre = dout;  // output layer: no activation
-        if (l < 3) {
-            hipLaunchKernelGGL(k_gelu_bwd, dim3(blocks((long)B * L.N, 256)), dim3(256), 0, s, gact,
-                               ws + mlp_ws_pre(l, B), gpre_buf, B * L.N);
-            gpre = gpre_buf;
-        }
-        const float* xin = (l == 0) ? x : ws + mlp_ws_act(l - 1, B);
-        hipLaunchKernelGGL(k_linear_bwd_weight, dim3(blocks((long)L.K * L.N + L.N, 128)), dim3(128),
-                           0, s, xin, gpre, B, L.K, L.N, ph ? 1 : 0, grads + L.w_off,
-                           grads + L.b_off);
-        if (l > 0)
-            hipLaunchKernelGGL(k_linear_bwd_data, dim3(blocks((long)B * L.K, 128)), dim3(128), 0, s,
-                               gpre, B, pf + L.w_off, ph ? ph + L.w_off : nullptr, L.K, L.N, gact);
-    }
+    // scratch: [B][128] twice, the pre-activation gradients of layers 1 and 0
+    float* gpre1 = scratch;
+    float* gpre0 = scratch + (size_t)B * kMlpHidden;
+    if (ph) launch_backward<true>(pf, ph, x, ws, dout, B, grads, gpre1, gpre0, s);
+    else launch_backward<false>(pf, ph, x, ws, dout, B, grads, gpre1, gpre0, s);
     return hipGetLastError();
 }
 
 hipError_t mlp_loss(const float* z, const float* t, const float* logL, int B, float* dz,
                     float* loss, hipStream_t s) {
-    hipLaunchKernelGGL(k_loss, dim3(blocks(B, 64)), dim3(64), 0, s, z, t, logL, B, dz, loss);
+    hipLaunchKernelGGL(k_loss, dim3(blocks(B, kRowSamples)), dim3(32 * kRowSamples), 0, s, z, t, logL,
+                       B, dz, loss);
     return hipGetLastError();
 }
 
@@ -263,8 +561,8 @@ hipError_t mlp_to_bf16(const float* p, uint16_t* ph, hipStream_t s) {
 
 hipError_t mlp_decode(const float* z, const double* gmin, const double* gmax, int B, double* ladder,
                       float* acc_pred, hipStream_t s) {
-    hipLaunchKernelGGL(k_decode, dim3(blocks(B, 64)), dim3(64), 0, s, z, gmin, gmax, B, ladder,
-                       acc_pred);
+    hipLaunchKernelGGL(k_decode, dim3(blocks(B, kRowSamples)), dim3(32 * kRowSamples), 0, s, z, gmin,
+                       gmax, B, ladder, acc_pred);
     return hipGetLastError();
 }
 
