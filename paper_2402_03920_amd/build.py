@@ -31,7 +31,7 @@ def _run(cmd, verbose):
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     objs = []
-    for src in ("qsg_kernels.hip", "qsg_overlaps.hip", "qsg_transfer.hip", "qsg_corr_mix.hip",
+    for src in ("qsg_kernels.hip", "qsg_overlaps.hip", "qsg_transfer.hip", "qsg_corr.hip",
                 "qsg_mlp.hip", "qsg_api.cpp", "qsg_transfer_api.cpp"):
         obj = os.path.join(BUILD, src + ".o")
         lang = ["-x", "hip"] if src.endswith(".hip") else []

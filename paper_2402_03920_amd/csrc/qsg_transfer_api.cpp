@@ -8,13 +8,12 @@
 
 #include <algorithm>
 #include <cmath>
-#include <initializer_list>
 #include <cstring>
 #include <limits>
 #include <vector>
 
 #include "../../include/qsg.h"
-#include "qsg_corr_mix.h"
+#include "qsg_corr.h"
 #include "qsg_transfer.h"
 
 namespace {
@@ -149,51 +148,20 @@ std::vector<double> tri_vector(const std::vector<double>& a, const std::vector<d
     return z;
 }
 
-// Entries of the Walsh-Hadamard transform of v^2 that the ground-state
-// correlations need (App. E): a set S of sites has R_S = W[S without the
-// last site] / W[0].  Ordered pairs and quadruples of sites reduce to the
-// set met an odd number of times (empty, a pair, a quadruple), so
+// Q2, Q4 and F (App. E) from the sums of squared correlations of pairs,
+// weighted pairs and quadruples of sites: ordered pairs and quadruples reduce
+// to the set met an odd number of times (empty, a pair, a quadruple), so
 //   Q2 = V + 2 sum_pairs R^2,
 //   Q4 = 3V^2 - 2V + (12V - 16) sum_pairs R^2 + 24 sum_quadruples R^2,
 //   F  = V + sum_pairs R^2 [cos(2 pi dx1 / L) + cos(2 pi dx2 / L)].
-// Weights per entry: (Q2, Q4, F).
-struct CorrTable {
-    std::vector<uint32_t> mask;
-    std::vector<double> w;
-    double q2 = 0, q4 = 0, f = 0;  // the empty set's terms
-};
-
-CorrTable corr_table(uint32_t L) {
-    CorrTable t;
-    const uint32_t V = L * L, last = V - 1;
-    auto bits = [&](std::initializer_list<uint32_t> s) {
-        uint32_t m = 0;
-        for (uint32_t i : s)
-            if (i != last) m |= 1u << i;
-        return m;
-    };
-    const double two_pi = 6.283185307179586476925286766559;
-    for (uint32_t x = 0; x < V; ++x)
-        for (uint32_t y = x + 1; y < V; ++y) {
-            t.mask.push_back(bits({x, y}));
-            const double dx1 = (double)(x % L) - (double)(y % L);
-            const double dx2 = (double)(x / L) - (double)(y / L);
-            t.w.insert(t.w.end(), {2.0, 12.0 * V - 16.0,
-                                   std::cos(two_pi * dx1 / L) + std::cos(two_pi * dx2 / L)});
-        }
-    for (uint32_t a = 0; a < V; ++a)
-        for (uint32_t b = a + 1; b < V; ++b)
-            for (uint32_t c = b + 1; c < V; ++c)
-                for (uint32_t d = c + 1; d < V; ++d) {
-                    t.mask.push_back(bits({a, b, c, d}));
-                    t.w.insert(t.w.end(), {0.0, 24.0, 0.0});
-                }
-    t.q2 = V;
-    t.q4 = 3.0 * V * V - 2.0 * V;
-    t.f = V;
-    return t;
+void correlations_of(uint32_t L, double pairs, double weighted, double quadruples, double* out) {
+    const double V = (double)L * L;
+    out[0] = V + 2.0 * pairs;
+    out[1] = 3.0 * V * V - 2.0 * V + ((12.0 * V - 16.0) * pairs + 24.0 * quadruples);
+    out[2] = V + weighted;
 }
 
+// Sets of two or four sites: the workspace sizes allow for a table of them.
 size_t corr_entries(uint32_t L) {
     const size_t V = (size_t)L * L;
     return V * (V - 1) / 2 + V * (V - 1) * (V - 2) * (V - 3) / 24;
@@ -332,33 +300,15 @@ qsg_status qsg_tm_correlations(uint32_t L, const double* d_vec, void* d_ws, size
         return qsg::report_error(QSG_E_BUFFER, "workspace needs %zu bytes",
                                  qsg_tm_correlations_workspace_bytes(L));
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const size_t N = (size_t)qsg_tm_dim(L);
-    const CorrTable t = corr_table(L);
-    const uint32_t E = (uint32_t)t.mask.size();
-    char* base = static_cast<char*>(d_ws);
-    double* W = reinterpret_cast<double*>(base);
-    uint32_t* mask = reinterpret_cast<uint32_t*>(base + align256(N * sizeof(double)));
-    double* w = reinterpret_cast<double*>(reinterpret_cast<char*>(mask) +
-                                          align256(E * sizeof(uint32_t)));
-    double* sums = reinterpret_cast<double*>(reinterpret_cast<char*>(w) +
-                                             align256(3 * (size_t)E * sizeof(double)));
-    TmParams P;
-    std::memset(&P, 0, sizeof P);
-    P.L = L;
-    P.n = L * L - 1;
-    TM_HIP(qsg::launch_tm_wht_squares(P, d_vec, W, s));
-    TM_HIP(hipMemcpyAsync(mask, t.mask.data(), E * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-    TM_HIP(hipMemcpyAsync(w, t.w.data(), 3 * (size_t)E * sizeof(double), hipMemcpyHostToDevice, s));
-    TM_HIP(qsg::launch_tm_corr(W, mask, w, E, sums, s));
+    double* ws = static_cast<double*>(d_ws);
+    double* sums = ws + qsg::tm_corr_ws_doubles(L, false);
+    TM_HIP(qsg::launch_tm_corr_sums(L, d_vec, nullptr, ws, sums, s));
     double h[3];
     TM_HIP(hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, s));
     TM_HIP(hipStreamSynchronize(s));
-    out[0] = t.q2 + h[0];
-    out[1] = t.q4 + h[1];
-    out[2] = t.f + h[2];
+    correlations_of(L, h[0], h[1], h[2], out);
     return QSG_OK;
 }
-
 
 size_t qsg_tm_correlations_lt_workspace_bytes(uint32_t L, uint32_t n) {
     const uint64_t N = qsg_tm_dim(L);
@@ -392,36 +342,18 @@ qsg_status qsg_tm_correlations_lt(uint32_t L, const double* d_even, const double
     for (uint32_t i = 0; i < n; ++i)
         w_odd[i] = l_taus[i] == 0 ? 0.0 : 1.0 / (1.0 + std::exp(l_taus[i] * log_ratio));
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const size_t N = (size_t)qsg_tm_dim(L);
-    const CorrTable t = corr_table(L);
-    const uint32_t E = (uint32_t)t.mask.size();
-    char* base = static_cast<char*>(d_ws);
-    double* We = reinterpret_cast<double*>(base);
-    double* Wo = reinterpret_cast<double*>(base + align256(N * sizeof(double)));
-    uint32_t* mask = reinterpret_cast<uint32_t*>(base + 2 * align256(N * sizeof(double)));
-    double* w = reinterpret_cast<double*>(reinterpret_cast<char*>(mask) +
-                                          align256(E * sizeof(uint32_t)));
-    double* wodd = reinterpret_cast<double*>(reinterpret_cast<char*>(w) +
-                                             align256(3 * (size_t)E * sizeof(double)));
-    double* sums = reinterpret_cast<double*>(reinterpret_cast<char*>(wodd) +
-                                             align256(3 * (size_t)n * sizeof(double)));
-    TmParams P;
-    std::memset(&P, 0, sizeof P);
-    P.L = L;
-    P.n = L * L - 1;
-    TM_HIP(qsg::launch_tm_wht_squares(P, d_even, We, s));
-    TM_HIP(qsg::launch_tm_wht_squares(P, d_odd, Wo, s));
-    TM_HIP(hipMemcpyAsync(mask, t.mask.data(), E * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-    TM_HIP(hipMemcpyAsync(w, t.w.data(), 3 * (size_t)E * sizeof(double), hipMemcpyHostToDevice, s));
-    TM_HIP(hipMemcpyAsync(wodd, w_odd.data(), n * sizeof(double), hipMemcpyHostToDevice, s));
-    TM_HIP(qsg::launch_tm_corr_mixed(We, Wo, mask, w, E, wodd, n, sums, s));
-    std::vector<double> h(3 * (size_t)n);
-    TM_HIP(hipMemcpyAsync(h.data(), sums, h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+    double* ws = static_cast<double*>(d_ws);
+    double* sums = ws + qsg::tm_corr_ws_doubles(L, true);
+    TM_HIP(qsg::launch_tm_corr_sums(L, d_even, d_odd, ws, sums, s));
+    double h[qsg::kCorrSums];
+    TM_HIP(hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, s));
     TM_HIP(hipStreamSynchronize(s));
+    // R = a R_e + b R_o: R^2 from the sums of R_e^2, R_e R_o and R_o^2
     for (uint32_t i = 0; i < n; ++i) {
-        out[3 * i] = t.q2 + h[3 * i];
-        out[3 * i + 1] = t.q4 + h[3 * i + 1];
-        out[3 * i + 2] = t.f + h[3 * i + 2];
+        const double b = w_odd[i], a = 1.0 - b;
+        double m[3];
+        for (int k = 0; k < 3; ++k) m[k] = a * a * h[k] + 2.0 * a * b * h[3 + k] + b * b * h[6 + k];
+        correlations_of(L, m[0], m[1], m[2], out + 3 * i);
     }
     return QSG_OK;
 }
