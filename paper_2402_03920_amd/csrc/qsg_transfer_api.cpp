@@ -141,6 +141,15 @@ std::vector<double> tri_vector(const std::vector<double>& a, const std::vector<d
         shifted_solve(a, b, m, theta, tiny, z);
         double nrm = 0.0;
         for (double v : z) nrm += v * v;
+        if (!std::isfinite(nrm)) {  // the squares overflow where a pivot vanishes
+            double big = 0.0;
+            for (double v : z) big = std::max(big, std::fabs(v));
+            nrm = 0.0;
+            for (double& v : z) {
+                v /= big;
+                nrm += v * v;
+            }
+        }
         nrm = std::sqrt(nrm);
         if (!(nrm > 0) || !std::isfinite(nrm)) break;
         for (double& v : z) v /= nrm;
