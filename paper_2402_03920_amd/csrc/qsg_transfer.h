@@ -35,8 +35,14 @@ constexpr uint32_t kTmDotBlocks = 512;  // partial sums per dot product
 // nv * kTmDotBlocks doubles.
 hipError_t launch_tm_dots(const double* V, uint32_t nv, size_t N, const double* w,
                           double* partial, double* h, hipStream_t s);
-// w -= sum_i h[i] V[i]
-hipError_t launch_tm_update(const double* V, uint32_t nv, size_t N, const double* h, double* w,
+// w -= sum_i h[i] V[i], then h2[i] = <V[i], w>
+hipError_t launch_tm_update_dots(const double* V, uint32_t nv, size_t N, const double* h, double* w,
+                                 double* partial, double* h2, hipStream_t s);
+// w -= sum_i h[i] V[i], then *nrm2 = <w, w>
+hipError_t launch_tm_update_norm(const double* V, uint32_t nv, size_t N, const double* h, double* w,
+                                 double* partial, double* nrm2, hipStream_t s);
+// out[0..2] = *a, *b, *c (out: host memory the device can write)
+hipError_t launch_tm_gather(const double* a, const double* b, const double* c, double* out,
                             hipStream_t s);
 // v = w / sqrt(*nrm2)
 hipError_t launch_tm_scale(const double* w, size_t N, const double* nrm2, double* v, hipStream_t s);

@@ -21,7 +21,9 @@
 // exp(k (L^2 - u)) staged in LDS.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "qsg_transfer.h"
 
@@ -316,8 +318,20 @@ k_tm_small(const TmParams P, const double* in, double* out) {
 }
 
 // ---------------------------------------------------------------------------
-// Lanczos support: deterministic dot products (fixed partial-sum layout and
-// reduction order), updates, scaling, seeded start vectors.
+// Lanczos support: dot products, updates, scaling, seeded start vectors.
+// Deterministic, and every sum has one order whichever kernel forms it: a dot
+// product is kTmDotBlocks x kTmThreads strided sums, then block_sum, then
+// k_tm_reduce; an update subtracts the basis vectors in ascending order.  The
+// solver's results (the sign of the Ritz vector among them) follow the last
+// bit of these sums.
+//
+// What bounds a step is reading the basis.  Orthogonalising twice took four
+// reads of it; the first update and the second dot products now share one
+// (k_tm_update_held keeps an element of all basis vectors in registers), and
+// the second update forms the norm: on a basis of 20 vectors of 2^24 (2.7 GB)
+// a step's four reads of 2.2 ms became three of 1.57 ms, at 5.2 TB/s.  (Merging
+// a vector's second orthogonalisation with the next one's first needs two
+// reads, 1.0 ms, but rounds alpha and beta differently.)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double block_sum(double v, double* red) {
 #pragma unroll
@@ -331,17 +345,64 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
     return s;  // valid in thread 0
 }
 
+// partial[(first + j) blocks + b] = block b's part of <V[first + j], w> for j <
+// n <= NV.  NV sums a thread: w is read once for up to NV vectors.
+template <int NV>
 __global__ void __launch_bounds__(kTmThreads)
-k_tm_dots(const double* __restrict__ V, size_t N, const double* __restrict__ w,
+k_tm_dots(const double* __restrict__ V, uint32_t n, size_t N, const double* __restrict__ w,
           double* __restrict__ partial) {
     __shared__ double red[kTmThreads / 64];
-    const double* __restrict__ v = V + (size_t)blockIdx.y * N;
-    double acc = 0.0;
+    double acc[NV] = {};
     for (size_t i = (size_t)blockIdx.x * kTmThreads + threadIdx.x; i < N;
-         i += (size_t)gridDim.x * kTmThreads)
-        acc += v[i] * w[i];
-    const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) partial[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+         i += (size_t)gridDim.x * kTmThreads) {
+        const double x = w[i];
+        double v[NV];
+#pragma unroll
+        for (int j = 0; j < NV; ++j)  // (past n: the last vector again, not used)
+            v[j] = V[min((uint32_t)j, n - 1) * N + i];
+#pragma unroll
+        for (int j = 0; j < NV; ++j) acc[j] = fma(v[j], x, acc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        if ((uint32_t)j < n) {
+            const double s = block_sum(acc[j], red);
+            if (threadIdx.x == 0) partial[(size_t)j * gridDim.x + blockIdx.x] = s;
+            __syncthreads();
+        }
+    }
+}
+
+// w -= sum_j h[j] V[j] for n <= NV basis vectors, whose elements stay in
+// registers, and of the new w the parts of <V[j], w> (kDots) or <w, w>.
+template <int NV, bool kDots>
+__global__ void __launch_bounds__(kTmThreads)
+k_tm_update_held(const double* __restrict__ V, uint32_t n, size_t N, const double* __restrict__ h,
+                 double* __restrict__ w, double* __restrict__ partial) {
+    __shared__ double red[kTmThreads / 64];
+    constexpr int kSums = kDots ? NV : 1;
+    double acc[kSums] = {};
+    for (size_t i = (size_t)blockIdx.x * kTmThreads + threadIdx.x; i < N;
+         i += (size_t)gridDim.x * kTmThreads) {
+        double v[NV];
+        double x = w[i];
+#pragma unroll
+        for (int j = 0; j < NV; ++j) v[j] = V[min((uint32_t)j, n - 1) * N + i];
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if ((uint32_t)j < n) x = fma(-h[j], v[j], x);
+        w[i] = x;
+#pragma unroll
+        for (int j = 0; j < kSums; ++j) acc[j] = fma(kDots ? v[j] : x, x, acc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < kSums; ++j) {
+        if ((uint32_t)j < n) {
+            const double s = block_sum(acc[j], red);
+            if (threadIdx.x == 0) partial[(size_t)j * gridDim.x + blockIdx.x] = s;
+            __syncthreads();
+        }
+    }
 }
 
 __global__ void __launch_bounds__(kTmThreads)
@@ -353,15 +414,31 @@ k_tm_reduce(const double* __restrict__ partial, uint32_t G, double* __restrict__
     if (threadIdx.x == 0) h[blockIdx.x] = s;
 }
 
+// The same for any number of basis vectors, without dot products: w -= sum_j
+// h[j] V[j]; with kNorm the parts of <w, w> of the new w.
+template <bool kNorm>
 __global__ void __launch_bounds__(kTmThreads)
 k_tm_update(const double* __restrict__ V, uint32_t nv, size_t N, const double* __restrict__ h,
-            double* __restrict__ w) {
+            double* __restrict__ w, double* __restrict__ partial) {
+    __shared__ double red[kTmThreads / 64];
+    double sum = 0.0;
     for (size_t i = (size_t)blockIdx.x * kTmThreads + threadIdx.x; i < N;
          i += (size_t)gridDim.x * kTmThreads) {
-        double acc = w[i];
-        for (uint32_t j = 0; j < nv; ++j) acc -= h[j] * V[(size_t)j * N + i];
-        w[i] = acc;
+        double x = w[i];
+        for (uint32_t j = 0; j < nv; j += 8) {  // eight reads in flight (past nv: the last again)
+            double v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = V[(size_t)min(j + k, nv - 1) * N + i];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (j + k < nv) x = fma(-h[j + k], v[k], x);
+        }
+        w[i] = x;
+        if (kNorm) sum = fma(x, x, sum);
     }
+    if (!kNorm) return;
+    const double s = block_sum(sum, red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
 __global__ void __launch_bounds__(kTmThreads)
@@ -371,6 +448,16 @@ k_tm_scale(const double* __restrict__ w, size_t N, const double* __restrict__ nr
     for (size_t i = (size_t)blockIdx.x * kTmThreads + threadIdx.x; i < N;
          i += (size_t)gridDim.x * kTmThreads)
         v[i] = w[i] * inv;
+}
+
+// out[i] = *in[i], i < 3 (a step's scalars for the host).
+__global__ void k_tm_gather(const double* a, const double* b, const double* c, double* out) {
+    if (threadIdx.x == 0) {
+        out[0] = *a;
+        out[1] = *b;
+        out[2] = *c;
+        __threadfence_system();
+    }
 }
 
 // splitmix64 (Steele, Lea and Flood, OOPSLA 2014) of seed + (i+1) * golden
@@ -425,21 +512,77 @@ hipError_t launch_tm_apply(const TmParams& P, const double* in, double* out, hip
     return hipGetLastError();
 }
 
+namespace {
+
+constexpr uint32_t kDotGroup = 32;    // vectors whose sums one pass over w holds
+constexpr uint32_t kFusedMax = 48;    // basis vectors k_tm_update_held holds (204 registers)
+
+// f(std::integral_constant<int, NV>) with the smallest multiple of 8 >= n.
+template <int NV, int Max, class F>
+void with_count(uint32_t n, F f) {
+    if constexpr (NV < Max) {
+        if (n > (uint32_t)NV) return with_count<NV + 8, Max>(n, f);
+    }
+    f(std::integral_constant<int, NV>{});
+}
+
+void reduce(const double* partial, uint32_t n, double* h, hipStream_t s) {
+    hipLaunchKernelGGL(k_tm_reduce, dim3(n), dim3(kTmThreads), 0, s, partial, kTmDotBlocks, h);
+}
+
+}  // namespace
+
 hipError_t launch_tm_dots(const double* V, uint32_t nv, size_t N, const double* w, double* partial,
                           double* h, hipStream_t s) {
-    hipLaunchKernelGGL(k_tm_dots, dim3(kTmDotBlocks, nv), dim3(kTmThreads), 0, s, V, N, w, partial);
-    hipLaunchKernelGGL(k_tm_reduce, dim3(nv), dim3(kTmThreads), 0, s, partial, kTmDotBlocks, h);
+    for (uint32_t first = 0; first < nv; first += kDotGroup) {
+        const uint32_t n = std::min(nv - first, kDotGroup);
+        with_count<8, kDotGroup>(n, [&](auto c) {
+            hipLaunchKernelGGL(k_tm_dots<decltype(c)::value>, dim3(kTmDotBlocks), dim3(kTmThreads), 0,
+                               s, V + (size_t)first * N, n, N, w,
+                               partial + (size_t)first * kTmDotBlocks);
+        });
+    }
+    reduce(partial, nv, h, s);
     return hipGetLastError();
 }
 
-hipError_t launch_tm_update(const double* V, uint32_t nv, size_t N, const double* h, double* w,
-                            hipStream_t s) {
-    hipLaunchKernelGGL(k_tm_update, dim3(stream_blocks(N)), dim3(kTmThreads), 0, s, V, nv, N, h, w);
+hipError_t launch_tm_update_dots(const double* V, uint32_t nv, size_t N, const double* h, double* w,
+                                 double* partial, double* h2, hipStream_t s) {
+    if (nv > kFusedMax) {
+        hipLaunchKernelGGL(k_tm_update<false>, dim3(stream_blocks(N)), dim3(kTmThreads), 0, s, V, nv,
+                           N, h, w, nullptr);
+        return launch_tm_dots(V, nv, N, w, partial, h2, s);
+    }
+    with_count<8, kFusedMax>(nv, [&](auto c) {
+        hipLaunchKernelGGL((k_tm_update_held<decltype(c)::value, true>), dim3(kTmDotBlocks),
+                           dim3(kTmThreads), 0, s, V, nv, N, h, w, partial);
+    });
+    reduce(partial, nv, h2, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_tm_update_norm(const double* V, uint32_t nv, size_t N, const double* h, double* w,
+                                 double* partial, double* nrm2, hipStream_t s) {
+    if (nv > kFusedMax)
+        hipLaunchKernelGGL(k_tm_update<true>, dim3(kTmDotBlocks), dim3(kTmThreads), 0, s, V, nv, N, h,
+                           w, partial);
+    else
+        with_count<8, kFusedMax>(nv, [&](auto c) {
+            hipLaunchKernelGGL((k_tm_update_held<decltype(c)::value, false>), dim3(kTmDotBlocks),
+                               dim3(kTmThreads), 0, s, V, nv, N, h, w, partial);
+        });
+    reduce(partial, 1, nrm2, s);
     return hipGetLastError();
 }
 
 hipError_t launch_tm_scale(const double* w, size_t N, const double* nrm2, double* v, hipStream_t s) {
     hipLaunchKernelGGL(k_tm_scale, dim3(stream_blocks(N)), dim3(kTmThreads), 0, s, w, N, nrm2, v);
+    return hipGetLastError();
+}
+
+hipError_t launch_tm_gather(const double* a, const double* b, const double* c, double* out,
+                            hipStream_t s) {
+    hipLaunchKernelGGL(k_tm_gather, dim3(1), dim3(64), 0, s, a, b, c, out);
     return hipGetLastError();
 }
 

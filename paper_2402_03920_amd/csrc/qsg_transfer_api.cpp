@@ -225,28 +225,43 @@ qsg_status qsg_tm_lanczos(const qsg_tm_desc* d, uint32_t max_iter, uint32_t n_ei
     double* nrm = h2 + (max_iter + 1);                          // [2]
     double* y = nrm + 2;                                        // [max_iter]
 
+    // a step's scalars, written by the device
+    struct Pinned {
+        double* p = nullptr;
+        hipEvent_t ready = nullptr;
+        ~Pinned() {
+            if (ready) (void)hipEventDestroy(ready);
+            if (p) (void)hipHostFree(p);
+        }
+    } host;
+    TM_HIP(hipHostMalloc(reinterpret_cast<void**>(&host.p), 3 * sizeof(double), hipHostMallocDefault));
+    TM_HIP(hipEventCreateWithFlags(&host.ready, hipEventDisableTiming));
+
     TM_HIP(qsg::launch_tm_random(w, N, seed, s));
     TM_HIP(qsg::launch_tm_dots(w, 1, N, w, partial, nrm, s));
     TM_HIP(qsg::launch_tm_scale(w, N, nrm, V, s));
+    TM_HIP(qsg::launch_tm_apply(P, V, w, s));
 
     std::vector<double> alpha, beta;  // the projection: diagonal, off-diagonal
     std::vector<double> theta, est;
     std::vector<double> y0;
     uint32_t m = 0;
     for (uint32_t j = 0; j < max_iter; ++j) {
-        double* vj = V + (size_t)j * N;
-        TM_HIP(qsg::launch_tm_apply(P, vj, w, s));
-        // classical Gram-Schmidt against every basis vector, twice
+        // w = T V[j]: classical Gram-Schmidt against every basis vector, twice
         TM_HIP(qsg::launch_tm_dots(V, j + 1, N, w, partial, h, s));
-        TM_HIP(qsg::launch_tm_update(V, j + 1, N, h, w, s));
-        TM_HIP(qsg::launch_tm_dots(V, j + 1, N, w, partial, h2, s));
-        TM_HIP(qsg::launch_tm_update(V, j + 1, N, h2, w, s));
-        TM_HIP(qsg::launch_tm_dots(w, 1, N, w, partial, nrm, s));
-        double hj[2], nr;
-        TM_HIP(hipMemcpyAsync(&hj[0], h + j, sizeof(double), hipMemcpyDeviceToHost, s));
-        TM_HIP(hipMemcpyAsync(&hj[1], h2 + j, sizeof(double), hipMemcpyDeviceToHost, s));
-        TM_HIP(hipMemcpyAsync(&nr, nrm, sizeof(double), hipMemcpyDeviceToHost, s));
-        TM_HIP(hipStreamSynchronize(s));
+        TM_HIP(qsg::launch_tm_update_dots(V, j + 1, N, h, w, partial, h2, s));
+        TM_HIP(qsg::launch_tm_update_norm(V, j + 1, N, h2, w, partial, nrm, s));
+        TM_HIP(qsg::launch_tm_gather(h + j, h2 + j, nrm, host.p, s));
+        TM_HIP(hipEventRecord(host.ready, s));
+        // the next vector and its product are under way while the host looks
+        // at this step (not used if it is the last)
+        if (j + 1 < max_iter) {
+            double* next = V + (size_t)(j + 1) * N;
+            TM_HIP(qsg::launch_tm_scale(w, N, nrm, next, s));
+            TM_HIP(qsg::launch_tm_apply(P, next, w, s));
+        }
+        TM_HIP(hipEventSynchronize(host.ready));
+        const double hj[2] = {host.p[0], host.p[1]}, nr = host.p[2];
         alpha.push_back(hj[0] + hj[1]);
         const double bj = std::sqrt(nr);
         m = j + 1;
@@ -275,7 +290,6 @@ qsg_status qsg_tm_lanczos(const qsg_tm_desc* d, uint32_t max_iter, uint32_t n_ei
             converged = est[i] <= tol * std::fabs(theta[0]);
         if (exhausted || converged) break;
         beta.push_back(bj);
-        if (j + 1 < max_iter) TM_HIP(qsg::launch_tm_scale(w, N, nrm, V + (size_t)(j + 1) * N, s));
     }
     for (uint32_t i = 0; i < n_eig; ++i) {
         const bool have = i < theta.size();
@@ -286,8 +300,8 @@ qsg_status qsg_tm_lanczos(const qsg_tm_desc* d, uint32_t max_iter, uint32_t n_ei
     if (d_vec) {
         TM_HIP(hipMemcpyAsync(y, y0.data(), m * sizeof(double), hipMemcpyHostToDevice, s));
         TM_HIP(qsg::launch_tm_combine(V, m, N, y, d_vec, s));
-        TM_HIP(hipStreamSynchronize(s));
     }
+    TM_HIP(hipStreamSynchronize(s));
     return QSG_OK;
 }
 
