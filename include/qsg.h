@@ -113,8 +113,11 @@ typedef struct {
                              0 = default 4).  Results do not depend on it.     */
     uint32_t tau_tile;    /* schedule of the colour pass: tau planes a thread
                              walks along one column (it updates tau_tile/2 words;
-                             0 = default 8).  Each group uses the largest power
-                             of two <= tau_tile (2..32) dividing its L_tau.
+                             0 = default: 2, 4 or 8 by the number of words a
+                             launch covers, all groups' in batched launches,
+                             one group's in launches per group).  Each group
+                             uses the largest power of two <= tau_tile (2..32)
+                             dividing its L_tau.
                              Results do not depend on it.                      */
 } qsg_run_config;
 

@@ -236,6 +236,9 @@ struct qsg_ctx {
     hipStream_t stream = nullptr;
     hipStream_t capture_stream = nullptr;
     std::vector<GroupDev> gd;         // host copies of the device group records
+    // the records of launches per group: the same but for the walk depth,
+    // whose default follows the words of one group
+    std::vector<GroupDev> gd_single;
     std::vector<std::vector<double>> ladder;
     std::vector<bool> ladder_set;
     uint32_t* d_counters = nullptr;   // device (t, p)
@@ -312,9 +315,9 @@ void destroy_graph(qsg_ctx* c) {
 
 // ---------------------------------------------------------------- passes --
 qsg_status plain_sweep(qsg_ctx* c, uint32_t t_add) {
-    for (const GroupDev& g : c->gd)
+    for (const GroupDev& g : c->gd_single)
         QSG_HIP(c, qsg::launch_half_sweep(g, 0, c->d_counters, t_add, c->stream));
-    for (const GroupDev& g : c->gd)
+    for (const GroupDev& g : c->gd_single)
         QSG_HIP(c, qsg::launch_half_sweep(g, 1, c->d_counters, t_add, c->stream));
     return QSG_OK;
 }
@@ -373,6 +376,12 @@ qsg_status build_chunk_graph(qsg_ctx* c, bool fused) {
     c->chunk_graph[f] = graph;
     QSG_HIP(c, hipGraphInstantiate(&c->chunk_exec[f], graph, nullptr, nullptr, 0));
     return QSG_OK;
+}
+
+// Set a record's walk depth (at most `tile` planes).
+void set_tile(GroupDev& g, uint32_t tile) {
+    g.tile = qsg::tile_for(g.Ltau, tile);
+    g.div_blocks = qsg::make_divisor(qsg::sweep_blocks_per_slot(g.V, g.tile));
 }
 
 // The colour pass's batched plan from the groups' current schedules: block
@@ -518,6 +527,9 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
     std::vector<uint32_t> pre_energy(n_groups + 1, 0),
         pre_swap(n_groups + 1, 0), pre_slots(n_groups + 1, 0);
     uint32_t max_v = 0;
+    uint64_t total_words = 0;
+    for (uint32_t i = 0; i < n_groups; ++i)
+        total_words += (uint64_t)groups[i].n_gamma * groups[i].L * groups[i].L * groups[i].L_tau;
     for (uint32_t i = 0; i < n_groups; ++i) {
         const qsg_group_desc& d = groups[i];
         const GroupLayout& gl = L.g[i];
@@ -533,9 +545,8 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
         g.div_half_row = qsg::make_divisor(d.L / 2);
         g.div_plane = qsg::make_divisor(d.L * d.L);
         g.div_row = qsg::make_divisor(d.L);
-        g.tile = qsg::tile_for(d.L_tau, cfg->tau_tile ? cfg->tau_tile : qsg::kDefaultTile);
+        set_tile(g, cfg->tau_tile ? cfg->tau_tile : qsg::default_tile(total_words));
         g.etile = qsg::tile_for(d.L_tau, qsg::kEnergyWords);
-        g.div_blocks = qsg::make_divisor(qsg::sweep_blocks_per_slot(g.V, g.tile));
         g.sw_cap = swap_cap_of(d);
         g.log_cap = cfg->swaplog_cap;
         g.q_split = cfg->sweep_split ? (cfg->sweep_split > 16 ? 16 : cfg->sweep_split) : 4;
@@ -560,6 +571,8 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
         g.lastmask = at<uint64_t>(c, gl.lastmask);
         g.hist = at<uint32_t>(c, gl.hist);
         c->gd.push_back(g);
+        if (cfg->tau_tile == 0) set_tile(g, qsg::default_tile((uint64_t)g.N * g.V));
+        c->gd_single.push_back(g);
         pre_energy[i + 1] = pre_energy[i] + g.N * qsg::energy_blocks_per_slot(g.V, g.etile);
         pre_swap[i + 1] = pre_swap[i] + (g.N >= 2 ? qsg::swap_blocks(g.V) : 0);
         pre_slots[i + 1] = pre_slots[i] + g.N;
@@ -954,21 +967,15 @@ qsg_status qsg_build_tables_k(uint32_t n_gamma, const double* k, uint32_t cap, u
 static_assert(sizeof(GroupDev) == 14 * 4 + 5 * sizeof(qsg::Divisor) + 18 * sizeof(void*),
               "GroupDev changed: update same_but_identity and group_record");
 
-qsg_status qsg_set_colour_schedule(qsg_ctx* c, uint32_t group, uint32_t sweep_split,
-                                   uint32_t tau_tile) {
-    if (qsg_status st = check_ctx(c)) return st;
-    if (group >= c->gd.size()) return fail(c, QSG_E_INVALID, "group %u out of range", group);
-    if (sweep_split < 1 || sweep_split > 16)
-        return fail(c, QSG_E_INVALID, "sweep_split %u outside 1..16", sweep_split);
-    if (tau_tile < 2 || tau_tile > qsg::kMaxTile)
-        return fail(c, QSG_E_INVALID, "tau_tile %u outside 2..%u", tau_tile, qsg::kMaxTile);
+// New schedule of a group: the record of the batched launches (in device
+// memory and in the plans' copies) and that of the launches per group.  Later
+// launches and the next graph capture see it.
+static qsg_status set_records(qsg_ctx* c, uint32_t group, uint32_t sweep_split, uint32_t tile,
+                              uint32_t single_tile) {
     GroupDev& g = c->gd[group];
     const GroupDev before = g;
     g.q_split = sweep_split;
-    g.tile = qsg::tile_for(g.Ltau, tau_tile);
-    g.div_blocks = qsg::make_divisor(qsg::sweep_blocks_per_slot(g.V, g.tile));
-    // later launches (and the next graph capture) see the new record, in
-    // device memory and in the plans' copies
+    set_tile(g, tile);
     hipError_t e = hipMemcpyAsync(c->d_groups + group, &g, sizeof(GroupDev),
                                   hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -976,6 +983,8 @@ qsg_status qsg_set_colour_schedule(qsg_ctx* c, uint32_t group, uint32_t sweep_sp
         g = before;
         return fail(c, QSG_E_DEVICE, "schedule upload: %s", hipGetErrorString(e));
     }
+    c->gd_single[group] = g;
+    set_tile(c->gd_single[group], single_tile);
     const uint32_t n = (uint32_t)c->gd.size();
     if (qsg_status st = upload_sweep_plan(c)) return st;
     for (qsg::BatchPlan* p : {&c->plan_energy, &c->plan_swap, &c->plan_slots})
@@ -984,10 +993,23 @@ qsg_status qsg_set_colour_schedule(qsg_ctx* c, uint32_t group, uint32_t sweep_sp
     return QSG_OK;
 }
 
+qsg_status qsg_set_colour_schedule(qsg_ctx* c, uint32_t group, uint32_t sweep_split,
+                                   uint32_t tau_tile) {
+    if (qsg_status st = check_ctx(c)) return st;
+    if (group >= c->gd.size()) return fail(c, QSG_E_INVALID, "group %u out of range", group);
+    if (sweep_split < 1 || sweep_split > 16)
+        return fail(c, QSG_E_INVALID, "sweep_split %u outside 1..16", sweep_split);
+    if (tau_tile < 2 || tau_tile > qsg::kMaxTile)
+        return fail(c, QSG_E_INVALID, "tau_tile %u outside 2..%u", tau_tile, qsg::kMaxTile);
+    return set_records(c, group, sweep_split, tau_tile, tau_tile);
+}
+
 qsg_status qsg_set_schedule(qsg_ctx* c, uint32_t group, uint32_t sweep_split) {
     if (qsg_status st = check_ctx(c)) return st;
     if (group >= c->gd.size()) return fail(c, QSG_E_INVALID, "group %u out of range", group);
-    return qsg_set_colour_schedule(c, group, sweep_split, c->gd[group].tile);
+    if (sweep_split < 1 || sweep_split > 16)
+        return fail(c, QSG_E_INVALID, "sweep_split %u outside 1..16", sweep_split);
+    return set_records(c, group, sweep_split, c->gd[group].tile, c->gd_single[group].tile);
 }
 
 qsg_status qsg_set_deadline(qsg_ctx* c, double seconds_from_now) {

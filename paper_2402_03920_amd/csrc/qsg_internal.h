@@ -210,10 +210,22 @@ hipError_t launch_energy_batched(const BatchPlan& plan, hipStream_t s);
 hipError_t launch_chunk_fused(const BatchPlan& slots, const uint32_t* ctr, uint32_t n_sweeps,
                               uint32_t lds_words, hipStream_t s);
 constexpr uint32_t kFusedLdsMaxWords = 7168;  // 56 KiB of spins per block
-// Column-walk depth of the colour pass: the default and the largest allowed
-// (tau planes per thread; each thread updates tile/2 words).
-constexpr uint32_t kDefaultTile = 8;
+// Column-walk depth of the colour pass (tau planes per thread; each thread
+// updates tile/2 words): the largest allowed, and the default for a launch
+// over `words` words.  Deep walks save loads and index work per word, shallow
+// ones give more waves, and a launch of few waves lasts as long as one thread
+// takes: the default is the deepest of 8, 4, 2 that leaves two rounds of
+// waves for the chip (2 x 8192).  Measured per pass at depths 8 / 4 / 2: 14.1
+// / 8.5 / 5.8 us on 33 k words, 17.3 / 12.6 / 12.1 on 1 M, 21.7 / 20.0 / 19.5
+// on 2 M, 33.5 / 30.6 / 31.9 on 4 M, 52.7 / 52.6 / 56.9 on 8 M, 93 / 97 / 107
+// on 17 M.
 constexpr uint32_t kMaxTile = 32;
+inline uint32_t default_tile(uint64_t words) {
+    constexpr uint64_t kWaves = 2 * 8192, kLanes = 64;
+    uint32_t tile = 8;
+    while (tile > 2 && words < kWaves * kLanes * tile) tile /= 2;
+    return tile;
+}
 // Largest power of two <= cap that divides Ltau (Ltau is even: at least 2).
 inline uint32_t tile_for(uint32_t Ltau, uint32_t cap) {
     uint32_t t = 2;
