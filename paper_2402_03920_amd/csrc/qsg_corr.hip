@@ -12,6 +12,8 @@
 //     its sets of R R' (see qsg_corr.h), one partial row per block;
 //   k_corr_sum: the rows in order.
 //
+// L <= 3 (at most 256 states) takes one block, k_corr_small.
+//
 // The vector is read once and 26 MB of it written and read again: at L = 5
 // what bounds the call is that read (134 MB; two vectors for the estimates at
 // finite lengths), of which 72 us of k_corr_low reach 3.7 TB/s: its three LDS
@@ -44,8 +46,7 @@ constexpr int count_low() {
 }
 constexpr int kLow = count_low();  // 1 + 12 + 66 + 220 + 495
 
-// The 12-bit values of at most four bits, ascending: those below 2^n come
-// first, so a smaller index space takes a prefix.
+// The 12-bit values of at most four bits, ascending.
 struct LowTable {
     uint16_t value[kLow];
 };
@@ -108,17 +109,17 @@ __device__ __forceinline__ double block_total(double v, double* red) {
 }
 
 // Low bits.  Block x takes tiles x T ... x T + T - 1 of the vector of
-// blockIdx.y; out: per vector [n_low][M], M = tiles of the vector.  With T =
+// blockIdx.y; out: per vector [kLow][M], M = tiles of the vector.  With T =
 // 8 the transform over the tile's low three bits is done too.
 template <int T>
 __global__ void __launch_bounds__(kThreads)
-k_corr_low(const double* __restrict__ even, const double* __restrict__ odd, uint32_t N, uint32_t M,
-           uint32_t n_low, double* __restrict__ out) {
+k_corr_low(const double* __restrict__ even, const double* __restrict__ odd, uint32_t M,
+           double* __restrict__ out) {
     __shared__ double lds[kTile + kPad];
     constexpr int kPer = (kLow + kThreads - 1) / kThreads;  // kept entries per thread
     const uint32_t t = threadIdx.x;
     const double* __restrict__ v = blockIdx.y ? odd : even;
-    double* __restrict__ dst = out + (size_t)blockIdx.y * n_low * M;
+    double* __restrict__ dst = out + (size_t)blockIdx.y * kLow * M;
     const uint32_t first = blockIdx.x * T;
     uint32_t pos[kPer];
 #pragma unroll
@@ -129,16 +130,11 @@ k_corr_low(const double* __restrict__ even, const double* __restrict__ odd, uint
     }
     auto load = [&](uint32_t tile, double (&x)[16]) {
         const size_t base = (size_t)tile * kTile + 16 * t;
-        if (N >= kTile) {
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                const double2 a = *reinterpret_cast<const double2*>(v + base + r);
-                x[r] = a.x;
-                x[r + 1] = a.y;
-            }
-        } else {  // one part-filled tile: the rest is zero
-#pragma unroll
-            for (int r = 0; r < 16; ++r) x[r] = base + r < N ? v[base + r] : 0.0;
+        for (int r = 0; r < 16; r += 2) {
+            const double2 a = *reinterpret_cast<const double2*>(v + base + r);
+            x[r] = a.x;
+            x[r + 1] = a.y;
         }
     };
     double keep[kPer][T], next[16];
@@ -162,7 +158,7 @@ k_corr_low(const double* __restrict__ even, const double* __restrict__ odd, uint
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
         const uint32_t j = t + kThreads * i;
-        if (j >= n_low) continue;
+        if (j >= kLow) continue;
         hadamard(keep[i]);
 #pragma unroll
         for (int k = 0; k < T; ++k) dst[(size_t)j * M + first + k] = keep[i][k];
@@ -173,19 +169,78 @@ struct CosTable {
     double c[kTmMaxL];  // cos(2 pi d / L)
 };
 
-// High bits and sums.  Blocks take the kept low entries in turn.
+// Adds a set's products R R' to the sums (the set as its bits, the last site
+// left out; nothing for other than one to four bits).
+template <bool kMixed>
+__device__ __forceinline__ void add_set(uint32_t set, uint32_t L, double re, double ro,
+                                        const double* cosl, double (&sum)[kCorrSums]) {
+    const uint32_t c = (uint32_t)__popc(set);
+    if (c == 0 || c > kMaxBits) return;
+    const double rr[3] = {re * re, re * ro, ro * ro};
+    if (c > 2) {
+#pragma unroll
+        for (int k = 0; k < (kMixed ? 3 : 1); ++k) sum[3 * k + 2] += rr[k];
+        return;
+    }
+    const uint32_t a = 31u - (uint32_t)__clz(set);
+    const uint32_t b = c == 1 ? L * L - 1 : (uint32_t)__ffs(set) - 1;
+    const int d1 = (int)(a % L) - (int)(b % L), d2 = (int)(a / L) - (int)(b / L);
+    const double w = cosl[abs(d1)] + cosl[abs(d2)];
+#pragma unroll
+    for (int k = 0; k < (kMixed ? 3 : 1); ++k) {
+        sum[3 * k] += rr[k];
+        sum[3 * k + 1] += w * rr[k];
+    }
+}
+
+// At most 256 states: one block, a state per thread, a round per index bit
+// through LDS.
+template <bool kMixed>
+__global__ void __launch_bounds__(kThreads)
+k_corr_small(const double* __restrict__ even, const double* __restrict__ odd, uint32_t L,
+             CosTable cosines, double* __restrict__ out) {
+    __shared__ double v[2][kThreads], red[kThreads / 64], cosl[kTmMaxL];
+    const uint32_t t = threadIdx.x, n = L * L - 1, N = 1u << n;
+    if (t < kTmMaxL) cosl[t] = cosines.c[t];
+    double e = t < N ? even[t] : 0.0, o = kMixed && t < N ? odd[t] : 0.0;
+    e *= e;
+    o *= o;
+    for (uint32_t j = 0; j < n; ++j) {
+        __syncthreads();
+        v[0][t] = e;
+        if (kMixed) v[1][t] = o;
+        __syncthreads();
+        const uint32_t s = t ^ (1u << j);
+        const bool up = (t >> j) & 1u;
+        e = up ? v[0][s] - e : e + v[0][s];
+        if (kMixed) o = up ? v[1][s] - o : o + v[1][s];
+    }
+    __syncthreads();
+    if (t == 0) {
+        v[0][0] = e;
+        v[1][0] = o;
+    }
+    __syncthreads();
+    double sum[kCorrSums] = {};
+    if (t < N) add_set<kMixed>(t, L, e * (1.0 / v[0][0]), kMixed ? o * (1.0 / v[1][0]) : 0.0, cosl, sum);
+#pragma unroll
+    for (int k = 0; k < (kMixed ? kCorrSums : 3); ++k) {
+        const double s = block_total(sum[k], red);
+        if (t == 0) out[k] = s;
+    }
+}
+
+// High bits and sums: block j the kept low entry j.
 template <int T, bool kMixed>
 __global__ void __launch_bounds__(kThreads)
-k_corr_high(const double* __restrict__ C, uint32_t L, uint32_t M, uint32_t n_low, CosTable cosines,
+k_corr_high(const double* __restrict__ C, uint32_t L, uint32_t M, CosTable cosines,
             double* __restrict__ partial) {
     __shared__ double lds[kTile + kPad];
     __shared__ double red[kThreads / 64];
     __shared__ double cosl[kTmMaxL];
     const uint32_t t = threadIdx.x;
     if (t < kTmMaxL) cosl[t] = cosines.c[t];
-    const size_t vec = (size_t)n_low * M;
-    const uint32_t low_bits = L * L - 1 < 12 ? L * L - 1 : 12;
-    const uint32_t last = L * L - 1;
+    const size_t vec = (size_t)kLow * M;
     // W[0] of a vector: the low entry 0 over all tiles (one of every T, the
     // others are differences within a group)
     auto norm = [&](const double* c) {
@@ -195,56 +250,36 @@ k_corr_high(const double* __restrict__ C, uint32_t L, uint32_t M, uint32_t n_low
     };
     const double inv_e = norm(C), inv_o = kMixed ? norm(C + vec) : 0.0;
     double sum[kCorrSums] = {};
-    for (uint32_t j = blockIdx.x; j < n_low; j += gridDim.x) {
-        const uint32_t low = c_low.value[j];
-        auto load = [&](const double* c, double (&x)[16]) {
-            const double* p = c + (size_t)j * M + 16 * t;
-            if (M == kTile) {
+    const uint32_t j = blockIdx.x, low = c_low.value[j];
+    auto load = [&](const double* c, double (&x)[16]) {
+        const double* p = c + (size_t)j * M + 16 * t;
+        if (M == kTile) {
 #pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    const double2 a = *reinterpret_cast<const double2*>(p + r);
-                    x[r] = a.x;
-                    x[r + 1] = a.y;
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) x[r] = 16 * t + r < M ? p[r] : 0.0;
+            for (int r = 0; r < 16; r += 2) {
+                const double2 a = *reinterpret_cast<const double2*>(p + r);
+                x[r] = a.x;
+                x[r + 1] = a.y;
             }
-        };
-        double e[16], o[16];
-        load(C, e);
-        if (kMixed) load(C + vec, o);
-        hadamard(e, T);
-        transform_tile(lds, e);
-        if (kMixed) {
-            __syncthreads();  // lds is used again
-            hadamard(o, T);
-            transform_tile(lds, o);
+        } else {  // fewer tiles: the rest is zero
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] = 16 * t + r < M ? p[r] : 0.0;
         }
-        __syncthreads();
+    };
+    double e[16], o[16];
+    load(C, e);
+    if (kMixed) load(C + vec, o);
+    hadamard(e, T);
+    transform_tile(lds, e);
+    if (kMixed) {
+        __syncthreads();  // lds is used again
+        hadamard(o, T);
+        transform_tile(lds, o);
+    }
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const uint32_t h = t + 256 * q;
-            const uint32_t set = h << low_bits | low;
-            const uint32_t c = (uint32_t)__popc(set);
-            if (h >= M || c == 0 || c > kMaxBits) continue;
-            const double re = e[q] * inv_e, ro = kMixed ? o[q] * inv_o : 0.0;
-            const double rr[3] = {re * re, re * ro, ro * ro};
-            if (c > 2) {
-#pragma unroll
-                for (int k = 0; k < (kMixed ? 3 : 1); ++k) sum[3 * k + 2] += rr[k];
-            } else {
-                const uint32_t a = 31u - (uint32_t)__clz(set);
-                const uint32_t b = c == 1 ? last : (uint32_t)__ffs(set) - 1;
-                const int d1 = (int)(a % L) - (int)(b % L), d2 = (int)(a / L) - (int)(b / L);
-                const double w = cosl[abs(d1)] + cosl[abs(d2)];
-#pragma unroll
-                for (int k = 0; k < (kMixed ? 3 : 1); ++k) {
-                    sum[3 * k] += rr[k];
-                    sum[3 * k + 1] += w * rr[k];
-                }
-            }
-        }
+    for (int q = 0; q < 16; ++q) {
+        const uint32_t h = t + 256 * q;
+        if (h < M)
+            add_set<kMixed>(h << 12 | low, L, e[q] * inv_e, kMixed ? o[q] * inv_o : 0.0, cosl, sum);
     }
 #pragma unroll
     for (int k = 0; k < (kMixed ? kCorrSums : 3); ++k) {
@@ -263,51 +298,48 @@ k_corr_sum(const double* __restrict__ partial, uint32_t rows, uint32_t n, double
     if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-struct Plan {
-    uint32_t N, M, n_low, rows;  // states, tiles, kept low entries, partial rows
-};
-Plan plan_of(uint32_t L) {
-    Plan p;
-    p.N = 1u << (L * L - 1);
-    p.M = p.N > kTile ? p.N / kTile : 1;
-    p.n_low = 0;
-    for (uint32_t v = 0; v < (uint32_t)kTile && v < p.N; ++v) p.n_low += bits_of((int)v) <= kMaxBits;
-    p.rows = p.N >= kTile ? p.n_low : 4;  // (few blocks where few entries)
-    return p;
-}
+uint32_t tiles_of(uint32_t L) { return (1u << (L * L - 1)) / kTile; }  // 0: one block does it
 
 template <int T>
-void launch_corr(const Plan& p, uint32_t L, const double* even, const double* odd, double* ws,
+void launch_corr(uint32_t M, uint32_t L, const double* even, const double* odd, double* ws,
                  double* partial, const CosTable& cosines, hipStream_t s) {
-    hipLaunchKernelGGL(k_corr_low<T>, dim3(p.M / T, odd ? 2 : 1), dim3(kThreads), 0, s, even, odd,
-                       p.N, p.M, p.n_low, ws);
+    hipLaunchKernelGGL(k_corr_low<T>, dim3(M / T, odd ? 2 : 1), dim3(kThreads), 0, s, even, odd, M, ws);
     if (odd)
-        hipLaunchKernelGGL((k_corr_high<T, true>), dim3(p.rows), dim3(kThreads), 0, s, ws, L, p.M,
-                           p.n_low, cosines, partial);
+        hipLaunchKernelGGL((k_corr_high<T, true>), dim3(kLow), dim3(kThreads), 0, s, ws, L, M, cosines,
+                           partial);
     else
-        hipLaunchKernelGGL((k_corr_high<T, false>), dim3(p.rows), dim3(kThreads), 0, s, ws, L, p.M,
-                           p.n_low, cosines, partial);
+        hipLaunchKernelGGL((k_corr_high<T, false>), dim3(kLow), dim3(kThreads), 0, s, ws, L, M,
+                           cosines, partial);
 }
 
 }  // namespace
 
 size_t tm_corr_ws_doubles(uint32_t L, bool mixed) {
-    const Plan p = plan_of(L);
-    return (size_t)(mixed ? 2 : 1) * p.n_low * p.M + (size_t)p.rows * kCorrSums;
+    const size_t M = tiles_of(L);
+    return M ? (mixed ? 2 : 1) * kLow * M + (size_t)kLow * kCorrSums : 0;
 }
 
 hipError_t launch_tm_corr_sums(uint32_t L, const double* even, const double* odd, double* ws,
                                double* out, hipStream_t s) {
-    const Plan p = plan_of(L);
-    double* partial = ws + (size_t)(odd ? 2 : 1) * p.n_low * p.M;
+    const uint32_t M = tiles_of(L);
     CosTable cosines;
     for (uint32_t d = 0; d < kTmMaxL; ++d)
         cosines.c[d] = std::cos(6.283185307179586476925286766559 * d / L);
+    if (M == 0) {
+        if (odd)
+            hipLaunchKernelGGL(k_corr_small<true>, dim3(1), dim3(kThreads), 0, s, even, odd, L, cosines,
+                               out);
+        else
+            hipLaunchKernelGGL(k_corr_small<false>, dim3(1), dim3(kThreads), 0, s, even, odd, L,
+                               cosines, out);
+        return hipGetLastError();
+    }
+    double* partial = ws + (size_t)(odd ? 2 : 1) * kLow * M;
     // eight tiles a block where that leaves two blocks a CU (L = 5)
-    if (p.M >= 4096) launch_corr<8>(p, L, even, odd, ws, partial, cosines, s);
-    else launch_corr<1>(p, L, even, odd, ws, partial, cosines, s);
+    if (M >= 4096) launch_corr<8>(M, L, even, odd, ws, partial, cosines, s);
+    else launch_corr<1>(M, L, even, odd, ws, partial, cosines, s);
     const uint32_t sums = odd ? kCorrSums : 3;
-    hipLaunchKernelGGL(k_corr_sum, dim3(sums), dim3(kThreads), 0, s, partial, p.rows, sums, out);
+    hipLaunchKernelGGL(k_corr_sum, dim3(sums), dim3(kThreads), 0, s, partial, (uint32_t)kLow, sums, out);
     return hipGetLastError();
 }
 
