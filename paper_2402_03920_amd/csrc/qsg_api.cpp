@@ -103,6 +103,12 @@ qsg_status check_desc(const qsg_group_desc& d, std::string* why) {
     return code;
 }
 
+uint64_t ensemble_words(const qsg_group_desc* d, uint32_t n) {
+    uint64_t words = 0;
+    for (uint32_t i = 0; i < n; ++i) words += (uint64_t)d[i].n_gamma * d[i].L * d[i].L * d[i].L_tau;
+    return words;
+}
+
 // QSG_OK or the status of the first bad descriptor (with `why` set).
 qsg_status make_layout(const qsg_group_desc* d, uint32_t n, const qsg_run_config& cfg,
                        Layout* out, std::string* why) {
@@ -166,10 +172,12 @@ qsg_status make_layout(const qsg_group_desc* d, uint32_t n, const qsg_run_config
     // every pass launches one grid over all groups: its block count must be
     // a valid grid size and fit the 32-bit block prefix sums
     uint64_t energy_blocks = 0, swap_blocks = 0;
+    const uint64_t total_words = ensemble_words(d, n);
     for (uint32_t i = 0; i < n; ++i) {
         const uint32_t V = d[i].L * d[i].L * d[i].L_tau;
         energy_blocks += (uint64_t)d[i].n_gamma *
-                         qsg::energy_blocks_per_slot(V, qsg::tile_for(d[i].L_tau, qsg::kEnergyWords));
+                         qsg::energy_blocks_per_slot(d[i].L * d[i].L,
+                                                     qsg::energy_walks(d[i].L_tau, total_words).tiles);
         swap_blocks += qsg::swap_blocks(V);
     }
     if (total_blocks >= (1ull << 31) || energy_blocks >= (1ull << 31) ||
@@ -244,6 +252,7 @@ struct qsg_ctx {
     uint32_t* d_counters = nullptr;   // device (t, p)
     uint64_t t = 0, p = 0;            // host mirror of the device counters
     qsg::BatchPlan plan_sweep{}, plan_energy{}, plan_swap{};
+    uint32_t energy_planes = 0;  // deepest walk of plan_energy
     GroupDev* d_groups = nullptr;
     qsg::BatchPlan plan_slots{};      // one block per slot (fused sweeps)
     uint32_t fused_lds_words = 0;     // slots at most this big run from LDS
@@ -338,7 +347,7 @@ qsg_status batched_sweep(qsg_ctx* c, hipStream_t s, uint32_t t_add) {
 }
 
 qsg_status batched_pt(qsg_ctx* c, hipStream_t s, uint32_t p_add) {
-    QSG_HIP(c, qsg::launch_energy_batched(c->plan_energy, s));
+    QSG_HIP(c, qsg::launch_energy_batched(c->plan_energy, c->energy_planes, s));
     QSG_HIP(c, qsg::launch_pt_batched(c->d_groups, (uint32_t)c->gd.size(), c->d_counters, p_add, s));
     QSG_HIP(c, qsg::launch_swap_apply_batched(c->plan_swap, s));
     return QSG_OK;
@@ -527,9 +536,7 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
     std::vector<uint32_t> pre_energy(n_groups + 1, 0),
         pre_swap(n_groups + 1, 0), pre_slots(n_groups + 1, 0);
     uint32_t max_v = 0;
-    uint64_t total_words = 0;
-    for (uint32_t i = 0; i < n_groups; ++i)
-        total_words += (uint64_t)groups[i].n_gamma * groups[i].L * groups[i].L * groups[i].L_tau;
+    const uint64_t total_words = ensemble_words(groups, n_groups);
     for (uint32_t i = 0; i < n_groups; ++i) {
         const qsg_group_desc& d = groups[i];
         const GroupLayout& gl = L.g[i];
@@ -546,7 +553,8 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
         g.div_plane = qsg::make_divisor(d.L * d.L);
         g.div_row = qsg::make_divisor(d.L);
         set_tile(g, cfg->tau_tile ? cfg->tau_tile : qsg::default_tile(total_words));
-        g.etile = qsg::tile_for(d.L_tau, qsg::kEnergyWords);
+        g.ewalk = qsg::energy_walks(d.L_tau, total_words);
+        c->energy_planes = std::max(c->energy_planes, g.ewalk.planes);
         g.sw_cap = swap_cap_of(d);
         g.log_cap = cfg->swaplog_cap;
         g.q_split = cfg->sweep_split ? (cfg->sweep_split > 16 ? 16 : cfg->sweep_split) : 4;
@@ -573,7 +581,7 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
         c->gd.push_back(g);
         if (cfg->tau_tile == 0) set_tile(g, qsg::default_tile((uint64_t)g.N * g.V));
         c->gd_single.push_back(g);
-        pre_energy[i + 1] = pre_energy[i] + g.N * qsg::energy_blocks_per_slot(g.V, g.etile);
+        pre_energy[i + 1] = pre_energy[i] + g.N * qsg::energy_blocks_per_slot(g.L * g.L, g.ewalk.tiles);
         pre_swap[i + 1] = pre_swap[i] + (g.N >= 2 ? qsg::swap_blocks(g.V) : 0);
         pre_slots[i + 1] = pre_slots[i] + g.N;
         if (g.V > max_v) max_v = g.V;
@@ -964,7 +972,7 @@ qsg_status qsg_build_tables_k(uint32_t n_gamma, const double* k, uint32_t cap, u
 // qsg::same_but_identity lists every field of the group record and the
 // kernels' group_record moves every pointer: a new field must be added to
 // both.
-static_assert(sizeof(GroupDev) == 14 * 4 + 5 * sizeof(qsg::Divisor) + 18 * sizeof(void*),
+static_assert(sizeof(GroupDev) == 16 * 4 + 5 * sizeof(qsg::Divisor) + 18 * sizeof(void*),
               "GroupDev changed: update same_but_identity and group_record");
 
 // New schedule of a group: the record of the batched launches (in device

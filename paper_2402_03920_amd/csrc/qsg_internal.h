@@ -58,6 +58,12 @@ inline Divisor make_divisor(uint32_t d) {
     return r;
 }
 
+// Column walks of the energy pass: Ltau planes in `tiles` tau tiles of
+// `planes` planes, the first `n_short` of them one plane less.
+struct EnergyWalks {
+    uint32_t tiles, planes, n_short;
+};
+
 // Everything a kernel needs to know about one group.  Lives on the host
 // (plain launches pass it by value) and in a device array (batched
 // launches index it).
@@ -71,7 +77,7 @@ struct GroupDev {
     uint32_t tile;        // colour-pass schedule: tau planes per column walk (even, divides Ltau)
     uint32_t exch_all;    // PT energy: 0 time bonds (Gamma ladder), 1 all bonds (k ladder)
     uint32_t anti;        // 1: antiperiodic along tau (the wrapping time bond flips sign)
-    uint32_t etile;       // energy pass, batched: tau planes per column walk (divides Ltau)
+    EnergyWalks ewalk;    // energy pass, batched
     Divisor div_half_plane, div_half_row, div_plane, div_row;
     Divisor div_blocks;   // colour-pass blocks per slot (sweep_blocks_per_slot(V, tile))
     uint64_t* spins;          // [N][Ltau][L][L]
@@ -154,7 +160,7 @@ inline bool same_but_identity(const GroupDev& a, const GroupDev& b, uint64_t shi
     auto div = [](Divisor x, Divisor y) { return x.m == y.m && x.s == y.s; };
     return a.L == b.L && a.Ltau == b.Ltau && a.N == b.N && a.V == b.V && a.sw_cap == b.sw_cap &&
            a.log_cap == b.log_cap && a.q_split == b.q_split && a.tile == b.tile &&
-           a.exch_all == b.exch_all && a.etile == b.etile &&
+           a.exch_all == b.exch_all && a.ewalk.tiles == b.ewalk.tiles &&
            a.anti == b.anti && div(a.div_half_plane, b.div_half_plane) &&
            div(a.div_half_row, b.div_half_row) && div(a.div_plane, b.div_plane) &&
            div(a.div_row, b.div_row) && div(a.div_blocks, b.div_blocks) &&
@@ -203,7 +209,8 @@ inline BatchPlan make_plan(const GroupDev* groups, const uint32_t* d_prefix,
 }
 hipError_t launch_half_sweep_batched(const BatchPlan& plan, uint32_t colour, const uint32_t* ctr,
                                      uint32_t t_add, hipStream_t s);
-hipError_t launch_energy_batched(const BatchPlan& plan, hipStream_t s);
+// eplanes: the deepest walk among the plan's groups.
+hipError_t launch_energy_batched(const BatchPlan& plan, uint32_t eplanes, hipStream_t s);
 // Fused sweeps over every slot (one block per slot, `slots.prefix` counts
 // slots per group): n_sweeps sweeps in one launch; slots of at most
 // lds_words words run from LDS.
@@ -232,6 +239,33 @@ inline uint32_t tile_for(uint32_t Ltau, uint32_t cap) {
     while (t * 2 <= cap && Ltau % (t * 2) == 0) t *= 2;
     return t;
 }
+// Energy pass: each thread walks one column through one tau tile of at most
+// kEnergyLong planes; walks of at most kEnergyShort planes run in an
+// instantiation with fewer counter planes.
+constexpr int kEnergyShort = 16;
+constexpr int kEnergyLong = 64;
+constexpr int kEnergyBlock = 256;
+// Depth of the walks of a launch over `words` words: every wave ends with
+// transposes that cost as much as 16 planes, so the deepest that leaves the
+// chip enough waves.  Tiles need not divide Ltau (their sizes differ by one
+// plane): where they had to, 3 M words at Ltau = 90 (walks of 2 planes) took
+// 75 us instead of 15.  Measured at depths 4 / 8 / 16 / 32 / 64 (us): 6.3 /
+// 6.6 / 7.1 / 12 / 12 on 33 k words, 8.0 / 7.3 / 8.8 / 13 / 16 on 324 k,
+// 14 / 9.8 / 9.0 / 13 / 18 on 1 M, 27 / 14 / 11 / 14 / 20 on 2 M, 48 / 28 /
+// 23 / 21 / 25 on 5 M, 510 / 278 / 200 / 183 / 182 on 67 M and 360 / 291 /
+// 257 (depths 16 / 32 / 64) on 113 M.
+inline EnergyWalks energy_walks(uint32_t Ltau, uint64_t words) {
+    const uint32_t depth = words >= (1ull << 26)   ? kEnergyLong
+                           : words >= (1ull << 22) ? 32
+                           : words >= 750000       ? 16
+                           : words >= (1ull << 18) ? 8
+                                                   : 4;
+    EnergyWalks w;
+    w.tiles = (Ltau + depth - 1) / depth;
+    w.planes = (Ltau + w.tiles - 1) / w.tiles;
+    w.n_short = w.tiles * w.planes - Ltau;
+    return w;
+}
 hipError_t launch_pt_batched(const GroupDev* groups, uint32_t n_groups, const uint32_t* ctr,
                              uint32_t p_add, hipStream_t s);
 hipError_t launch_swap_apply_batched(const BatchPlan& plan, hipStream_t s);
@@ -240,18 +274,12 @@ hipError_t launch_swap_apply_batched(const BatchPlan& plan, hipStream_t s);
 // The colour pass gives each thread one column (x, y) of one tau tile of
 // `tile` planes: V / tile threads per slot.
 __host__ __device__ inline uint32_t sweep_blocks_per_slot(uint32_t V, uint32_t tile);
-__host__ __device__ inline uint32_t energy_blocks_per_slot(uint32_t V, uint32_t words);
+__host__ __device__ inline uint32_t energy_blocks_per_slot(uint32_t P, uint32_t tiles);
 __host__ __device__ inline uint32_t swap_blocks(uint32_t V);
 
 constexpr uint32_t kMaxSlots = 64;  // slots per group (the C ABI's QSG_MAX_GAMMA)
 constexpr int kSweepBlock = 256;   // threads per block of a colour pass
 constexpr uint32_t kWaveSize = 64;
-// Energy pass: each thread walks one column through a tau tile of at most
-// this many planes (batched launches; a launch for one group takes at most
-// kEnergyPlanesSlot so that it still has enough blocks).
-constexpr int kEnergyWords = 64;
-constexpr int kEnergyPlanesSlot = 16;
-constexpr int kEnergyBlock = 256;
 constexpr int kSwapBlock = 256;
 
 }  // namespace qsg
@@ -262,9 +290,9 @@ __host__ __device__ inline uint32_t sweep_blocks_per_slot(uint32_t V, uint32_t t
 }
 // The fused chunk kernel walks a slot's colour-c words block by block.
 __host__ __device__ inline uint32_t fused_words_per_colour(uint32_t V) { return V / 2; }
-// `planes` divides Ltau, so V / planes threads cover the slot exactly.
-__host__ __device__ inline uint32_t energy_blocks_per_slot(uint32_t V, uint32_t planes) {
-    return (V / planes + kEnergyBlock - 1) / kEnergyBlock;
+// One thread per column (P = L^2 of them) and tau tile.
+__host__ __device__ inline uint32_t energy_blocks_per_slot(uint32_t P, uint32_t tiles) {
+    return (P * tiles + kEnergyBlock - 1) / kEnergyBlock;
 }
 __host__ __device__ inline uint32_t swap_blocks(uint32_t V) {
     return (V + kSwapBlock - 1) / kSwapBlock;

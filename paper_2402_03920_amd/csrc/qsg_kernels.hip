@@ -713,9 +713,8 @@ k_chunk_fused(const BatchPlan slots, const uint32_t* __restrict__ ctr, uint32_t 
 // (order-independent, exact).
 // ---------------------------------------------------------------------------
 // Bit-sliced per-lane counter: value = ones + 2 twos + 4 fours + 8 * (hi as
-// a binary number).  Planes are added four at a time with carry-save adders
-// (Harley-Seal): three adders, then the carry into `fours` and the binary
-// part rippled once per four planes.
+// a binary number).  Planes are added eight at a time with carry-save adders
+// (Harley-Seal): seven adders, then the binary part rippled once.
 // Binary planes a LaneCounter needs above ones/twos/fours to hold `max`.
 constexpr int counter_planes(int max) {
     int nh = 0;
@@ -739,14 +738,21 @@ __device__ __forceinline__ void csa(uint64_t& h, uint64_t& l, uint64_t a, uint64
               __builtin_amdgcn_bitop3_b32(ahi, bhi, chi, 0xE8));  // majority
 }
 
+// Four words into `ones` and `twos`; what they carry into the fours.
 template <int NH>
-__device__ __forceinline__ void add4(LaneCounter<NH>& c, const uint64_t (&x)[4]) {
+__device__ __forceinline__ uint64_t add4(LaneCounter<NH>& c, const uint64_t (&x)[4]) {
     uint64_t twosA, twosB, fours;
     csa(twosA, c.ones, c.ones, x[0], x[1]);
     csa(twosB, c.ones, c.ones, x[2], x[3]);
     csa(fours, c.twos, c.twos, twosA, twosB);
-    uint64_t eights = c.fours & fours;
-    c.fours ^= fours;
+    return fours;
+}
+
+// The carries of two such additions.
+template <int NH>
+__device__ __forceinline__ void add_fours(LaneCounter<NH>& c, uint64_t a, uint64_t b) {
+    uint64_t eights;
+    csa(eights, c.fours, c.fours, a, b);
 #pragma unroll
     for (int i = 0; i < NH; ++i) {
         const uint64_t carry = c.hi[i] & eights;
@@ -802,12 +808,13 @@ __device__ __forceinline__ uint32_t lane_total(const LaneCounter<NH>& c) {
 }
 
 // Column walk: thread `item` of slot g owns column (x, y) = item mod L^2 of
-// tau tile item / L^2 (`planes` planes, planes dividing Ltau) and walks it
-// bottom to top.  Each bond is counted once, from its lower endpoint: per
+// tau tile item / L^2 and walks it bottom to top.  The slot's `tiles` tiles
+// have planes = ceil(Ltau / tiles) planes, the first tiles * planes - Ltau
+// of them one less.  Each bond is counted once, from its lower endpoint: per
 // word the +x and +y neighbours in the same plane and the word above, which
 // is the next step's centre, so a step costs three loads; the offsets are
 // fixed for the walk and the slot base advances one plane per step.  Only
-// the tile's last bond can wrap round tau.
+// the last tile's last bond can wrap round tau.
 //
 // The walk runs in batches of kEnergyBatch steps, software-pipelined: the
 // loads of the next batch are issued before the current batch is counted,
@@ -815,7 +822,15 @@ __device__ __forceinline__ uint32_t lane_total(const LaneCounter<NH>& c) {
 // a batch take no branch (the compiler would otherwise wait for every load
 // in flight before counting): steps past the tile's end re-read its last
 // plane and are not counted, the wrapping bond's word comes through a
-// selected offset, and its antiperiodic sign is applied when counting.
+// selected offset, and its antiperiodic sign is applied when counting.  A
+// short tile's step planes-1 lies in the tile above it (the last tile is
+// never short), so it is read like any other and masked out.
+//
+// What bounds it: on a full chip the reads of the spins (182 us on 67 M
+// words, 3.0 TB/s; 257 us on 113 M, 3.5 TB/s: a third fewer instructions in
+// the adds changed neither); on few words the transposes at the end of every
+// wave (16 to 22 of them, as many instructions as 16 planes) against too few
+// waves: energy_walks picks the depth.
 constexpr int kEnergyBatch = 4;
 
 struct EnergyBatch {
@@ -824,9 +839,9 @@ struct EnergyBatch {
 
 template <int kMaxPlanes>
 __device__ __forceinline__ void energy_walk(const GroupDev& G, uint32_t g, uint32_t item,
-                                            uint32_t planes, int32_t* __restrict__ cnt) {
-    const uint32_t L = G.L, P = L * L;
-    const uint32_t n_items = G.V >> __builtin_ctz(planes);
+                                            const EnergyWalks W, int32_t* __restrict__ cnt) {
+    const uint32_t L = G.L, P = L * L, planes = W.planes;
+    const uint32_t n_items = P * W.tiles;
     // a wave without a column (the tail of a slot's last block) has nothing
     // to add: it leaves before the cross-lane transposes
     if (__builtin_amdgcn_readfirstlane(item) >= n_items) return;
@@ -842,15 +857,16 @@ __device__ __forceinline__ void energy_walk(const GroupDev& G, uint32_t g, uint3
         const uint32_t x = col - y * L;
         const uint32_t xp = (x + 1 == L) ? 0 : x + 1;
         const uint32_t yp = (y + 1 == L) ? 0 : y + 1;
-        const uint32_t base = tile * planes * P;
+        const uint32_t base = (tile * planes - min(tile, W.n_short)) * P;
         // byte offsets: o_xp, o_yp from the step's plane; up words from S
         uint32_t o_xp = (base + y * L + xp) * 8u, o_yp = (base + yp * L + x) * 8u;
         uint32_t o_up = (base + col + P) * 8u;
         const uint32_t o_wrap = col * 8u;  // slice 0, above the top slice
         const uint64_t jx = G.Jx[col], jy = G.Jy[col];
-        const bool top = tile * planes + planes == G.Ltau;  // the last bond wraps to slice 0
+        const bool top = tile + 1 == W.tiles;  // the last bond wraps to slice 0
         const uint64_t flip = (top && G.anti) ? ~0ull : 0ull;  // antiperiodic wrap bond
         const uint32_t last = planes - 1;
+        const uint64_t live = tile < W.n_short ? 0ull : ~0ull;  // step `last` belongs to the tile
         auto fetch = [&](uint32_t k0, EnergyBatch& B) {
             asm volatile("" : "+v"(o_up), "+v"(o_xp), "+v"(o_yp));  // 32-bit offsets in the loop
 #pragma unroll
@@ -864,7 +880,8 @@ __device__ __forceinline__ void energy_walk(const GroupDev& G, uint32_t g, uint3
         };
         uint64_t w = load_at(S, (base + col) * 8u);
         // kGuard: some steps of the batch may lie past the tile's end
-        auto count = [&](auto guard, uint32_t k0, const EnergyBatch& B) {
+        // ct, cq: the batch's carries into the fours of Ct and Cq
+        auto count = [&](auto guard, uint32_t k0, const EnergyBatch& B, uint64_t& ct, uint64_t& cq) {
             constexpr bool kGuard = decltype(guard)::value;
             uint64_t xs[kEnergyBatch], ys[kEnergyBatch], ts[kEnergyBatch], qs[kEnergyBatch];
 #pragma unroll
@@ -880,30 +897,41 @@ __device__ __forceinline__ void energy_walk(const GroupDev& G, uint32_t g, uint3
                     qs[k] = lo_hi(BITOP3(lo, lo >> 1, 0x55555555u, 0x28),
                                   BITOP3(hi, hi >> 1, 0x55555555u, 0x28));
                     w = up;
+                    if (kGuard && k0 + k == last) {
+                        xs[k] &= live;
+                        ys[k] &= live;
+                        ts[k] &= live;
+                        qs[k] &= live;
+                    }
                 }
             }
-            add4(Csp, xs);
-            add4(Csp, ys);
-            add4(Ct, ts);
-            add4(Cq, qs);
+            const uint64_t cx = add4(Csp, xs);
+            add_fours(Csp, cx, add4(Csp, ys));
+            ct = add4(Ct, ts);
+            cq = add4(Cq, qs);
         };
         EnergyBatch b0, b1;
-        if (planes % (2 * kEnergyBatch) == 0) {
+        uint64_t ct0, cq0, ct1, cq1;
+        if (planes % (2 * kEnergyBatch) == 0 && W.n_short == 0) {
             // two batch buffers used in turn (no copies between them); the
             // last fetch re-reads the top plane and is not counted
             fetch(0, b0);
 #pragma unroll 1
             for (uint32_t k0 = 0; k0 < planes; k0 += 2 * kEnergyBatch) {
                 fetch(k0 + kEnergyBatch, b1);
-                count(std::false_type{}, k0, b0);
+                count(std::false_type{}, k0, b0, ct0, cq0);
                 fetch(k0 + 2 * kEnergyBatch, b0);
-                count(std::false_type{}, k0 + kEnergyBatch, b1);
+                count(std::false_type{}, k0 + kEnergyBatch, b1, ct1, cq1);
+                add_fours(Ct, ct0, ct1);
+                add_fours(Cq, cq0, cq1);
             }
-        } else {  // tiles of 2 or 4 planes
+        } else {
 #pragma unroll 1
             for (uint32_t k0 = 0; k0 < planes; k0 += kEnergyBatch) {
                 fetch(k0, b0);
-                count(std::true_type{}, k0, b0);
+                count(std::true_type{}, k0, b0, ct0, cq0);
+                add_fours(Ct, ct0, 0);
+                add_fours(Cq, cq0, 0);
             }
         }
     }
@@ -917,21 +945,23 @@ __device__ __forceinline__ void energy_walk(const GroupDev& G, uint32_t g, uint3
     if (!(lane & 1u) && my_q) atomicAdd(&c[128 + (lane >> 1)], (int32_t)my_q);
 }
 
+template <int kMaxPlanes>
 __global__ void __launch_bounds__(kEnergyBlock)
-k_energy(const GroupDev G, int32_t* cnt, uint32_t planes) {
-    energy_walk<kEnergyPlanesSlot>(G, blockIdx.y, blockIdx.x * kEnergyBlock + threadIdx.x, planes,
-                                   cnt);
+k_energy(const GroupDev G, int32_t* cnt, const EnergyWalks walks) {
+    energy_walk<kMaxPlanes>(G, blockIdx.y, blockIdx.x * kEnergyBlock + threadIdx.x, walks, cnt);
 }
 
+template <int kMaxPlanes>
 __global__ void __launch_bounds__(kEnergyBlock)
 k_energy_batched(const BatchPlan plan) {
     const BlockPlace at = locate<false>(plan, blockIdx.x);
     const GroupDev G = group_record<false>(plan, at.gi);
     const uint32_t local = at.local;
-    const uint32_t nb = energy_blocks_per_slot(G.V, G.etile);
+    const uint32_t nb = energy_blocks_per_slot(G.L * G.L, G.ewalk.tiles);
     // block-uniform: keeps the slot's address arithmetic on the scalar unit
     const uint32_t g = __builtin_amdgcn_readfirstlane(local / nb);
-    energy_walk<kEnergyWords>(G, g, (local - g * nb) * kEnergyBlock + threadIdx.x, G.etile, G.cnt);
+    energy_walk<kMaxPlanes>(G, g, (local - g * nb) * kEnergyBlock + threadIdx.x, G.ewalk,
+                            G.cnt);
 }
 
 // ---------------------------------------------------------------------------
@@ -1221,9 +1251,12 @@ hipError_t launch_half_sweep(const GroupDev& g, uint32_t colour, const uint32_t*
     return hipGetLastError();
 }
 hipError_t launch_energy(const GroupDev& g, int32_t* cnt, hipStream_t s) {
-    const uint32_t planes = tile_for(g.Ltau, kEnergyPlanesSlot);
-    hipLaunchKernelGGL(k_energy, dim3(energy_blocks_per_slot(g.V, planes), g.N),
-                       dim3(kEnergyBlock), 0, s, g, cnt, planes);
+    const EnergyWalks w = energy_walks(g.Ltau, (uint64_t)g.N * g.V);
+    const dim3 grid(energy_blocks_per_slot(g.L * g.L, w.tiles), g.N), block(kEnergyBlock);
+    if (w.planes <= (uint32_t)kEnergyShort)
+        hipLaunchKernelGGL(k_energy<kEnergyShort>, grid, block, 0, s, g, cnt, w);
+    else
+        hipLaunchKernelGGL(k_energy<kEnergyLong>, grid, block, 0, s, g, cnt, w);
     return hipGetLastError();
 }
 hipError_t launch_pt(const GroupDev& g, const uint32_t* ctr, uint32_t p_add, hipStream_t s) {
@@ -1277,9 +1310,14 @@ hipError_t launch_chunk_fused(const BatchPlan& slots, const uint32_t* ctr, uint3
     return hipGetLastError();
 }
 
-hipError_t launch_energy_batched(const BatchPlan& plan, hipStream_t s) {
+hipError_t launch_energy_batched(const BatchPlan& plan, uint32_t eplanes, hipStream_t s) {
     if (plan.n_blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_energy_batched, dim3(plan.n_blocks), dim3(kEnergyBlock), 0, s, plan);
+    if (eplanes <= (uint32_t)kEnergyShort)
+        hipLaunchKernelGGL(k_energy_batched<kEnergyShort>, dim3(plan.n_blocks), dim3(kEnergyBlock),
+                           0, s, plan);
+    else
+        hipLaunchKernelGGL(k_energy_batched<kEnergyLong>, dim3(plan.n_blocks), dim3(kEnergyBlock),
+                           0, s, plan);
     return hipGetLastError();
 }
 hipError_t launch_pt_batched(const GroupDev* groups, uint32_t n_groups, const uint32_t* ctr,
