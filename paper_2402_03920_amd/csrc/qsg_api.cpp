@@ -331,11 +331,14 @@ qsg_status plain_sweep(qsg_ctx* c, uint32_t t_add) {
     return QSG_OK;
 }
 
-qsg_status plain_pt(qsg_ctx* c, uint32_t p_add) {
+// A PT step after `sweeps` sweeps that the device counters do not hold yet.
+qsg_status plain_pt(qsg_ctx* c, uint32_t sweeps) {
     for (const GroupDev& g : c->gd) {
         QSG_HIP(c, qsg::launch_energy(g, g.cnt, c->stream));
-        QSG_HIP(c, qsg::launch_pt(g, c->d_counters, p_add, c->stream));
-        QSG_HIP(c, qsg::launch_swap_apply(g, c->stream));
+        QSG_HIP(c, qsg::launch_pt(g, c->d_counters, c->stream));
+        const bool last = &g == &c->gd.back();  // every group has read the PT counter
+        QSG_HIP(c, qsg::launch_swap_apply(g, {last ? c->d_counters : nullptr, sweeps, 1},
+                                          c->stream));
     }
     return QSG_OK;
 }
@@ -346,16 +349,16 @@ qsg_status batched_sweep(qsg_ctx* c, hipStream_t s, uint32_t t_add) {
     return QSG_OK;
 }
 
-qsg_status batched_pt(qsg_ctx* c, hipStream_t s, uint32_t p_add) {
+qsg_status batched_pt(qsg_ctx* c, hipStream_t s, uint32_t sweeps) {
     QSG_HIP(c, qsg::launch_energy_batched(c->plan_energy, c->energy_planes, s));
-    QSG_HIP(c, qsg::launch_pt_batched(c->d_groups, (uint32_t)c->gd.size(), c->d_counters, p_add, s));
-    QSG_HIP(c, qsg::launch_swap_apply_batched(c->plan_swap, s));
+    QSG_HIP(c, qsg::launch_pt_batched(c->d_groups, (uint32_t)c->gd.size(), c->d_counters, s));
+    QSG_HIP(c, qsg::launch_swap_apply_batched(c->plan_swap, {c->d_counters, sweeps, 1}, s));
     return QSG_OK;
 }
 
 // One whole PT chunk on stream s: pt_every sweeps (colour passes over all
-// groups, or one fused launch), the energy pass, the PT step, the exchange
-// pass and the counter advance.
+// groups, or one fused launch), the energy pass, the PT step and the exchange
+// pass, which advances the counters.
 qsg_status enqueue_chunk(qsg_ctx* c, hipStream_t s, bool fused) {
     const uint32_t pe = c->cfg.pt_every;
     if (fused) {
@@ -364,9 +367,7 @@ qsg_status enqueue_chunk(qsg_ctx* c, hipStream_t s, bool fused) {
         for (uint32_t i = 0; i < pe; ++i)
             if (qsg_status st = batched_sweep(c, s, i)) return st;
     }
-    if (qsg_status st = batched_pt(c, s, 0)) return st;
-    QSG_HIP(c, qsg::launch_advance(c->d_counters, pe, 1, s));
-    return QSG_OK;
+    return batched_pt(c, s, pe);
 }
 
 qsg_status build_chunk_graph(qsg_ctx* c, bool fused) {
@@ -694,13 +695,11 @@ qsg_status qsg_sweep(qsg_ctx* c, uint32_t n_sweeps, uint32_t flags) {
             }
             const bool pt_now = do_pt && pe > 0 && (c->t + n) % pe == 0;
             if (pt_now) {
-                QSG_HIP(c, qsg::launch_advance(c->d_counters, n, 0, c->stream));
-                qsg_status st = batched ? batched_pt(c, c->stream, 0) : plain_pt(c, 0);
+                qsg_status st = batched ? batched_pt(c, c->stream, n) : plain_pt(c, n);
                 if (st) return st;
-                QSG_HIP(c, qsg::launch_advance(c->d_counters, 0, 1, c->stream));
                 c->p += 1;
             } else {
-                QSG_HIP(c, qsg::launch_advance(c->d_counters, n, 0, c->stream));
+                QSG_HIP(c, qsg::launch_advance({c->d_counters, n, 0}, c->stream));
             }
             done += n;
             c->t += n;
@@ -719,7 +718,6 @@ qsg_status qsg_pt_swap(qsg_ctx* c) {
     if (qsg_status st = check_ctx(c)) return st;
     if (qsg_status st = check_ready(c)) return st;
     if (qsg_status st = batched_pt(c, c->stream, 0)) return st;
-    QSG_HIP(c, qsg::launch_advance(c->d_counters, 0, 1, c->stream));
     c->p += 1;
     return QSG_OK;
 }

@@ -102,7 +102,7 @@ struct GroupDev {
 
 // Launchers (qsg_kernels.hip).  All enqueue on `s` and return the launch
 // status.  `ctr` is the device pair (sweeps done, PT steps done); sweep and
-// PT kernels use ctr[0] + t_add and ctr[1] + p_add as their indices.
+// PT kernels use ctr[0] + t_add and ctr[1] as their indices.
 hipError_t launch_init_couplings(const GroupDev& g, hipStream_t s);
 hipError_t launch_init_spins(const GroupDev& g, hipStream_t s);
 hipError_t launch_init_state(const GroupDev& g, hipStream_t s);
@@ -112,9 +112,16 @@ hipError_t launch_init_state(const GroupDev& g, hipStream_t s);
 hipError_t launch_half_sweep(const GroupDev& g, uint32_t colour, const uint32_t* ctr,
                              uint32_t t_add, hipStream_t s);
 hipError_t launch_energy(const GroupDev& g, int32_t* cnt, hipStream_t s);
-hipError_t launch_pt(const GroupDev& g, const uint32_t* ctr, uint32_t p_add, hipStream_t s);
-hipError_t launch_advance(uint32_t* ctr, uint32_t dt, uint32_t dp, hipStream_t s);
-hipError_t launch_swap_apply(const GroupDev& g, hipStream_t s);
+hipError_t launch_pt(const GroupDev& g, const uint32_t* ctr, hipStream_t s);
+// The device counters (sweeps done, PT steps done) and what to add to them.
+struct Advance {
+    uint32_t* ctr;
+    uint32_t dt, dp;
+};
+hipError_t launch_advance(const Advance& adv, hipStream_t s);
+// The exchange pass is the last launch of a PT step and advances the counters
+// (adv.ctr null: the launch for another group does).
+hipError_t launch_swap_apply(const GroupDev& g, const Advance& adv, hipStream_t s);
 hipError_t launch_zero32(void* p, size_t n_words32, hipStream_t s);
 
 hipError_t launch_philox(const uint32_t* in, uint32_t* out, uint32_t n, hipStream_t s);
@@ -267,8 +274,8 @@ inline EnergyWalks energy_walks(uint32_t Ltau, uint64_t words) {
     return w;
 }
 hipError_t launch_pt_batched(const GroupDev* groups, uint32_t n_groups, const uint32_t* ctr,
-                             uint32_t p_add, hipStream_t s);
-hipError_t launch_swap_apply_batched(const BatchPlan& plan, hipStream_t s);
+                             hipStream_t s);
+hipError_t launch_swap_apply_batched(const BatchPlan& plan, const Advance& adv, hipStream_t s);
 
 // Blocks one group needs in each pass (host and device agree on these).
 // The colour pass gives each thread one column (x, y) of one tau tile of
@@ -280,6 +287,7 @@ __host__ __device__ inline uint32_t swap_blocks(uint32_t V);
 constexpr uint32_t kMaxSlots = 64;  // slots per group (the C ABI's QSG_MAX_GAMMA)
 constexpr int kSweepBlock = 256;   // threads per block of a colour pass
 constexpr uint32_t kWaveSize = 64;
+constexpr int kPtBlock = 1024;   // one block per group: 16 waves share its slots
 constexpr int kSwapBlock = 256;
 
 }  // namespace qsg

@@ -965,171 +965,239 @@ k_energy_batched(const BatchPlan plan) {
 }
 
 // ---------------------------------------------------------------------------
-// Parallel tempering step of one group: 64 threads, thread j = lane j.
-// Turns the pass counters into bond sums, accumulates the measurement sums,
-// then visits pairs g = 0..N-2 in order; `cur` is the configuration that
-// currently sits at slot g (it may have arrived from g-1 in this step).
+// Parallel tempering step of one group: one block, thread j of a wave = lane
+// j.  In order: (1) the waves share the slots: each turns the pass counters
+// of its slots into bond sums, adds them to the measurement sums, and works
+// out what the pair (g, g+1) accepts; (2) the first wave visits the pairs g =
+// 0..N-2 in order, `cur` being the configuration that currently sits at slot
+// g (it may have arrived from g-1 in this step); (3) the waves share the
+// slots again and write the new state.
+//
+// What bounds it: latency alone.  Only (2) is a chain, so everything that
+// does not depend on the pairs before is moved out of it: a pair's random
+// numbers, and its exchange table too, for the table falls with m and so
+// "random number <= entry m" is "m <= most" with a `most` found beforehand
+// (most_accepted).  The chain is left with LDS reads that can run ahead, one
+// comparison and a ballot.  Per launch: 6.5 us for one group of 16 slots, 18.5
+// for 64 of 32, 37 for two of 48 with long tables; one wave doing it all, with
+// a table look-up and a Philox block in every link, took 23, 79 and 114.
 // ---------------------------------------------------------------------------
+struct PtShared {
+    int32_t sp[kMaxSlots][64];     // space-bond sums
+    int32_t e[kMaxSlots][64];      // what the exchange weighs: time bonds, or all
+    uint32_t most[kMaxSlots][64];  // pair (g, g+1) accepts -D = 4m for m <= most
+    uint8_t walker[kMaxSlots][64];
+    uint8_t from[kMaxSlots][64];   // slot that slot g's new configuration comes from
+};
+constexpr uint32_t kAlways = 0xFFFFFFFFu;
+
+// Entries of a falling table that are >= r (r > 0).  The entries are 2^32
+// q^m rounded down, so the logarithms of r and of the first entry give the
+// count to one or two; four entries around it settle it, or else a search of
+// the table.
+__device__ __forceinline__ uint32_t most_accepted(const uint32_t* __restrict__ thr, uint32_t len,
+                                                  uint32_t r) {
+    if (len == 0) return 0;
+    constexpr float kUnit = 2.3283064365386963e-10f;  // 2^-32
+    const float lq = log1pf(-(float)(0u - thr[0]) * kUnit);
+    const float lr = r < 0x80000000u ? logf((float)r * kUnit) : log1pf(-(float)(0u - r) * kUnit);
+    const uint32_t near = (uint32_t)fminf(fmaxf(lr / lq, 0.f), (float)len);
+    const uint32_t base = near > 2 ? near - 2 : 0;
+    uint32_t n = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t t = thr[min(base + k, len - 1)];
+        n += (base + k < len && t >= r) ? 1u : 0u;
+    }
+    if ((n > 0 || base == 0) && (n < 4 || base + 4 >= len)) return base + n;
+    uint32_t lo = 0, hi = len;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (thr[mid] >= r)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
 __device__ __forceinline__ void pt_group(const GroupDev& G, uint32_t p) {
-    // The pass's energies and the walker labels of this group, lane j's
-    // column of each: the pairs are visited in order, each seeing the state
-    // the previous one left, so the chain runs on LDS instead of on global
-    // loads.  One wave per group: no barriers needed.
-    __shared__ int32_t s_sp[kMaxSlots][64], s_t[kMaxSlots][64];
-    __shared__ uint32_t s_w[kMaxSlots][64];
-    __shared__ uint64_t s_mask[kMaxSlots];
-    const uint32_t j = threadIdx.x;
+    __shared__ PtShared sh;
+    const uint32_t j = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr uint32_t kWaves = kPtBlock / 64;
     const uint32_t N = G.N;
     const int32_t V = (int32_t)G.V;
-    for (uint32_t g = 0; g < N; ++g) {
-        int32_t* c = G.cnt + g * kCntStride;
-        const int32_t bsp = 2 * V - 2 * c[j];
-        const int32_t bt = V - 2 * c[64 + j];
-        c[j] = 0;
-        c[64 + j] = 0;
-        s_sp[g][j] = bsp;
-        s_t[g][j] = bt;
-        s_w[g][j] = G.walker[g * 64 + j];
-        int64_t* sm = G.sums + (size_t)g * kSumStride;
-        sm[j] += bsp;
-        sm[64 + j] += bt;
-        const uint32_t u = (uint32_t)(V - bt) >> 1;
-        atomicAdd(&G.hist[g * kHistBins + (uint32_t)(((uint64_t)u * kHistBins) / ((uint64_t)V + 1))], 1u);
-        if (j < 32) {
-            const int64_t q = (int64_t)V - 2 * (int64_t)c[128 + j];
-            c[128 + j] = 0;
-            sm[128 + j] += q;
-            sm[160 + j] += q * q;
-        }
-    }
-    int32_t cur_sp = s_sp[0][j], cur_t = s_t[0][j];
-    uint32_t cur_w = s_w[0][j];
-    // per-pair table lengths and equal-slot flags, lane g holding pair g's
-    const uint32_t my_len = j + 1 < N ? G.sw_len[j] : 0u;
-    const uint32_t my_eq = j + 1 < N ? (uint32_t)G.sw_eq[j] : 0u;
-    uint64_t any = 0;
-    for (uint32_t g = 0; g + 1 < N; ++g) {
-        const int32_t nx_sp = s_sp[g + 1][j];
-        const int32_t nx_t = s_t[g + 1][j];
-        const uint32_t nx_w = s_w[g + 1][j];
-        // |Bsp| <= 2V and |Bt| <= V with V <= 2^29: the difference of two
-        // whole energies needs 64 bits, that of two time-bond sums does not
-        const int64_t D = G.exch_all ? ((int64_t)nx_sp + nx_t) - ((int64_t)cur_sp + cur_t)
-                                     : (int64_t)(nx_t - cur_t);
-        bool accept;
-        const uint32_t len = __builtin_amdgcn_readlane(my_len, g);
-        if (__builtin_amdgcn_readlane(my_eq, g) || D >= 0) {
-            accept = true;
-        } else {
-            const uint32_t m = (uint32_t)((uint64_t)(-D) >> 2);
-            const uint32_t th = (m >= 1 && m <= len) ? G.sw_thr[(size_t)g * G.sw_cap + (m - 1)] : 0u;
+    for (uint32_t g = wave; g < N; g += kWaves) {
+        int32_t* __restrict__ c = G.cnt + g * kCntStride;
+        int64_t* __restrict__ sm = G.sums + (size_t)g * kSumStride;
+        const int32_t csp = c[j], ct = c[64 + j], cq = j < 32 ? c[128 + j] : 0;
+        const int64_t s0 = sm[j], s1 = sm[64 + j];
+        const int64_t s2 = j < 32 ? sm[128 + j] : 0, s3 = j < 32 ? sm[160 + j] : 0;
+        const uint32_t w = G.walker[g * 64 + j];
+        uint32_t most = 0;
+        if (g + 1 < N) {
             const uint4 o = philox(make_uint4(j >> 2, p, (1u << 24) | g, G.gid), G.key0, G.key1);
             const uint32_t sel = j & 3u;
             const uint32_t r = sel == 0 ? o.x : sel == 1 ? o.y : sel == 2 ? o.z : o.w;
-            accept = r <= th;
+            most = G.sw_eq[g] || r == 0
+                       ? kAlways
+                       : most_accepted(G.sw_thr + (size_t)g * G.sw_cap, G.sw_len[g], r);
         }
-        const uint64_t mask = __ballot((int)accept);
-        if (accept) {  // slot g takes the next configuration; cur moves up
-            s_sp[g][j] = nx_sp;
-            s_t[g][j] = nx_t;
-            s_w[g][j] = nx_w;
-        } else {       // cur stays at g; the next one becomes cur
-            s_sp[g][j] = cur_sp;
-            s_t[g][j] = cur_t;
-            s_w[g][j] = cur_w;
-            cur_sp = nx_sp;
-            cur_t = nx_t;
-            cur_w = nx_w;
+        // |bsp| <= 2V and |bt| <= V with V <= 2^29: their sum fits 32 bits,
+        // and the difference of two such sums fits 32 bits without a sign
+        const int32_t bsp = 2 * V - 2 * csp;
+        const int32_t bt = V - 2 * ct;
+        sh.sp[g][j] = bsp;
+        sh.e[g][j] = G.exch_all ? bsp + bt : bt;
+        sh.most[g][j] = most;
+        sh.walker[g][j] = (uint8_t)w;
+        c[j] = 0;
+        c[64 + j] = 0;
+        sm[j] = s0 + bsp;
+        sm[64 + j] = s1 + bt;
+        if (j < 32) {
+            const int64_t q = (int64_t)V - 2 * (int64_t)cq;
+            c[128 + j] = 0;
+            sm[128 + j] = s2 + q;
+            sm[160 + j] = s3 + q * q;
         }
-        if (j == 0) s_mask[g] = mask;
-        any |= mask;
+        // floor(u * bins / (V + 1)): both below 2^53 and the quotient, if not
+        // whole, at least 2^-30 away from a whole number, so the rounded
+        // quotient has the same floor
+        const uint32_t u = (uint32_t)(V - bt) >> 1;
+        const uint32_t bin = (uint32_t)(((double)u * kHistBins) / ((double)V + 1.0));
+        atomicAdd(&G.hist[g * kHistBins + bin], 1u);
     }
-    s_sp[N - 1][j] = cur_sp;
-    s_t[N - 1][j] = cur_t;
-    s_w[N - 1][j] = cur_w;
-    for (uint32_t g = 0; g < N; ++g) {
-        G.E[(g * 64 + j) * 2 + 0] = s_sp[g][j];
-        G.E[(g * 64 + j) * 2 + 1] = s_t[g][j];
-        G.walker[g * 64 + j] = s_w[g][j];
+    __syncthreads();
+    if (wave == 0) {
+        const uint64_t acc0 = j + 1 < N ? G.acc[j] : 0;
+        int32_t cur = sh.e[0][j];
+        uint32_t cur_from = 0;
+        uint64_t my_mask = 0, any = 0;
+        for (uint32_t g = 0; g + 1 < N; ++g) {
+            const int32_t nx = sh.e[g + 1][j];
+            const uint32_t most = sh.most[g][j];
+            // D = nx - cur: accepted if D >= 0, else if m = -D / 4 <= most
+            const uint32_t m = ((uint32_t)cur - (uint32_t)nx) >> 2;
+            const bool accept = nx >= cur || m - 1u < most || most == kAlways;
+            const uint64_t mask = __ballot((int)accept);
+            // accepted: slot g takes the next configuration, cur moves up;
+            // else cur stays at g and the next one becomes cur
+            sh.from[g][j] = (uint8_t)(accept ? g + 1 : cur_from);
+            cur = accept ? cur : nx;
+            cur_from = accept ? cur_from : g + 1;
+            my_mask = j == g ? mask : my_mask;
+            any |= mask;
+        }
+        sh.from[N - 1][j] = (uint8_t)cur_from;
+        if (j + 1 < N) {
+            G.swaplog[(size_t)(p % G.log_cap) * (N - 1) + j] = my_mask;
+            G.acc[j] = acc0 + (uint64_t)__popcll(my_mask);
+            G.lastmask[j] = my_mask;
+        }
+        if (j == 0) G.lastmask[N - 1] = any ? 1ull : 0ull;
     }
-    __syncthreads();  // s_mask complete (one wave: cheap)
-    if (j + 1 < N) {
-        const uint64_t mask = s_mask[j];
-        G.swaplog[(size_t)(p % G.log_cap) * (N - 1) + j] = mask;
-        G.acc[j] += (uint64_t)__popcll(mask);
-        G.lastmask[j] = mask;
-    }
-    if (j == 0) G.lastmask[N - 1] = any ? 1ull : 0ull;
-
+    __syncthreads();
     // round trips 0 -> N-1 -> 0; this step ends at PT time p+1.  One slot
     // has no exchange partner and no pair of distinct end slots: its walkers
     // never move, and no round trip is counted.
-    if (N < 2) return;
     const uint32_t now = p + 1;
-    RoundTrip& r0 = G.rt[s_w[0][j] * 64 + j];
-    if (r0.state == 2) {
-        r0.count += 1;
-        r0.sum += (uint64_t)(now - r0.t_last);
-        r0.t_last = now;
-        r0.state = 1;
-    } else if (r0.state == 0) {
-        r0.t_last = now;
-        r0.state = 1;
+    if (wave == kWaves - 1 && N >= 2) {
+        RoundTrip& r0 = G.rt[sh.walker[sh.from[0][j]][j] * 64 + j];
+        if (r0.state == 2) {
+            r0.count += 1;
+            r0.sum += (uint64_t)(now - r0.t_last);
+            r0.t_last = now;
+            r0.state = 1;
+        } else if (r0.state == 0) {
+            r0.t_last = now;
+            r0.state = 1;
+        }
     }
-    RoundTrip& rtop = G.rt[s_w[N - 1][j] * 64 + j];
-    if (rtop.state == 1) rtop.state = 2;
+    if (wave == kWaves - 2 && N >= 2) {  // another walker's record
+        RoundTrip& rtop = G.rt[sh.walker[sh.from[N - 1][j]][j] * 64 + j];
+        if (rtop.state == 1) rtop.state = 2;
+    }
+    for (uint32_t g = wave; g < N; g += kWaves) {
+        const uint32_t f = sh.from[g][j];
+        const int32_t bsp = sh.sp[f][j], e = sh.e[f][j];
+        G.E[(g * 64 + j) * 2 + 0] = bsp;
+        G.E[(g * 64 + j) * 2 + 1] = G.exch_all ? e - bsp : e;
+        G.walker[g * 64 + j] = sh.walker[f][j];
+    }
 }
 
-__global__ void __launch_bounds__(64)
-k_pt(const GroupDev G, const uint32_t* __restrict__ ctr, uint32_t p_add) {
-    pt_group(G, ctr[1] + p_add);
+__global__ void __launch_bounds__(kPtBlock)
+k_pt(const GroupDev G, const uint32_t* __restrict__ ctr) {
+    pt_group(G, ctr[1]);
 }
 
-__global__ void __launch_bounds__(64)
-k_pt_batched(const GroupDev* __restrict__ groups, const uint32_t* __restrict__ ctr, uint32_t p_add) {
+__global__ void __launch_bounds__(kPtBlock)
+k_pt_batched(const GroupDev* __restrict__ groups, const uint32_t* __restrict__ ctr) {
     const GroupDev G = uniform_record(groups + blockIdx.x);
-    pt_group(G, ctr[1] + p_add);
+    pt_group(G, ctr[1]);
 }
 
 // Sweep and PT counters live on the device so that a captured graph can be
 // replayed: every launch reads them and adds its own offset.
-__global__ void k_advance(uint32_t* ctr, uint32_t dt, uint32_t dp) {
-    if (threadIdx.x == 0) {
-        ctr[0] += dt;
-        ctr[1] += dp;
-    }
+__device__ __forceinline__ void advance_counters(const Advance& a) {
+    a.ctr[0] += a.dt;
+    a.ctr[1] += a.dp;
+}
+__global__ void k_advance(const Advance a) {
+    if (threadIdx.x == 0) advance_counters(a);
 }
 
 // ---------------------------------------------------------------------------
 // Apply the accepted exchanges of the latest PT step to the spins: at every
 // site, the pairs' masked bit exchanges in ascending order (each word read
-// and written once).
+// and written once).  The slots' words are loaded a batch ahead of the
+// stores, which the compiler may not reorder: on small samples the pass lasts
+// as long as one site's chain (4.2 us for 16 slots,
+// 5.7 with one load per link), on large ones as long as the copy of
+// the spins (171 us on 537 MB).  The pass reads neither counter, and it is
+// the last of a PT step: its first thread advances them, which saves the
+// launch of its own that this took (4 us).
 // ---------------------------------------------------------------------------
+constexpr uint32_t kSwapBatch = 8;
 __device__ __forceinline__ void swap_site(const GroupDev& G, uint32_t site) {
-    const uint32_t N = G.N;
+    const uint32_t pairs = G.N - 1;
     uint64_t* S = G.spins + site;
     const size_t V = G.V;
     uint64_t cur = S[0];  // running content of slot g
     uint64_t orig = cur;  // what slot g held before this step
-    for (uint32_t g = 0; g + 1 < N; ++g) {
-        const uint64_t nx = S[(size_t)(g + 1) * V];
-        const uint64_t d = (cur ^ nx) & G.lastmask[g];
-        cur ^= d;
-        if (cur != orig) S[(size_t)g * V] = cur;
-        cur = nx ^ d;
-        orig = nx;
+    for (uint32_t g0 = 0; g0 < pairs; g0 += kSwapBatch) {
+        uint64_t next[kSwapBatch], mask[kSwapBatch];
+#pragma unroll
+        for (uint32_t k = 0; k < kSwapBatch; ++k) {
+            const uint32_t g = min(g0 + k, pairs - 1);  // block-uniform
+            next[k] = S[(size_t)(g + 1) * V];
+            mask[k] = G.lastmask[g];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kSwapBatch; ++k) {
+            if (g0 + k >= pairs) break;
+            const uint64_t d = (cur ^ next[k]) & mask[k];
+            cur ^= d;
+            if (cur != orig) S[(size_t)(g0 + k) * V] = cur;
+            cur = next[k] ^ d;
+            orig = next[k];
+        }
     }
-    if (cur != orig) S[(size_t)(N - 1) * V] = cur;
+    if (cur != orig) S[(size_t)pairs * V] = cur;
 }
 
-__global__ void __launch_bounds__(kSwapBlock) k_swap_apply(const GroupDev G) {
+__global__ void __launch_bounds__(kSwapBlock) k_swap_apply(const GroupDev G, const Advance adv) {
+    if (adv.ctr && (blockIdx.x | threadIdx.x) == 0) advance_counters(adv);
     if (G.N < 2 || G.lastmask[G.N - 1] == 0) return;
     const uint32_t site = blockIdx.x * kSwapBlock + threadIdx.x;
     if (site < G.V) swap_site(G, site);
 }
 
 __global__ void __launch_bounds__(kSwapBlock)
-k_swap_apply_batched(const BatchPlan plan) {
+k_swap_apply_batched(const BatchPlan plan, const Advance adv) {
+    if ((blockIdx.x | threadIdx.x) == 0) advance_counters(adv);
     const BlockPlace at = locate<false>(plan, blockIdx.x);
     const GroupDev G = group_record<false>(plan, at.gi);
     if (G.N < 2 || G.lastmask[G.N - 1] == 0) return;
@@ -1259,12 +1327,12 @@ hipError_t launch_energy(const GroupDev& g, int32_t* cnt, hipStream_t s) {
         hipLaunchKernelGGL(k_energy<kEnergyLong>, grid, block, 0, s, g, cnt, w);
     return hipGetLastError();
 }
-hipError_t launch_pt(const GroupDev& g, const uint32_t* ctr, uint32_t p_add, hipStream_t s) {
-    hipLaunchKernelGGL(k_pt, dim3(1), dim3(64), 0, s, g, ctr, p_add);
+hipError_t launch_pt(const GroupDev& g, const uint32_t* ctr, hipStream_t s) {
+    hipLaunchKernelGGL(k_pt, dim3(1), dim3(kPtBlock), 0, s, g, ctr);
     return hipGetLastError();
 }
-hipError_t launch_swap_apply(const GroupDev& g, hipStream_t s) {
-    hipLaunchKernelGGL(k_swap_apply, dim3(swap_blocks(g.V)), dim3(kSwapBlock), 0, s, g);
+hipError_t launch_swap_apply(const GroupDev& g, const Advance& adv, hipStream_t s) {
+    hipLaunchKernelGGL(k_swap_apply, dim3(swap_blocks(g.V)), dim3(kSwapBlock), 0, s, g, adv);
     return hipGetLastError();
 }
 hipError_t launch_zero32(void* p, size_t n, hipStream_t s) {
@@ -1321,18 +1389,19 @@ hipError_t launch_energy_batched(const BatchPlan& plan, uint32_t eplanes, hipStr
     return hipGetLastError();
 }
 hipError_t launch_pt_batched(const GroupDev* groups, uint32_t n_groups, const uint32_t* ctr,
-                             uint32_t p_add, hipStream_t s) {
+                             hipStream_t s) {
     if (n_groups == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pt_batched, dim3(n_groups), dim3(64), 0, s, groups, ctr, p_add);
+    hipLaunchKernelGGL(k_pt_batched, dim3(n_groups), dim3(kPtBlock), 0, s, groups, ctr);
     return hipGetLastError();
 }
-hipError_t launch_advance(uint32_t* ctr, uint32_t dt, uint32_t dp, hipStream_t s) {
-    hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, s, ctr, dt, dp);
+hipError_t launch_advance(const Advance& adv, hipStream_t s) {
+    hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, s, adv);
     return hipGetLastError();
 }
-hipError_t launch_swap_apply_batched(const BatchPlan& plan, hipStream_t s) {
-    if (plan.n_blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_swap_apply_batched, dim3(plan.n_blocks), dim3(kSwapBlock), 0, s, plan);
+hipError_t launch_swap_apply_batched(const BatchPlan& plan, const Advance& adv, hipStream_t s) {
+    if (plan.n_blocks == 0) return launch_advance(adv, s);  // groups of one slot only
+    hipLaunchKernelGGL(k_swap_apply_batched, dim3(plan.n_blocks), dim3(kSwapBlock), 0, s, plan,
+                       adv);
     return hipGetLastError();
 }
 
