@@ -256,6 +256,11 @@ struct qsg_ctx {
     GroupDev* d_groups = nullptr;
     qsg::BatchPlan plan_slots{};      // one block per slot (fused sweeps)
     uint32_t fused_lds_words = 0;     // slots at most this big run from LDS
+    // pinned buffer of the readings: the groups' offsets, then the reading
+    // (at most kStageBytes of it); grows to what was asked for, freed with
+    // the context
+    uint8_t* stage = nullptr;
+    size_t stage_bytes = 0;
     hipGraphExec_t chunk_exec[2] = {nullptr, nullptr};  // [fused]
     hipGraph_t chunk_graph[2] = {nullptr, nullptr};
     bool failed = false;
@@ -350,7 +355,7 @@ qsg_status batched_sweep(qsg_ctx* c, hipStream_t s, uint32_t t_add) {
 }
 
 qsg_status batched_pt(qsg_ctx* c, hipStream_t s, uint32_t sweeps) {
-    QSG_HIP(c, qsg::launch_energy_batched(c->plan_energy, c->energy_planes, s));
+    QSG_HIP(c, qsg::launch_energy_batched(c->plan_energy, c->energy_planes, false, s));
     QSG_HIP(c, qsg::launch_pt_batched(c->d_groups, (uint32_t)c->gd.size(), c->d_counters, s));
     QSG_HIP(c, qsg::launch_swap_apply_batched(c->plan_swap, {c->d_counters, sweeps, 1}, s));
     return QSG_OK;
@@ -722,23 +727,65 @@ qsg_status qsg_pt_swap(qsg_ctx* c) {
     return QSG_OK;
 }
 
+namespace {
+
+// Bytes of one group's reading; 0 for an unknown one.
+size_t reading_bytes(const qsg_ctx* c, const qsg_group_desc& d, uint32_t what) {
+    const size_t N = d.n_gamma, pairs = N > 1 ? N - 1 : 1;
+    switch (what) {
+        case QSG_M_ENERGY: return N * 64 * 2 * 4;
+        case QSG_M_OVERLAP: return N * 32 * 8;
+        case QSG_M_ACCEPT: return pairs * 8;
+        case QSG_M_WALKERS: return N * 64;
+        case QSG_M_SWAPLOG: return (size_t)c->cfg.swaplog_cap * pairs * 8;
+        case QSG_M_ROUNDTRIP: return N * 64 * sizeof(qsg_roundtrip);
+        case QSG_M_SUMS: return N * qsg::kSumStride * 8;
+        case QSG_M_HIST: return N * qsg::kHistBins * 4;
+        default: return 0;
+    }
+}
+
+qsg::Reading reading_kind(uint32_t what) {
+    switch (what) {
+        case QSG_M_ENERGY: return qsg::Reading::energy;
+        case QSG_M_OVERLAP: return qsg::Reading::overlap;
+        case QSG_M_ACCEPT: return qsg::Reading::accepts;
+        case QSG_M_WALKERS: return qsg::Reading::walkers;
+        case QSG_M_SWAPLOG: return qsg::Reading::swaplog;
+        case QSG_M_ROUNDTRIP: return qsg::Reading::roundtrips;
+        case QSG_M_SUMS: return qsg::Reading::sums;
+        default: return qsg::Reading::hist;
+    }
+}
+
+constexpr size_t kStageBytes = 16u << 20;
+
+qsg_status grow_stage(qsg_ctx* c, size_t bytes) {
+    if (bytes <= c->stage_bytes) return QSG_OK;
+    if (c->stage) QSG_HIP(c, hipHostFree(c->stage));
+    c->stage = nullptr;
+    c->stage_bytes = 0;
+    void* p = nullptr;
+    QSG_HIP(c, hipHostMalloc(&p, bytes, hipHostMallocDefault));
+    c->stage = static_cast<uint8_t*>(p);
+    c->stage_bytes = bytes;
+    return QSG_OK;
+}
+
+}  // namespace
+
 qsg_status qsg_measure(qsg_ctx* c, uint32_t what, void* host_out, size_t bytes) {
     if (qsg_status st = check_ctx(c)) return st;
     if (!host_out) return fail(c, QSG_E_INVALID, "host_out is null");
+    const uint32_t n = (uint32_t)c->desc.size();
     size_t need = 0;
-    for (const auto& d : c->desc) {
-        const size_t N = d.n_gamma, pairs = N > 1 ? N - 1 : 1;
-        switch (what) {
-            case QSG_M_ENERGY: need += N * 64 * 2 * 4; break;
-            case QSG_M_OVERLAP: need += N * 32 * 8; break;
-            case QSG_M_ACCEPT: need += pairs * 8; break;
-            case QSG_M_WALKERS: need += N * 64; break;
-            case QSG_M_SWAPLOG: need += (size_t)c->cfg.swaplog_cap * pairs * 8; break;
-            case QSG_M_ROUNDTRIP: need += N * 64 * sizeof(qsg_roundtrip); break;
-            case QSG_M_SUMS: need += N * qsg::kSumStride * 8; break;
-            case QSG_M_HIST: need += N * qsg::kHistBins * 4; break;
-            case QSG_M_COUNTERS: need = 16; break;
-            default: return fail(c, QSG_E_INVALID, "unknown measurement %u", what);
+    if (what == QSG_M_COUNTERS) {
+        need = 16;
+    } else {
+        for (const auto& d : c->desc) {
+            const size_t b = reading_bytes(c, d, what);
+            if (b == 0) return fail(c, QSG_E_INVALID, "unknown measurement %u", what);
+            need += b;
         }
     }
     if (bytes < need) return fail(c, QSG_E_BUFFER, "measure needs %zu bytes, got %zu", need, bytes);
@@ -750,69 +797,43 @@ qsg_status qsg_measure(qsg_ctx* c, uint32_t what, void* host_out, size_t bytes) 
     }
     if (what == QSG_M_ENERGY || what == QSG_M_OVERLAP) {
         if (!c->spins_ready) return fail(c, QSG_E_STATE, "spins not initialised");
-        for (const GroupDev& g : c->gd) {
-            QSG_HIP(c, qsg::launch_zero32(g.meas, (size_t)g.N * qsg::kCntStride, s));
-            QSG_HIP(c, qsg::launch_energy(g, g.meas, s));
-        }
-        uint8_t* o = static_cast<uint8_t*>(host_out);
-        std::vector<int32_t> cnt;
-        QSG_HIP(c, hipStreamSynchronize(s));
-        for (const GroupDev& g : c->gd) {
-            cnt.resize((size_t)g.N * qsg::kCntStride);
-            QSG_HIP(c, hipMemcpy(cnt.data(), g.meas, cnt.size() * 4, hipMemcpyDeviceToHost));
-            const int64_t V = g.V;
-            if (what == QSG_M_ENERGY) {
-                int32_t* e = reinterpret_cast<int32_t*>(o);
-                for (uint32_t k = 0; k < g.N; ++k)
-                    for (int j = 0; j < 64; ++j) {
-                        e[(k * 64 + j) * 2 + 0] = (int32_t)(2 * V - 2 * cnt[k * qsg::kCntStride + j]);
-                        e[(k * 64 + j) * 2 + 1] = (int32_t)(V - 2 * cnt[k * qsg::kCntStride + 64 + j]);
-                    }
-                o += (size_t)g.N * 64 * 2 * 4;
-            } else {
-                int64_t* q = reinterpret_cast<int64_t*>(o);
-                for (uint32_t k = 0; k < g.N; ++k)
-                    for (int p = 0; p < 32; ++p)
-                        q[k * 32 + p] = V - 2 * (int64_t)cnt[k * qsg::kCntStride + 128 + p];
-                o += (size_t)g.N * 32 * 8;
-            }
-        }
-        return QSG_OK;
+        QSG_HIP(c, qsg::launch_zero_meas(c->d_groups, n, s));
+        QSG_HIP(c, qsg::launch_energy_batched(c->plan_energy, c->energy_planes, true, s));
     }
-    QSG_HIP(c, hipStreamSynchronize(s));
+    // Runs of groups whose readings fit the staging buffer: one launch and
+    // one wait each.  A group that does not fit alone (a swap log of more
+    // than 16 MiB) is copied by itself.
     uint8_t* o = static_cast<uint8_t*>(host_out);
-    for (const GroupDev& g : c->gd) {
-        const size_t N = g.N, pairs = N > 1 ? N - 1 : 1;
-        switch (what) {
-            case QSG_M_ACCEPT:
-                QSG_HIP(c, hipMemcpy(o, g.acc, pairs * 8, hipMemcpyDeviceToHost));
-                o += pairs * 8;
-                break;
-            case QSG_M_WALKERS: {
-                std::vector<uint32_t> w(N * 64);
-                QSG_HIP(c, hipMemcpy(w.data(), g.walker, w.size() * 4, hipMemcpyDeviceToHost));
-                for (size_t i = 0; i < w.size(); ++i) o[i] = (uint8_t)w[i];
-                o += N * 64;
-                break;
-            }
-            case QSG_M_SWAPLOG:
-                QSG_HIP(c, hipMemcpy(o, g.swaplog, (size_t)g.log_cap * pairs * 8,
-                                     hipMemcpyDeviceToHost));
-                o += (size_t)g.log_cap * pairs * 8;
-                break;
-            case QSG_M_ROUNDTRIP:
-                QSG_HIP(c, hipMemcpy(o, g.rt, N * 64 * sizeof(RoundTrip), hipMemcpyDeviceToHost));
-                o += N * 64 * sizeof(RoundTrip);
-                break;
-            case QSG_M_SUMS:
-                QSG_HIP(c, hipMemcpy(o, g.sums, N * qsg::kSumStride * 8, hipMemcpyDeviceToHost));
-                o += N * qsg::kSumStride * 8;
-                break;
-            case QSG_M_HIST:
-                QSG_HIP(c, hipMemcpy(o, g.hist, N * qsg::kHistBins * 4, hipMemcpyDeviceToHost));
-                o += N * qsg::kHistBins * 4;
-                break;
+    const size_t head = align_up((size_t)n * 8);
+    for (uint32_t i0 = 0; i0 < n;) {
+        size_t used = 0;
+        uint32_t i1 = i0;
+        for (; i1 < n; ++i1) {
+            const size_t b = reading_bytes(c, c->desc[i1], what);
+            if (used + b > kStageBytes) break;
+            used += b;
         }
+        if (i1 == i0) {
+            const size_t b = reading_bytes(c, c->desc[i0], what);
+            QSG_HIP(c, hipStreamSynchronize(s));
+            QSG_HIP(c, hipMemcpy(o, c->gd[i0].swaplog, b, hipMemcpyDeviceToHost));
+            o += b;
+            ++i0;
+            continue;
+        }
+        if (qsg_status st = grow_stage(c, head + used)) return st;
+        uint64_t* off = reinterpret_cast<uint64_t*>(c->stage);
+        uint64_t at = 0;
+        for (uint32_t i = i0; i < i1; ++i) {
+            off[i - i0] = at;
+            at += reading_bytes(c, c->desc[i], what);
+        }
+        QSG_HIP(c, qsg::launch_read(c->d_groups + i0, i1 - i0, reading_kind(what), off,
+                                    c->stage + head, s));
+        QSG_HIP(c, hipStreamSynchronize(s));
+        std::memcpy(o, c->stage + head, used);
+        o += used;
+        i0 = i1;
     }
     return QSG_OK;
 }
@@ -1041,6 +1062,7 @@ void qsg_destroy(qsg_ctx* c) {
     (void)hipStreamSynchronize(c->stream);
     destroy_graph(c);
     if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
+    if (c->stage) (void)hipHostFree(c->stage);
     delete c;
 }
 

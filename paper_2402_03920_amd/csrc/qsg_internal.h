@@ -122,7 +122,6 @@ hipError_t launch_advance(const Advance& adv, hipStream_t s);
 // The exchange pass is the last launch of a PT step and advances the counters
 // (adv.ctr null: the launch for another group does).
 hipError_t launch_swap_apply(const GroupDev& g, const Advance& adv, hipStream_t s);
-hipError_t launch_zero32(void* p, size_t n_words32, hipStream_t s);
 
 hipError_t launch_philox(const uint32_t* in, uint32_t* out, uint32_t n, hipStream_t s);
 hipError_t launch_philox_probe(uint32_t* out, uint32_t n, uint32_t blocks, uint64_t key,
@@ -216,8 +215,16 @@ inline BatchPlan make_plan(const GroupDev* groups, const uint32_t* d_prefix,
 }
 hipError_t launch_half_sweep_batched(const BatchPlan& plan, uint32_t colour, const uint32_t* ctr,
                                      uint32_t t_add, hipStream_t s);
-// eplanes: the deepest walk among the plan's groups.
-hipError_t launch_energy_batched(const BatchPlan& plan, uint32_t eplanes, hipStream_t s);
+// eplanes: the deepest walk among the plan's groups.  The counts are added
+// to the groups' pass counters, or (`reading`) to their `meas` arrays.
+hipError_t launch_energy_batched(const BatchPlan& plan, uint32_t eplanes, bool reading,
+                                 hipStream_t s);
+hipError_t launch_zero_meas(const GroupDev* groups, uint32_t n_groups, hipStream_t s);
+// Readings of groups[0 .. n_groups) into one buffer that device and host see:
+// group i's starts at byte offsets[i], in the C ABI's layout.
+enum class Reading : uint32_t { energy, overlap, walkers, accepts, swaplog, roundtrips, sums, hist };
+hipError_t launch_read(const GroupDev* groups, uint32_t n_groups, Reading what,
+                       const uint64_t* offsets, void* out, hipStream_t s);
 // Fused sweeps over every slot (one block per slot, `slots.prefix` counts
 // slots per group): n_sweeps sweeps in one launch; slots of at most
 // lds_words words run from LDS.

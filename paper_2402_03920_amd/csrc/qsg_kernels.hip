@@ -953,7 +953,7 @@ k_energy(const GroupDev G, int32_t* cnt, const EnergyWalks walks) {
 
 template <int kMaxPlanes>
 __global__ void __launch_bounds__(kEnergyBlock)
-k_energy_batched(const BatchPlan plan) {
+k_energy_batched(const BatchPlan plan, uint32_t reading) {
     const BlockPlace at = locate<false>(plan, blockIdx.x);
     const GroupDev G = group_record<false>(plan, at.gi);
     const uint32_t local = at.local;
@@ -961,7 +961,7 @@ k_energy_batched(const BatchPlan plan) {
     // block-uniform: keeps the slot's address arithmetic on the scalar unit
     const uint32_t g = __builtin_amdgcn_readfirstlane(local / nb);
     energy_walk<kMaxPlanes>(G, g, (local - g * nb) * kEnergyBlock + threadIdx.x, G.ewalk,
-                            G.cnt);
+                            reading ? G.meas : G.cnt);
 }
 
 // ---------------------------------------------------------------------------
@@ -1206,6 +1206,60 @@ k_swap_apply_batched(const BatchPlan plan, const Advance adv) {
 }
 
 // ---------------------------------------------------------------------------
+// Readings: every group's region into one packed buffer in pinned host
+// memory, so that an ensemble costs one launch and one wait instead of one
+// copy per group: energies, sums and exchange counts of 64 groups of 32 slots
+// took 4.5 ms that way and take 1.  Bound by launch and bus latency, on
+// megabytes by the bus.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(256)
+k_zero_meas(const GroupDev* __restrict__ groups) {
+    const GroupDev G = uniform_record(groups + blockIdx.x);
+    for (uint32_t i = threadIdx.x; i < G.N * kCntStride; i += 256) G.meas[i] = 0;
+}
+
+__device__ __forceinline__ void read_raw(uint64_t* __restrict__ out, const void* src, size_t words,
+                                         uint32_t first, uint32_t step) {
+    for (size_t i = first; i < words; i += step) out[i] = static_cast<const uint64_t*>(src)[i];
+}
+
+__global__ void __launch_bounds__(256)
+k_read(const GroupDev* __restrict__ groups, Reading what, const uint64_t* __restrict__ offsets,
+       uint8_t* __restrict__ out) {
+    const GroupDev G = uniform_record(groups + blockIdx.x);
+    uint8_t* o = out + offsets[blockIdx.x];
+    const uint32_t first = blockIdx.y * 256 + threadIdx.x, step = gridDim.y * 256;
+    const uint32_t N = G.N, pairs = N > 1 ? N - 1 : 1;
+    const int32_t V = (int32_t)G.V;
+    uint64_t* o64 = (uint64_t*)o;
+    switch (what) {
+        case Reading::energy:
+            for (uint32_t i = first; i < N * 64; i += step) {
+                const int32_t* c = G.meas + (i >> 6) * kCntStride + (i & 63u);
+                ((int2*)o)[i] = make_int2(2 * V - 2 * c[0], V - 2 * c[64]);
+            }
+            break;
+        case Reading::overlap:
+            for (uint32_t i = first; i < N * 32; i += step)
+                ((int64_t*)o)[i] =
+                    (int64_t)V - 2 * (int64_t)G.meas[(i >> 5) * kCntStride + 128 + (i & 31u)];
+            break;
+        case Reading::walkers:
+            for (uint32_t i = first; i < N * 64; i += step) o[i] = (uint8_t)G.walker[i];
+            break;
+        case Reading::accepts: read_raw(o64, G.acc, pairs, first, step); break;
+        case Reading::swaplog:
+            read_raw(o64, G.swaplog, (size_t)G.log_cap * pairs, first, step);
+            break;
+        case Reading::roundtrips:
+            read_raw(o64, G.rt, (size_t)N * 64 * (sizeof(RoundTrip) / 8), first, step);
+            break;
+        case Reading::sums: read_raw(o64, G.sums, (size_t)N * kSumStride, first, step); break;
+        case Reading::hist: read_raw(o64, G.hist, (size_t)N * kHistBins / 2, first, step); break;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Initialisation.
 // ---------------------------------------------------------------------------
 // Couplings: lane j has J_{i,d} = -1 iff bit 0 of word 0 of Philox with
@@ -1259,11 +1313,6 @@ __global__ void k_init_state(const GroupDev G) {
     for (uint32_t g = j; g < pairs; g += 64) G.acc[g] = 0;
     const size_t nlog = (size_t)G.log_cap * (N > 1 ? N - 1 : 1);
     for (size_t i = j; i < nlog; i += 64) G.swaplog[i] = 0;
-}
-
-__global__ void k_zero32(uint32_t* p, size_t n) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
 }
 
 __global__ void k_philox(const uint32_t* in, uint32_t* out, uint32_t n) {
@@ -1335,10 +1384,15 @@ hipError_t launch_swap_apply(const GroupDev& g, const Advance& adv, hipStream_t 
     hipLaunchKernelGGL(k_swap_apply, dim3(swap_blocks(g.V)), dim3(kSwapBlock), 0, s, g, adv);
     return hipGetLastError();
 }
-hipError_t launch_zero32(void* p, size_t n, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       (uint32_t*)p, n);
+hipError_t launch_zero_meas(const GroupDev* groups, uint32_t n_groups, hipStream_t s) {
+    hipLaunchKernelGGL(k_zero_meas, dim3(n_groups), dim3(256), 0, s, groups);
+    return hipGetLastError();
+}
+hipError_t launch_read(const GroupDev* groups, uint32_t n_groups, Reading what,
+                       const uint64_t* offsets, void* out, hipStream_t s) {
+    constexpr uint32_t kSplit = 8;  // blocks per group
+    hipLaunchKernelGGL(k_read, dim3(n_groups, kSplit), dim3(256), 0, s, groups, what, offsets,
+                       (uint8_t*)out);
     return hipGetLastError();
 }
 hipError_t launch_philox(const uint32_t* in, uint32_t* out, uint32_t n, hipStream_t s) {
@@ -1378,14 +1432,15 @@ hipError_t launch_chunk_fused(const BatchPlan& slots, const uint32_t* ctr, uint3
     return hipGetLastError();
 }
 
-hipError_t launch_energy_batched(const BatchPlan& plan, uint32_t eplanes, hipStream_t s) {
+hipError_t launch_energy_batched(const BatchPlan& plan, uint32_t eplanes, bool reading,
+                                 hipStream_t s) {
     if (plan.n_blocks == 0) return hipSuccess;
     if (eplanes <= (uint32_t)kEnergyShort)
         hipLaunchKernelGGL(k_energy_batched<kEnergyShort>, dim3(plan.n_blocks), dim3(kEnergyBlock),
-                           0, s, plan);
+                           0, s, plan, (uint32_t)reading);
     else
         hipLaunchKernelGGL(k_energy_batched<kEnergyLong>, dim3(plan.n_blocks), dim3(kEnergyBlock),
-                           0, s, plan);
+                           0, s, plan, (uint32_t)reading);
     return hipGetLastError();
 }
 hipError_t launch_pt_batched(const GroupDev* groups, uint32_t n_groups, const uint32_t* ctr,

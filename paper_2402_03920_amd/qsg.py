@@ -313,12 +313,10 @@ class Ensemble:
         _check(lib().qsg_tau_overlaps(self.ctx, group, slots[0], len(slots), _ptr(t), n,
                                       C.c_void_p(out.data_ptr()), words), self.ctx)
         self.sync()
-        res = []
-        for a in out.cpu().numpy().reshape(len(slots), per):
-            res.append({"q2": a[:64 * n].reshape(64, n), "q4": a[64 * n:128 * n].reshape(64, n),
-                        "A": a[128 * n:128 * n + n * L].reshape(n, L),
-                        "B": a[128 * n + n * L:].reshape(n, L)})
-        return res
+        a = out.cpu().numpy().reshape(len(slots), per)
+        q = a[:, :128 * n].reshape(-1, 2, 64, n)
+        ab = a[:, 128 * n:].reshape(-1, 2, n, L)
+        return [{"q2": q2, "q4": q4, "A": A, "B": B} for (q2, q4), (A, B) in zip(q, ab)]
 
     def init_spins(self):
         _check(lib().qsg_init_spins(self.ctx), self.ctx)
