@@ -255,7 +255,8 @@ struct qsg_ctx {
     uint32_t energy_planes = 0;  // deepest walk of plan_energy
     GroupDev* d_groups = nullptr;
     qsg::BatchPlan plan_slots{};      // one block per slot (fused sweeps)
-    uint32_t fused_lds_words = 0;     // slots at most this big run from LDS
+    qsg::FusedShape fused{};
+    bool fused_graph = false;  // chunk graphs hold the fused launch
     // pinned buffer of the readings: the groups' offsets, then the reading
     // (at most kStageBytes of it); grows to what was asked for, freed with
     // the context
@@ -367,7 +368,7 @@ qsg_status batched_pt(qsg_ctx* c, hipStream_t s, uint32_t sweeps) {
 qsg_status enqueue_chunk(qsg_ctx* c, hipStream_t s, bool fused) {
     const uint32_t pe = c->cfg.pt_every;
     if (fused) {
-        QSG_HIP(c, qsg::launch_chunk_fused(c->plan_slots, c->d_counters, pe, c->fused_lds_words, s));
+        QSG_HIP(c, qsg::launch_chunk_fused(c->plan_slots, c->d_counters, pe, c->fused, s));
     } else {
         for (uint32_t i = 0; i < pe; ++i)
             if (qsg_status st = batched_sweep(c, s, i)) return st;
@@ -541,7 +542,7 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
 
     std::vector<uint32_t> pre_energy(n_groups + 1, 0),
         pre_swap(n_groups + 1, 0), pre_slots(n_groups + 1, 0);
-    uint32_t max_v = 0;
+    uint32_t max_v = 0, max_lds = 0;
     const uint64_t total_words = ensemble_words(groups, n_groups);
     for (uint32_t i = 0; i < n_groups; ++i) {
         const qsg_group_desc& d = groups[i];
@@ -590,7 +591,8 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
         pre_energy[i + 1] = pre_energy[i] + g.N * qsg::energy_blocks_per_slot(g.L * g.L, g.ewalk.tiles);
         pre_swap[i + 1] = pre_swap[i] + (g.N >= 2 ? qsg::swap_blocks(g.V) : 0);
         pre_slots[i + 1] = pre_slots[i] + g.N;
-        if (g.V > max_v) max_v = g.V;
+        max_v = std::max(max_v, g.V);
+        max_lds = std::max(max_lds, g.V + 2 * g.L * g.L);
     }
     c->plan_energy = qsg::make_plan(c->d_groups, at<uint32_t>(c, L.prefix_energy),
                                     pre_energy.data(), n_groups, c->gd.data());
@@ -598,7 +600,8 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
                                   n_groups, c->gd.data());
     c->plan_slots = qsg::make_plan(c->d_groups, at<uint32_t>(c, L.prefix_slots), pre_slots.data(),
                                    n_groups, c->gd.data());
-    c->fused_lds_words = max_v <= qsg::kFusedLdsMaxWords ? max_v : 0;
+    c->fused = qsg::fused_shape(max_v, max_lds);
+    c->fused_graph = max_v <= qsg::kFusedGraphWords;
 
     auto bail = [&](qsg_status st) {
         g_create_error = c->err;
@@ -675,7 +678,7 @@ qsg_status qsg_sweep(qsg_ctx* c, uint32_t n_sweeps, uint32_t flags) {
     while (done < n_sweeps) {
         // whole PT chunks aligned to the cadence: one fused launch for the
         // sweeps and/or a replay of the captured chunk graph
-        const bool fused = flags & QSG_FUSED;
+        const bool fused = (flags & QSG_FUSED) || ((flags & QSG_GRAPH) && c->fused_graph);
         if (batched && (flags & (QSG_GRAPH | QSG_FUSED)) && do_pt && pe > 0 && c->t % pe == 0 &&
             n_sweeps - done >= pe) {
             if (flags & QSG_GRAPH) {

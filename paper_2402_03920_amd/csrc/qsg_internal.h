@@ -226,11 +226,31 @@ enum class Reading : uint32_t { energy, overlap, walkers, accepts, swaplog, roun
 hipError_t launch_read(const GroupDev* groups, uint32_t n_groups, Reading what,
                        const uint64_t* offsets, void* out, hipStream_t s);
 // Fused sweeps over every slot (one block per slot, `slots.prefix` counts
-// slots per group): n_sweeps sweeps in one launch; slots of at most
-// lds_words words run from LDS.
+// slots per group): n_sweeps sweeps in one launch.
+constexpr uint32_t kFusedBlock = 1024;
+constexpr uint32_t kFusedLdsWords = 20000;  // 156 KiB of a CU's 160
+struct FusedShape {
+    uint32_t threads;    // per block, whole waves
+    uint32_t lds_words;  // spins and couplings of the largest slot; 0: run from global memory
+};
+// max_v: words of the largest slot; max_lds: its words and couplings, V + 2
+// L^2.  As few rounds of words as 1024 threads allow, with as few threads as
+// these rounds need.
+inline FusedShape fused_shape(uint32_t max_v, uint32_t max_lds) {
+    const uint32_t half = max_v / 2, rounds = (half + kFusedBlock - 1) / kFusedBlock;
+    const uint32_t threads = ((half + rounds - 1) / rounds + 63) / 64 * 64;
+    return {threads, max_lds <= kFusedLdsWords ? max_lds : 0};
+}
+// A chunk graph holds the fused launch instead of the colour passes if no
+// slot has more words than this.  A colour pass of a graph lasts at least 5.7
+// us, a fused one 1.1 us and 2.3 per 1024 words on the one CU that a slot is
+// on: they meet at about 3000 words a slot where slots are few, later where
+// they are many.  100 sweeps, passes / fused: 1.38 / 0.99 ms for 16 slots of
+// 2048 words, 1.96 / 1.14 for 256, 4.42 / 2.86 for 1024; 3.42 / 2.67 for 600
+// of 2160; but 1.41 / 1.74 for 16 of 4096.
+constexpr uint32_t kFusedGraphWords = 2560;
 hipError_t launch_chunk_fused(const BatchPlan& slots, const uint32_t* ctr, uint32_t n_sweeps,
-                              uint32_t lds_words, hipStream_t s);
-constexpr uint32_t kFusedLdsMaxWords = 7168;  // 56 KiB of spins per block
+                              const FusedShape& shape, hipStream_t s);
 // Column-walk depth of the colour pass (tau planes per thread; each thread
 // updates tile/2 words): the largest allowed, and the default for a launch
 // over `words` words.  Deep walks save loads and index work per word, shallow
@@ -303,8 +323,6 @@ namespace qsg {
 __host__ __device__ inline uint32_t sweep_blocks_per_slot(uint32_t V, uint32_t tile) {
     return (V / tile + kSweepBlock - 1) / kSweepBlock;
 }
-// The fused chunk kernel walks a slot's colour-c words block by block.
-__host__ __device__ inline uint32_t fused_words_per_colour(uint32_t V) { return V / 2; }
 // One thread per column (P = L^2 of them) and tau tile.
 __host__ __device__ inline uint32_t energy_blocks_per_slot(uint32_t P, uint32_t tiles) {
     return (P * tiles + kEnergyBlock - 1) / kEnergyBlock;

@@ -240,12 +240,18 @@ __device__ __forceinline__ Word class_code(uint32_t regime, uint32_t s, uint64_t
 }
 
 
-// Load the neighbourhood of colour-c word `idx` of a slot.  Colour-c words of
-// a slot are numbered plane by plane, row by row: idx = tau*(L*L/2) +
-// y*(L/2) + xh, x = 2*xh + ((c + y + tau) & 1).
+// Where colour-c word `idx` of a slot has its neighbourhood, and its
+// couplings.  Colour-c words of a slot are numbered plane by plane, row by
+// row: idx = tau*(L*L/2) + y*(L/2) + xh, x = 2*xh + ((c + y + tau) & 1).
+struct WordSite {
+    uint32_t s, xp, xm, yp, ym, above, below;  // word indices in the slot
+    uint32_t flip;                             // bit 0 / 1: above / below lies across the ends
+    uint64_t jxp, jxm, jyp, jym;
+};
 template <bool kGlobal>
-__device__ __forceinline__ Word load_word(const GroupDev& G, const uint64_t* __restrict__ S,
-                                          uint32_t regime, uint32_t colour, uint32_t idx) {
+__device__ __forceinline__ WordSite locate_word(const GroupDev& G, const uint64_t* __restrict__ Jx,
+                                                const uint64_t* __restrict__ Jy, uint32_t colour,
+                                                uint32_t idx) {
     const uint32_t L = G.L;
     const uint32_t P = L * L;
     const uint32_t tau = fast_div(idx, G.div_half_plane);
@@ -260,23 +266,40 @@ __device__ __forceinline__ Word load_word(const GroupDev& G, const uint64_t* __r
     const uint32_t tm = (tau == 0) ? G.Ltau - 1 : tau - 1;
     const uint32_t row = y * L;
     const uint32_t plane = tau * P;
-    const uint32_t site = plane + row + x;
-    const uint64_t w = load64<kGlobal>(S, site);
-    const SpaceCount n = count_space(
-        w, load64<kGlobal>(S, plane + row + xp), load64<kGlobal>(S, plane + row + xm),
-        load64<kGlobal>(S, plane + yp * L + x), load64<kGlobal>(S, plane + ym * L + x),
-        load64<true>(G.Jx, row + x), load64<true>(G.Jx, row + xm),  // -x bond: the +x bond of x-1
-        load64<true>(G.Jy, row + x), load64<true>(G.Jy, ym * L + x));
-    uint64_t above = load64<kGlobal>(S, tp * P + row + x);
-    uint64_t below = load64<kGlobal>(S, tm * P + row + x);
+    WordSite r;
+    r.s = plane + row + x;
+    r.xp = plane + row + xp;
+    r.xm = plane + row + xm;
+    r.yp = plane + yp * L + x;
+    r.ym = plane + ym * L + x;
+    r.above = tp * P + row + x;
+    r.below = tm * P + row + x;
+    r.flip = (tp == 0 ? 1u : 0u) | (tau == 0 ? 2u : 0u);
+    r.jxp = load64<kGlobal>(Jx, row + x);
+    r.jxm = load64<kGlobal>(Jx, row + xm);  // the -x bond is the +x bond of x-1
+    r.jyp = load64<kGlobal>(Jy, row + x);
+    r.jym = load64<kGlobal>(Jy, ym * L + x);
+    return r;
+}
+
+template <bool kGlobal>
+__device__ __forceinline__ Word load_word(const GroupDev& G, const uint64_t* __restrict__ S,
+                                          uint32_t regime, const WordSite& at) {
+    const uint64_t w = load64<kGlobal>(S, at.s);
+    const SpaceCount n =
+        count_space(w, load64<kGlobal>(S, at.xp), load64<kGlobal>(S, at.xm),
+                    load64<kGlobal>(S, at.yp), load64<kGlobal>(S, at.ym), at.jxp, at.jxm, at.jyp,
+                    at.jym);
+    uint64_t above = load64<kGlobal>(S, at.above);
+    uint64_t below = load64<kGlobal>(S, at.below);
     // on an antiperiodic prism the bond that wraps round tau counts with the
     // opposite sign, which is the neighbour's word inverted
     if (G.anti) {
         asm volatile("");  // a block-uniform branch: periodic groups skip this
-        if (tau + 1 == G.Ltau) above = ~above;
-        if (tau == 0) below = ~below;
+        if (at.flip & 1u) above = ~above;
+        if (at.flip & 2u) below = ~below;
     }
-    return class_code(regime, site, w, n, above, below);
+    return class_code(regime, at.s, w, n, above, below);
 }
 
 // Threshold plane T of one level: bit j = the level's threshold bit of lane
@@ -376,7 +399,6 @@ __device__ __forceinline__ Word pop_word(const SweepQueue& Q, uint32_t k) {
 // one pair per call parity (see SweepQueue); within a call, round j writes
 // counter j & 1, which round j - 1 cleared after every thread had read its
 // previous value.
-template <bool kGlobal>
 __device__ __forceinline__ void sweep_words(const GroupDev& G, uint64_t* __restrict__ S, uint32_t g,
                                             uint32_t t, const Word& r, bool valid, SweepQueue& Q,
                                             uint32_t parity) {
@@ -395,7 +417,7 @@ __device__ __forceinline__ void sweep_words(const GroupDev& G, uint64_t* __restr
         if (und != 0)
             push_word(Q, atomicAdd(&cnt[0], 1u), r, w, und);
         else
-            store64<kGlobal>(S, r.s, w);
+            store64<true>(S, r.s, w);
     }
     __syncthreads();
     uint32_t n = __builtin_amdgcn_readfirstlane(cnt[0]);
@@ -418,30 +440,17 @@ __device__ __forceinline__ void sweep_words(const GroupDev& G, uint64_t* __restr
             compare_levels(G, g, t, entries, e, q, q1, acc, und);
             const uint64_t w = bop3<kXorAndNot>(e.w, acc, und);
             if (last)
-                store64<kGlobal>(S, e.s, w ^ und);
+                store64<true>(S, e.s, w ^ und);
             else if (und != 0)
                 push_word(Q, atomicAdd(&cnt[j & 1u], 1u), e, w, und);
             else
-                store64<kGlobal>(S, e.s, w);
+                store64<true>(S, e.s, w);
         }
         if (last) break;
         __syncthreads();
         n = __builtin_amdgcn_readfirstlane(cnt[j & 1u]);
         q = q1;
     }
-}
-
-// One word per thread, numbered as in load_word (the fused chunk kernel).
-// S: the slot's spins (global memory, or a copy in LDS).  parity: alternate
-// 0/1 between consecutive calls in one block.
-template <bool kGlobal>
-__device__ __forceinline__ void sweep_block(const GroupDev& G, uint64_t* __restrict__ S, uint32_t g,
-                                            uint32_t colour, uint32_t t, uint32_t idx, bool valid,
-                                            SweepQueue& Q, uint32_t parity) {
-    const uint32_t regime = __builtin_amdgcn_readfirstlane(G.thr[g * kThrStride + 15]);
-    Word r{};
-    if (valid) r = load_word<kGlobal>(G, S, regime, colour, idx);
-    sweep_words<kGlobal>(G, S, g, t, r, valid, Q, parity);
 }
 
 // Column walk: thread `item` of a slot owns column (x, y) = item mod L^2 of
@@ -473,7 +482,8 @@ __device__ __forceinline__ T* scalar_ptr(T* p) {
 
 __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restrict__ S, uint32_t g,
                                            uint32_t colour, uint32_t t, uint32_t item,
-                                           uint32_t n_items, SweepQueue& Q, WalkCouplings& J) {
+                                           uint32_t n_items, SweepQueue& Q,
+                                           WalkCouplings& J) {
     const bool valid = item < n_items;
     const uint32_t regime = __builtin_amdgcn_readfirstlane(G.thr[g * kThrStride + 15]);
     const uint32_t L = G.L, P = L * L, Ltau = G.Ltau;
@@ -540,7 +550,7 @@ __device__ __forceinline__ void walk_block(const GroupDev& G, uint64_t* __restri
             r = class_code(regime, site0 + 2 * k * P, w, n, above, below);
             below = above;
         }
-        sweep_words<true>(G, S, g, t, r, valid, Q, k);
+        sweep_words(G, S, g, t, r, valid, Q, k);
     }
 }
 
@@ -669,38 +679,82 @@ k_half_sweep_batched(const BatchPlan plan, uint32_t colour, const uint32_t* __re
 // ---------------------------------------------------------------------------
 // Fused sweeps: one block owns one slot for `n_sweeps` sweeps (no other
 // block touches it before the PT step), so colour passes are separated by
-// block barriers only and all sweeps of a PT chunk are one launch.  Slots of
-// at most `lds_words` words are copied into LDS for the chunk.
+// block barriers only and all sweeps of a PT chunk are one launch.  One word
+// per thread and round.  The slots run from LDS (kLds: spins, then the
+// couplings, copied in, and the spins back), or from global memory where the
+// launch's largest slot does not fit.
+//
+// What bounds it: vector issue of the one CU a slot is on (3.4 us per pass of
+// 1024 words; 16 waves of 515 instructions are 3.7 us at 2.2 GHz), below a
+// few hundred words the latency of one word's comparison (2 us).  So every
+// wave takes its words to the end by itself: packing the words still
+// undecided, as the colour pass does, saves a fifth of the comparisons but
+// costs barriers and LDS traffic that one block per CU cannot hide (4.8 us),
+// and one Philox block per wave of a shared word, or two at a time, no less
+// (4.9, 4.0).  Where the block has a thread for every word of a colour the
+// neighbourhoods are found once (3.9 us if found in every pass).  With 256
+// threads, packing and the couplings in global memory a pass took 12.4 us;
+// the colour passes of a graph take 5.7 each on so few words.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kSweepBlock)
-k_chunk_fused(const BatchPlan slots, const uint32_t* __restrict__ ctr, uint32_t n_sweeps,
-              uint32_t lds_words) {
-    extern __shared__ uint64_t lds_spins[];
-    __shared__ SweepQueue Q;
+template <bool kGlobal>
+__device__ __forceinline__ void update_word(const GroupDev& G, uint64_t* __restrict__ S,
+                                            uint32_t regime, uint32_t g, uint32_t t,
+                                            const WordSite& at) {
+    const Word r = load_word<kGlobal>(G, S, regime, at);
+    uint64_t acc = ~r.und, und = r.und;  // lanes outside the seven classes: dE <= 0, accepted
+    compare_levels(G, g, t, G.thr + g * kThrStride + kLevelEntries, r, 0, 16, acc, und);
+    // a lane equal on all 32 bits has r == thr, accepted
+    store64<kGlobal>(S, r.s, bop3<kXorAndNot>(r.w, acc, und) ^ und);
+}
+
+template <bool kLds>
+__global__ void __launch_bounds__(kFusedBlock, 8)
+k_chunk_fused(const BatchPlan slots, const uint32_t* __restrict__ ctr, uint32_t n_sweeps) {
+    extern __shared__ uint64_t lds_words[];
     const BlockPlace at = locate<false>(slots, blockIdx.x);
     const GroupDev G = group_record<false>(slots, at.gi);
     const uint32_t g = __builtin_amdgcn_readfirstlane(at.local);
-    const uint32_t V = G.V, half = V >> 1;
+    const uint32_t V = G.V, half = V >> 1, P = G.L * G.L;
     uint64_t* Sg = G.spins + (size_t)g * V;
-    const bool in_lds = V <= lds_words;
-    uint64_t* S = in_lds ? lds_spins : Sg;
-    if (in_lds) {
-        for (uint32_t i = threadIdx.x; i < V; i += kSweepBlock) lds_spins[i] = Sg[i];
+    const uint32_t regime = __builtin_amdgcn_readfirstlane(G.thr[g * kThrStride + 15]);
+    if (kLds) {
+        for (uint32_t i = threadIdx.x; i < V; i += blockDim.x) lds_words[i] = Sg[i];
+        for (uint32_t i = threadIdx.x; i < P; i += blockDim.x) {
+            lds_words[V + i] = G.Jx[i];
+            lds_words[V + P + i] = G.Jy[i];
+        }
         __syncthreads();
     }
     const uint32_t t0 = __builtin_amdgcn_readfirstlane(ctr[0]);
-    uint32_t call = 0;
-    for (uint32_t it = 0; it < n_sweeps; ++it) {
-        for (uint32_t colour = 0; colour < 2; ++colour) {
-            for (uint32_t base = 0; base < half; base += kSweepBlock) {
-                const uint32_t idx = base + threadIdx.x;
-                sweep_block<false>(G, S, g, colour, t0 + it, idx, idx < half, Q, call++);
-            }
+    uint64_t* S = kLds ? lds_words : Sg;
+    const uint64_t* Jx = kLds ? lds_words + V : G.Jx;
+    const uint64_t* Jy = kLds ? lds_words + V + P : G.Jy;
+    if (kLds && half <= blockDim.x) {  // a thread's two words are the same in every sweep
+        const uint32_t idx = threadIdx.x;
+        WordSite red{}, blue{};
+        if (idx < half) {
+            red = locate_word<!kLds>(G, Jx, Jy, 0, idx);
+            blue = locate_word<!kLds>(G, Jx, Jy, 1, idx);
+        }
+#pragma unroll 1
+        for (uint32_t it = 0; it < n_sweeps; ++it) {
+            if (idx < half) update_word<!kLds>(G, S, regime, g, t0 + it, red);
             __syncthreads();  // the next colour reads what this one wrote
+            if (idx < half) update_word<!kLds>(G, S, regime, g, t0 + it, blue);
+            __syncthreads();
+        }
+    } else {
+#pragma unroll 1
+        for (uint32_t pass = 0; pass < 2 * n_sweeps; ++pass) {
+#pragma unroll 1
+            for (uint32_t idx = threadIdx.x; idx < half; idx += blockDim.x)
+                update_word<!kLds>(G, S, regime, g, t0 + (pass >> 1),
+                                   locate_word<!kLds>(G, Jx, Jy, pass & 1u, idx));
+            __syncthreads();
         }
     }
-    if (in_lds)
-        for (uint32_t i = threadIdx.x; i < V; i += kSweepBlock) Sg[i] = lds_spins[i];
+    if (kLds)
+        for (uint32_t i = threadIdx.x; i < V; i += blockDim.x) Sg[i] = lds_words[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -1419,16 +1473,22 @@ hipError_t launch_half_sweep_batched(const BatchPlan& plan, uint32_t colour, con
     return hipGetLastError();
 }
 hipError_t launch_chunk_fused(const BatchPlan& slots, const uint32_t* ctr, uint32_t n_sweeps,
-                              uint32_t lds_words, hipStream_t s) {
+                              const FusedShape& f, hipStream_t s) {
     if (slots.n_blocks == 0) return hipSuccess;
-    const size_t lds = (size_t)lds_words * sizeof(uint64_t);
-    if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_chunk_fused,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
+    const size_t lds = (size_t)f.lds_words * sizeof(uint64_t);
+    if (lds) {
+        if (lds > 48 * 1024) {
+            hipError_t e = hipFuncSetAttribute((const void*)k_chunk_fused<true>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(k_chunk_fused<true>, dim3(slots.n_blocks), dim3(f.threads), lds, s,
+                           slots, ctr, n_sweeps);
+    } else {
+        hipLaunchKernelGGL(k_chunk_fused<false>, dim3(slots.n_blocks), dim3(f.threads), 0, s, slots,
+                           ctr, n_sweeps);
     }
-    hipLaunchKernelGGL(k_chunk_fused, dim3(slots.n_blocks), dim3(kSweepBlock), lds, s, slots, ctr,
-                       n_sweeps, lds_words);
     return hipGetLastError();
 }
 
