@@ -110,7 +110,8 @@ typedef struct {
     uint32_t sweep_split; /* schedule of the colour pass: Philox blocks every
                              word goes through before the words still undecided
                              are packed into fewer waves (1..16; 16 = never;
-                             0 = default 4).  Results do not depend on it.     */
+                             0 = default 4; the fused chunk never packs).
+                             Results do not depend on it.                      */
     uint32_t tau_tile;    /* schedule of the colour pass: tau planes a thread
                              walks along one column (it updates tau_tile/2 words;
                              0 = default: 2, 4 or 8 by the number of words a
@@ -124,14 +125,16 @@ typedef struct {
 /* qsg_sweep flags */
 #define QSG_PLAIN 0u    /* one launch per group and pass (per-sample launches) */
 #define QSG_BATCHED 1u  /* one launch per pass over every group                */
-#define QSG_GRAPH 2u    /* with QSG_BATCHED: replay a captured HIP graph       */
+#define QSG_GRAPH 2u    /* with QSG_BATCHED: replay a captured HIP graph (with
+                           the fused chunk where no slot has more than 2560
+                           words)                                              */
 #define QSG_NO_PT 4u    /* skip the PT steps that fall due                     */
 #define QSG_FUSED 8u    /* with QSG_BATCHED: the sweeps of a whole PT chunk in
                            one launch, one block per slot (small slots from LDS);
                            pays off only when every slot is small (one block
                            then replaces a launch per colour pass); a slot of
-                           many blocks' worth of words runs serially in its one
-                           block, far slower than the per-pass form          */
+                           many thousand words runs serially in its one block,
+                           slower than the per-pass form                     */
 
 /* qsg_measure selectors (one at a time) */
 #define QSG_M_ENERGY 1u    /* int32 [G][N][64][2]: (Bsp, Bt) recomputed now      */
@@ -434,7 +437,7 @@ size_t qsg_tm_lanczos_workspace_bytes(uint32_t L, uint32_t max_iter);
  * once), entries beyond the number found are NaN.  d_vec (device, may be
  * NULL): the unit Ritz vector of eigs[0].  d_ws: qsg_tm_lanczos_workspace_
  * bytes(L, max_iter) bytes, device, caller owned.  Synchronises hip_stream
- * (every step reads two scalars back).  1 <= n_eig <= max_iter <= 4096. */
+ * (every step reads three scalars back).  1 <= n_eig <= max_iter <= 4096. */
 qsg_status qsg_tm_lanczos(const qsg_tm_desc* d, uint32_t max_iter, uint32_t n_eig, double tol,
                           uint64_t seed, void* d_ws, size_t ws_bytes, double* eigs,
                           double* resid, uint32_t* iters, double* d_vec, void* hip_stream);
@@ -447,11 +450,10 @@ qsg_status qsg_tm_lanczos(const qsg_tm_desc* d, uint32_t max_iter, uint32_t n_ei
  * Mt_xy = M_xy [cos(2 pi (x1-y1)/L) + cos(2 pi (x2-y2)/L)] / 2:
  *   out[0] = Q2 = Tr M^2,  out[1] = Q4 = sum_{x,y,z,u} R_xyzu^2,
  *   out[2] = F = Tr M Mt   (host, 3 doubles).
- * Computed from the Walsh-Hadamard transform of v^2 on the device (the
- * product's passes with the factor (a, b) -> (a + b, a - b)) and a
- * fixed-order reduction over the pairs and quadruples of sites.  d_ws:
- * qsg_tm_correlations_workspace_bytes(L) bytes of device memory, caller
- * owned.  Synchronises hip_stream. */
+ * Computed from the Walsh-Hadamard transform of v^2 on the device (only the
+ * entries of the pairs and quadruples of sites that are needed, summed in a
+ * fixed order).  d_ws: qsg_tm_correlations_workspace_bytes(L) bytes of device
+ * memory, caller owned.  Synchronises hip_stream. */
 size_t qsg_tm_correlations_workspace_bytes(uint32_t L);
 qsg_status qsg_tm_correlations(uint32_t L, const double* d_vec, void* d_ws, size_t ws_bytes,
                                double* out, void* hip_stream);

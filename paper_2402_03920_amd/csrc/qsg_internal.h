@@ -84,7 +84,7 @@ struct GroupDev {
     uint64_t* Jx;             // [L*L]
     uint64_t* Jy;             // [L*L]
     const uint64_t* jseed;    // [64] coupling keys
-    uint32_t* thr;            // [N][kThrStride] thresholds, regime, level picks
+    uint32_t* thr;            // [N][kThrStride] thresholds, regime, handler entries
     uint32_t* sw_thr;         // [N-1][sw_cap]
     uint32_t* sw_len;         // [N-1]
     uint32_t* sw_eq;          // [N-1]
@@ -108,7 +108,8 @@ hipError_t launch_init_spins(const GroupDev& g, hipStream_t s);
 hipError_t launch_init_state(const GroupDev& g, hipStream_t s);
 // The colour pass follows the group's schedule G.q_split: Philox blocks every
 // word goes through before the words still undecided are packed into the
-// first waves of the block (16: no packing).  Results do not depend on it.
+// first waves of the block (16: no packing; the fused chunk never packs).
+// Results do not depend on it.
 hipError_t launch_half_sweep(const GroupDev& g, uint32_t colour, const uint32_t* ctr,
                              uint32_t t_add, hipStream_t s);
 hipError_t launch_energy(const GroupDev& g, int32_t* cnt, hipStream_t s);

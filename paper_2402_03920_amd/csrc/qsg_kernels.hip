@@ -7,13 +7,13 @@
 // uint64 (bit j = lane j), so a thread updates 64 spins with bitwise logic:
 //   * unsatisfied bonds: u = s ^ neighbour ^ J (bit set <=> J S S' < 0);
 //   * per-lane counts n_s (4 space bonds) and n_t (2 time bonds) as
-//     bit-sliced adders, turned into 15 one-hot class masks;
+//     bit-sliced adders, turned into a three-bit class code;
 //   * acceptance r_j <= thr[class_j]: lane numbers are bit-sliced over 32
 //     levels (bit 31-b of r_j is bit j of level b), so all 64 comparisons run
 //     together, most significant level first, and stop as soon as every lane
 //     of the wave is decided.  One Philox block yields two levels.
-// Nothing here is a dense contraction, so there is no matrix-core work: the
-// pass is integer VALU work on data streamed from HBM.
+// The sweeps hold no contraction, so there is no matrix-core work here: they
+// are integer VALU work on data streamed from HBM (or held in LDS).
 #include <hip/hip_runtime.h>
 
 #include "qsg_internal.h"
@@ -169,8 +169,7 @@ struct WalkCouplings {
 // Spin and coupling words are addressed as base + 32-bit byte offset, so
 // global accesses keep the base in SGPRs and only the offset in a VGPR.  The
 // host rejects slots of more than 2^29 words, so a word index i < 2^29 gives
-// a byte offset i * 8 < 2^32.  The fused kernel may hold a slot in LDS and
-// addresses it generically.
+// a byte offset i * 8 < 2^32.  The fused kernel may hold a slot in LDS.
 typedef char __attribute__((address_space(1))) GlobalByte;
 template <bool kGlobal>
 __device__ __forceinline__ uint64_t load64(const uint64_t* base, uint32_t i) {
@@ -1208,9 +1207,8 @@ __global__ void k_advance(const Advance a) {
 // site, the pairs' masked bit exchanges in ascending order (each word read
 // and written once).  The slots' words are loaded a batch ahead of the
 // stores, which the compiler may not reorder: on small samples the pass lasts
-// as long as one site's chain (4.2 us for 16 slots,
-// 5.7 with one load per link), on large ones as long as the copy of
-// the spins (171 us on 537 MB).  The pass reads neither counter, and it is
+// as long as one site's chain (4.2 us for 16 slots, 5.7 with one load per
+// link), on large ones as long as the copy of the spins (171 us on 537 MB).  The pass reads neither counter, and it is
 // the last of a PT step: its first thread advances them, which saves the
 // launch of its own that this took (4 us).
 // ---------------------------------------------------------------------------
