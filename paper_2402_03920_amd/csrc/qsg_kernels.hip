@@ -1205,30 +1205,36 @@ __global__ void k_advance(const Advance a) {
 // ---------------------------------------------------------------------------
 // Apply the accepted exchanges of the latest PT step to the spins: at every
 // site, the pairs' masked bit exchanges in ascending order (each word read
-// and written once).  The slots' words are loaded a batch ahead of the
-// stores, which the compiler may not reorder: on small samples the pass lasts
-// as long as one site's chain (4.2 us for 16 slots, 5.7 with one load per
-// link), on large ones as long as the copy of the spins (171 us on 537 MB).  The pass reads neither counter, and it is
+// and written once).  On few sites the pass lasts as long as one site's
+// chain: the slots' words are then loaded a batch ahead of the stores
+// (kAhead), which the compiler may not reorder (4.3 us for 16 slots of 2048
+// words, 7.0 with one load per link; 11.9 and 13.1 for 570 blocks).  Once the
+// blocks fill the chip more than once it lasts as long as the copy of the
+// spins, and one load per link is as fast or faster (172 us either way on 537
+// MB, 321 against 337 on 906 MB).  The pass reads neither counter, and it is
 // the last of a PT step: its first thread advances them, which saves the
 // launch of its own that this took (4 us).
 // ---------------------------------------------------------------------------
 constexpr uint32_t kSwapBatch = 8;
+constexpr uint32_t kSwapAheadBlocks = 2048;  // eight blocks on each of 256 CUs
+template <bool kAhead>
 __device__ __forceinline__ void swap_site(const GroupDev& G, uint32_t site) {
+    constexpr uint32_t kBatch = kAhead ? kSwapBatch : 1;
     const uint32_t pairs = G.N - 1;
     uint64_t* S = G.spins + site;
     const size_t V = G.V;
     uint64_t cur = S[0];  // running content of slot g
     uint64_t orig = cur;  // what slot g held before this step
-    for (uint32_t g0 = 0; g0 < pairs; g0 += kSwapBatch) {
-        uint64_t next[kSwapBatch], mask[kSwapBatch];
+    for (uint32_t g0 = 0; g0 < pairs; g0 += kBatch) {
+        uint64_t next[kBatch], mask[kBatch];
 #pragma unroll
-        for (uint32_t k = 0; k < kSwapBatch; ++k) {
+        for (uint32_t k = 0; k < kBatch; ++k) {
             const uint32_t g = min(g0 + k, pairs - 1);  // block-uniform
             next[k] = S[(size_t)(g + 1) * V];
             mask[k] = G.lastmask[g];
         }
 #pragma unroll
-        for (uint32_t k = 0; k < kSwapBatch; ++k) {
+        for (uint32_t k = 0; k < kBatch; ++k) {
             if (g0 + k >= pairs) break;
             const uint64_t d = (cur ^ next[k]) & mask[k];
             cur ^= d;
@@ -1240,13 +1246,15 @@ __device__ __forceinline__ void swap_site(const GroupDev& G, uint32_t site) {
     if (cur != orig) S[(size_t)pairs * V] = cur;
 }
 
+template <bool kAhead>
 __global__ void __launch_bounds__(kSwapBlock) k_swap_apply(const GroupDev G, const Advance adv) {
     if (adv.ctr && (blockIdx.x | threadIdx.x) == 0) advance_counters(adv);
     if (G.N < 2 || G.lastmask[G.N - 1] == 0) return;
     const uint32_t site = blockIdx.x * kSwapBlock + threadIdx.x;
-    if (site < G.V) swap_site(G, site);
+    if (site < G.V) swap_site<kAhead>(G, site);
 }
 
+template <bool kAhead>
 __global__ void __launch_bounds__(kSwapBlock)
 k_swap_apply_batched(const BatchPlan plan, const Advance adv) {
     if ((blockIdx.x | threadIdx.x) == 0) advance_counters(adv);
@@ -1254,7 +1262,7 @@ k_swap_apply_batched(const BatchPlan plan, const Advance adv) {
     const GroupDev G = group_record<false>(plan, at.gi);
     if (G.N < 2 || G.lastmask[G.N - 1] == 0) return;
     const uint32_t site = at.local * kSwapBlock + threadIdx.x;
-    if (site < G.V) swap_site(G, site);
+    if (site < G.V) swap_site<kAhead>(G, site);
 }
 
 // ---------------------------------------------------------------------------
@@ -1433,7 +1441,11 @@ hipError_t launch_pt(const GroupDev& g, const uint32_t* ctr, hipStream_t s) {
     return hipGetLastError();
 }
 hipError_t launch_swap_apply(const GroupDev& g, const Advance& adv, hipStream_t s) {
-    hipLaunchKernelGGL(k_swap_apply, dim3(swap_blocks(g.V)), dim3(kSwapBlock), 0, s, g, adv);
+    const uint32_t blocks = swap_blocks(g.V);
+    if (blocks <= kSwapAheadBlocks)
+        hipLaunchKernelGGL(k_swap_apply<true>, dim3(blocks), dim3(kSwapBlock), 0, s, g, adv);
+    else
+        hipLaunchKernelGGL(k_swap_apply<false>, dim3(blocks), dim3(kSwapBlock), 0, s, g, adv);
     return hipGetLastError();
 }
 hipError_t launch_zero_meas(const GroupDev* groups, uint32_t n_groups, hipStream_t s) {
@@ -1513,8 +1525,12 @@ hipError_t launch_advance(const Advance& adv, hipStream_t s) {
 }
 hipError_t launch_swap_apply_batched(const BatchPlan& plan, const Advance& adv, hipStream_t s) {
     if (plan.n_blocks == 0) return launch_advance(adv, s);  // groups of one slot only
-    hipLaunchKernelGGL(k_swap_apply_batched, dim3(plan.n_blocks), dim3(kSwapBlock), 0, s, plan,
-                       adv);
+    if (plan.n_blocks <= kSwapAheadBlocks)
+        hipLaunchKernelGGL(k_swap_apply_batched<true>, dim3(plan.n_blocks), dim3(kSwapBlock), 0, s,
+                           plan, adv);
+    else
+        hipLaunchKernelGGL(k_swap_apply_batched<false>, dim3(plan.n_blocks), dim3(kSwapBlock), 0, s,
+                           plan, adv);
     return hipGetLastError();
 }
 
