@@ -454,7 +454,9 @@ __global__ void k_to_bf16(const float* __restrict__ p, uint16_t* __restrict__ ph
 
 // Ladder from the 31 increment logits: log G_i = log Gmin + (log Gmax -
 // log Gmin) * cumulative softmax, non-decreasing, ends pinned exactly;
-// predicted acceptance 1 - exp(z31)/31.  Thread l forms point l + 1.
+// predicted acceptance 1 - exp(z31)/31.  Thread l forms point l + 1.  (Ends
+// given the wrong way round, Gmin > Gmax, keep Gmin up to the last inner
+// point, which like the end is Gmax.)
 __global__ void __launch_bounds__(32 * kRowSamples)
 k_decode(const float* __restrict__ z, const double* __restrict__ gmin,
          const double* __restrict__ gmax, int B, double* __restrict__ ladder,
@@ -478,12 +480,13 @@ k_decode(const float* __restrict__ z, const double* __restrict__ gmin,
     const double lo = log(first), hi = log(last);
     double v = exp(lo + (hi - lo) * c);  // (comparisons that leave a NaN in place)
     if (v < first) v = first;
-    if (v > last) v = last;
+    if (last >= first && v > last) v = last;
 #pragma unroll
     for (int off = 1; off < 32; off <<= 1) {  // running maximum over the points
         const double below = __shfl_up(v, off, 32);
         if (l >= off && below > v) v = below;
     }
+    if (l == kMlpInc - 2 && v > last) v = last;
     if (b >= B) return;
     double* out = ladder + (size_t)b * kMlpLadder;
     if (head) {
