@@ -338,7 +338,8 @@ k_backward_weight(const float* __restrict__ X, const float* __restrict__ dout, i
                     s = fmaf(v.z, w3[n + 2], s);
                     s = fmaf(v.w, w3[n + 3], s);
                 }
-                gv[i] = s * gelu_grad(gv[i]);
+                // nothing where the batch has ended (0 times an infinite weight is not 0)
+                gv[i] = b0 + row + kDwTile * i < B ? s * gelu_grad(gv[i]) : 0.0f;
                 asm volatile("" : "+v"(gv[i]) : : "memory");  // one row's reads at a time
             }
         }

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
-from paper_2402_03920_amd import qsg  # noqa: E402
+from paper_2402_03920_amd import ladder, qsg  # noqa: E402
 
 
 def _decode(z, lo, hi):
@@ -45,3 +45,40 @@ def test_decode_of_ends_in_either_order():
     back = lo > hi
     assert np.array_equal(got[back, 1:30], np.repeat(lo[back, None], 29, axis=1))
     assert np.array_equal(got[:, 31], hi)
+
+
+def _kind(a):
+    """0 finite, 1 NaN, 2 inf, 3 -inf."""
+    return np.where(np.isnan(a), 1, np.where(np.isposinf(a), 2, np.where(np.isneginf(a), 3, 0)))
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("B", [3, 128, 131])
+def test_an_infinite_weight_reaches_the_gradients_it_meets(B, bf16):
+    """The weight gradients are formed 128 samples at a time; the places of a
+    round without a sample add nothing, whatever the weights hold."""
+    print(f"[mlp] B={B} bf16={bf16}", flush=True)
+    rng = np.random.default_rng(B)
+    X = rng.normal(size=(B, 6)).astype(np.float32)
+    p = ladder.init_params(4).astype(np.float32)
+    out_w = len(p) - 32 - 128 * 32
+    p[out_w + 7 * 32 + 3] = np.inf
+    p[out_w - 128 + 7] = 12.0  # its unit is on for every sample: one sign of infinity
+    dout = rng.uniform(0.5, 1.5, size=(B, 32)).astype(np.float32)
+    net = ladder.LadderMLP(bf16=bf16, params=p.astype(np.float64))
+    x = torch.tensor(X, device="cuda")
+    _, ws = net.forward(x)
+    grads = torch.empty(net.n_params, device="cuda")
+    qsg.qsg_mlp_backward(net.params, net.bf16, x, ws, torch.tensor(dout, device="cuda"), grads,
+                         torch.empty(2 * B * 128, device="cuda"))
+    p = p.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        cache = omlp.forward(p, X.astype(np.float64), bf16=bf16)
+        # the activations of the pass itself: far below zero an FP32 one is 0,
+        # and 0 times infinity no infinity
+        for l, act in enumerate(ws.cpu().numpy()[:6 * B * 128].reshape(3, 2, B, 128)[:, 1]):
+            cache["inputs"][l + 1] = omlp.to_bf16(act) if bf16 else act.astype(np.float64)
+        want = omlp.backward(p, cache, dout.astype(np.float64), bf16=bf16)
+    got = _kind(grads.cpu().numpy())
+    assert np.array_equal(got, _kind(want)), np.nonzero(got != _kind(want))[0][:8]
+    assert np.any(_kind(want) == 2)
