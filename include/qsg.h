@@ -37,8 +37,11 @@
  *  - Memory: the caller owns every device buffer.  qsg_create carves its
  *    state out of one caller-allocated device workspace of
  *    qsg_workspace_bytes() bytes, which must stay alive until qsg_destroy.
- *    The library allocates no device memory (hipGraph objects aside).
- *    Host buffers passed in are read before the call returns.
+ *    The library allocates no device memory (hipGraph objects aside).  A
+ *    context's first qsg_measure takes up to 1 MiB of pinned host memory (and
+ *    8 bytes per group) for its readings, which qsg_destroy gives back; where
+ *    there is none, readings do without.  Host buffers passed in are read
+ *    before the call returns.
  *  - Streams: work is enqueued on the caller's HIP stream.  qsg_measure,
  *    qsg_get_* and qsg_sync synchronise that stream.
  *  - Errors: functions return QSG_OK or a negative qsg_status and never

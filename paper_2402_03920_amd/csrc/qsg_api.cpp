@@ -8,6 +8,7 @@
 // exchange pass, counter advance).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cstdarg>
 #include <cmath>
@@ -257,11 +258,10 @@ struct qsg_ctx {
     qsg::BatchPlan plan_slots{};      // one block per slot (fused sweeps)
     qsg::FusedShape fused{};
     bool fused_graph = false;  // chunk graphs hold the fused launch
-    // pinned buffer of the readings: the groups' offsets, then the reading
-    // (at most kStageBytes of it); grows to what was asked for, freed with
-    // the context
+    // pinned buffer of the readings: the groups' offsets, then a run of groups'
+    // readings; freed with the context
     uint8_t* stage = nullptr;
-    size_t stage_bytes = 0;
+    size_t stage_bytes = 0;  // without the offsets
     hipGraphExec_t chunk_exec[2] = {nullptr, nullptr};  // [fused]
     hipGraph_t chunk_graph[2] = {nullptr, nullptr};
     bool failed = false;
@@ -761,17 +761,72 @@ qsg::Reading reading_kind(uint32_t what) {
     }
 }
 
-constexpr size_t kStageBytes = 16u << 20;
+// The pinned buffer holds the largest kind of reading, up to 1 MiB: pinning
+// memory takes 0.55 ms per MiB (16 MiB for a swap log's first reading took 8.3
+// ms where the copy takes 2.0), and further runs of groups cost a launch and a
+// wait each, 15 us.  A group of more than 512 KiB is copied as fast by itself.
+constexpr size_t kStageBytes = 1u << 20;
+constexpr size_t kCopyBytes = 512u << 10;
 
-qsg_status grow_stage(qsg_ctx* c, size_t bytes) {
-    if (bytes <= c->stage_bytes) return QSG_OK;
-    if (c->stage) QSG_HIP(c, hipHostFree(c->stage));
-    c->stage = nullptr;
-    c->stage_bytes = 0;
+size_t stage_head(const qsg_ctx* c) { return align_up(c->desc.size() * 8); }
+
+// Allocates the pinned buffer on the first reading.  Without it (no pinned
+// memory to be had) groups are copied one by one.
+void need_stage(qsg_ctx* c) {
+    if (c->stage) return;
+    size_t largest = 0;
+    for (uint32_t what = QSG_M_ENERGY; what <= QSG_M_HIST; ++what) {
+        size_t total = 0;
+        for (const auto& d : c->desc) {
+            const size_t b = reading_bytes(c, d, what);
+            if (b <= kCopyBytes) total += b;
+        }
+        largest = std::max(largest, std::min(total, kStageBytes));
+    }
     void* p = nullptr;
-    QSG_HIP(c, hipHostMalloc(&p, bytes, hipHostMallocDefault));
+    if (hipHostMalloc(&p, stage_head(c) + largest, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();  // not an error of the launches that follow
+        return;
+    }
     c->stage = static_cast<uint8_t*>(p);
-    c->stage_bytes = bytes;
+    c->stage_bytes = largest;
+}
+
+// One group's reading copied by itself (the stream has been waited for).
+qsg_status copy_reading(qsg_ctx* c, const GroupDev& g, uint32_t what, uint8_t* o, size_t bytes) {
+    const size_t slots = g.N;
+    const int64_t V = g.V;
+    const void* raw = what == QSG_M_ACCEPT      ? (const void*)g.acc
+                      : what == QSG_M_SWAPLOG   ? (const void*)g.swaplog
+                      : what == QSG_M_ROUNDTRIP ? (const void*)g.rt
+                      : what == QSG_M_SUMS      ? (const void*)g.sums
+                      : what == QSG_M_HIST      ? (const void*)g.hist
+                                                : nullptr;
+    if (raw) {
+        QSG_HIP(c, hipMemcpy(o, raw, bytes, hipMemcpyDeviceToHost));
+        return QSG_OK;
+    }
+    if (what == QSG_M_WALKERS) {
+        std::vector<uint32_t> w(slots * 64);
+        QSG_HIP(c, hipMemcpy(w.data(), g.walker, w.size() * 4, hipMemcpyDeviceToHost));
+        for (size_t i = 0; i < w.size(); ++i) o[i] = (uint8_t)w[i];
+        return QSG_OK;
+    }
+    std::vector<int32_t> cnt(slots * qsg::kCntStride);
+    QSG_HIP(c, hipMemcpy(cnt.data(), g.meas, cnt.size() * 4, hipMemcpyDeviceToHost));
+    for (size_t k = 0; k < slots; ++k) {
+        const int32_t* n = &cnt[k * qsg::kCntStride];
+        if (what == QSG_M_ENERGY) {
+            int32_t* e = reinterpret_cast<int32_t*>(o) + k * 128;
+            for (int j = 0; j < 64; ++j) {
+                e[2 * j] = (int32_t)(2 * V - 2 * n[j]);
+                e[2 * j + 1] = (int32_t)(V - 2 * n[64 + j]);
+            }
+        } else {
+            int64_t* q = reinterpret_cast<int64_t*>(o) + k * 32;
+            for (int i = 0; i < 32; ++i) q[i] = V - 2 * (int64_t)n[128 + i];
+        }
+    }
     return QSG_OK;
 }
 
@@ -803,38 +858,32 @@ qsg_status qsg_measure(qsg_ctx* c, uint32_t what, void* host_out, size_t bytes) 
         QSG_HIP(c, qsg::launch_zero_meas(c->d_groups, n, s));
         QSG_HIP(c, qsg::launch_energy_batched(c->plan_energy, c->energy_planes, true, s));
     }
-    // Runs of groups whose readings fit the staging buffer: one launch and
-    // one wait each.  A group that does not fit alone (a swap log of more
-    // than 16 MiB) is copied by itself.
+    // Runs of groups whose readings fit the pinned buffer: one launch and one
+    // wait each.  The others are copied by themselves.
+    need_stage(c);
     uint8_t* o = static_cast<uint8_t*>(host_out);
-    const size_t head = align_up((size_t)n * 8);
     for (uint32_t i0 = 0; i0 < n;) {
+        uint64_t* off = reinterpret_cast<uint64_t*>(c->stage);
         size_t used = 0;
         uint32_t i1 = i0;
-        for (; i1 < n; ++i1) {
+        for (; c->stage && i1 < n; ++i1) {
             const size_t b = reading_bytes(c, c->desc[i1], what);
-            if (used + b > kStageBytes) break;
+            if (b > kCopyBytes || used + b > c->stage_bytes) break;
+            off[i1 - i0] = used;
             used += b;
         }
         if (i1 == i0) {
             const size_t b = reading_bytes(c, c->desc[i0], what);
             QSG_HIP(c, hipStreamSynchronize(s));
-            QSG_HIP(c, hipMemcpy(o, c->gd[i0].swaplog, b, hipMemcpyDeviceToHost));
+            if (qsg_status st = copy_reading(c, c->gd[i0], what, o, b)) return st;
             o += b;
             ++i0;
             continue;
         }
-        if (qsg_status st = grow_stage(c, head + used)) return st;
-        uint64_t* off = reinterpret_cast<uint64_t*>(c->stage);
-        uint64_t at = 0;
-        for (uint32_t i = i0; i < i1; ++i) {
-            off[i - i0] = at;
-            at += reading_bytes(c, c->desc[i], what);
-        }
-        QSG_HIP(c, qsg::launch_read(c->d_groups + i0, i1 - i0, reading_kind(what), off,
-                                    c->stage + head, s));
+        uint8_t* data = c->stage + stage_head(c);
+        QSG_HIP(c, qsg::launch_read(c->d_groups + i0, i1 - i0, reading_kind(what), off, data, s));
         QSG_HIP(c, hipStreamSynchronize(s));
-        std::memcpy(o, c->stage + head, used);
+        std::memcpy(o, data, used);
         o += used;
         i0 = i1;
     }
