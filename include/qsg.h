@@ -440,7 +440,9 @@ size_t qsg_tm_lanczos_workspace_bytes(uint32_t L, uint32_t max_iter);
  * once), entries beyond the number found are NaN.  d_vec (device, may be
  * NULL): the unit Ritz vector of eigs[0].  d_ws: qsg_tm_lanczos_workspace_
  * bytes(L, max_iter) bytes, device, caller owned.  Synchronises hip_stream
- * (every step reads three scalars back).  1 <= n_eig <= max_iter <= 4096. */
+ * (every step reads three scalars back; for them a thread keeps a page of
+ * pinned memory and an event per device until it ends, or does without).
+ * 1 <= n_eig <= max_iter <= 4096. */
 qsg_status qsg_tm_lanczos(const qsg_tm_desc* d, uint32_t max_iter, uint32_t n_eig, double tol,
                           uint64_t seed, void* d_ws, size_t ws_bytes, double* eigs,
                           double* resid, uint32_t* iters, double* d_vec, void* hip_stream);

@@ -157,6 +157,47 @@ std::vector<double> tri_vector(const std::vector<double>& a, const std::vector<d
     return z;
 }
 
+// Pinned memory for the scalars of a solve's step, with the event that says
+// they are there: the next step's product then runs while the host looks at
+// them (a copy to ordinary memory in its place takes 25 us a step, a third of
+// a solve at L = 4).  Memory is not given back after each solve, which would
+// wait for every stream of the device: a thread keeps one cell per device it
+// solved on until it ends.  Null where there is no pinned memory to be had.
+struct StepCell {
+    int device = -1;
+    double* p = nullptr;
+    hipEvent_t ready = nullptr;
+};
+struct StepCells {
+    std::vector<StepCell> cells;
+    ~StepCells() {
+        for (const StepCell& c : cells) {
+            (void)hipEventDestroy(c.ready);
+            (void)hipHostFree(c.p);
+        }
+    }
+};
+
+const StepCell* step_cell() {
+    static thread_local StepCells mine;
+    StepCell c;
+    if (hipGetDevice(&c.device) != hipSuccess) return nullptr;
+    for (const StepCell& have : mine.cells)
+        if (have.device == c.device) return &have;
+    if (hipHostMalloc(reinterpret_cast<void**>(&c.p), 3 * sizeof(double), hipHostMallocDefault) !=
+        hipSuccess) {
+        (void)hipGetLastError();  // not an error of the launches that follow
+        return nullptr;
+    }
+    if (hipEventCreateWithFlags(&c.ready, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipHostFree(c.p);
+        return nullptr;
+    }
+    mine.cells.push_back(c);
+    return &mine.cells.back();
+}
+
 // Q2, Q4 and F (App. E) from the sums of squared correlations of pairs,
 // weighted pairs and quadruples of sites: ordered pairs and quadruples reduce
 // to the set met an odd number of times (empty, a pair, a quadruple), so
@@ -224,18 +265,12 @@ qsg_status qsg_tm_lanczos(const qsg_tm_desc* d, uint32_t max_iter, uint32_t n_ei
     double* h2 = h + (max_iter + 1);
     double* nrm = h2 + (max_iter + 1);                          // [2]
     double* y = nrm + 2;                                        // [max_iter]
-
-    // a step's scalars, written by the device
-    struct Pinned {
-        double* p = nullptr;
-        hipEvent_t ready = nullptr;
-        ~Pinned() {
-            if (ready) (void)hipEventDestroy(ready);
-            if (p) (void)hipHostFree(p);
-        }
-    } host;
-    TM_HIP(hipHostMalloc(reinterpret_cast<void**>(&host.p), 3 * sizeof(double), hipHostMallocDefault));
-    TM_HIP(hipEventCreateWithFlags(&host.ready, hipEventDisableTiming));
+    const StepCell* cell = step_cell();
+    // a solve that ends early leaves nothing under way that writes the cell
+    struct Wait {
+        hipStream_t s;
+        ~Wait() { (void)hipStreamSynchronize(s); }
+    } wait{s};
 
     TM_HIP(qsg::launch_tm_random(w, N, seed, s));
     TM_HIP(qsg::launch_tm_dots(w, 1, N, w, partial, nrm, s));
@@ -251,8 +286,15 @@ qsg_status qsg_tm_lanczos(const qsg_tm_desc* d, uint32_t max_iter, uint32_t n_ei
         TM_HIP(qsg::launch_tm_dots(V, j + 1, N, w, partial, h, s));
         TM_HIP(qsg::launch_tm_update_dots(V, j + 1, N, h, w, partial, h2, s));
         TM_HIP(qsg::launch_tm_update_norm(V, j + 1, N, h2, w, partial, nrm, s));
-        TM_HIP(qsg::launch_tm_gather(h + j, h2 + j, nrm, host.p, s));
-        TM_HIP(hipEventRecord(host.ready, s));
+        // the step's scalars, written by the device to pinned memory, or copied
+        TM_HIP(qsg::launch_tm_gather(h + j, h2 + j, nrm, cell ? cell->p : partial, s));
+        double step[3];
+        if (cell) {
+            TM_HIP(hipEventRecord(cell->ready, s));
+        } else {
+            TM_HIP(hipMemcpyAsync(step, partial, sizeof step, hipMemcpyDeviceToHost, s));
+            TM_HIP(hipStreamSynchronize(s));
+        }
         // the next vector and its product are under way while the host looks
         // at this step (not used if it is the last)
         if (j + 1 < max_iter) {
@@ -260,8 +302,11 @@ qsg_status qsg_tm_lanczos(const qsg_tm_desc* d, uint32_t max_iter, uint32_t n_ei
             TM_HIP(qsg::launch_tm_scale(w, N, nrm, next, s));
             TM_HIP(qsg::launch_tm_apply(P, next, w, s));
         }
-        TM_HIP(hipEventSynchronize(host.ready));
-        const double hj[2] = {host.p[0], host.p[1]}, nr = host.p[2];
+        if (cell) {
+            TM_HIP(hipEventSynchronize(cell->ready));
+            std::memcpy(step, cell->p, sizeof step);
+        }
+        const double hj[2] = {step[0], step[1]}, nr = step[2];
         alpha.push_back(hj[0] + hj[1]);
         const double bj = std::sqrt(nr);
         m = j + 1;

@@ -12,7 +12,7 @@
 #include "../paper_2402_03920_amd/csrc/qsg_internal.h"
 
 namespace host {
-int pinned_allocs = 0, pinned_frees = 0, event_calls = 0, stream_waits = 0;
+int pinned_allocs = 0, pinned_frees = 0, events = 0;
 bool fail_pinned = false;
 hipError_t last_error = hipSuccess;  // as the runtime: kept until it is asked for
 inline hipError_t launched() { return hipGetLastError(); }
@@ -45,11 +45,25 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) {
-    ++host::stream_waits;
     return hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
     *s = nullptr;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) {
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+    ++host::events;
+    *e = nullptr;
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) {
+    --host::events;
     return hipSuccess;
 }
 }

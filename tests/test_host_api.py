@@ -13,7 +13,7 @@ def run(tmp_path, program, sources):
     # launchers that a program does not define are not called by it
     subprocess.run(["g++", "-std=c++17", "-O1", "-no-pie", "-D__HIP_PLATFORM_AMD__", "-isystem",
                     "/opt/rocm/include", os.path.join(ROOT, "tests", program),
-                    *(os.path.join(CSRC, s) for s in sources), "-o", exe, "-lquadmath",
+                    *(os.path.join(CSRC, s) for s in sources), "-o", exe, "-lquadmath", "-pthread",
                     "-Wl,--unresolved-symbols=ignore-all"], check=True)
     return subprocess.run([exe], capture_output=True, text=True, timeout=60)
 
@@ -23,3 +23,10 @@ def test_readings_without_pinned_memory(tmp_path):
     by one, with the same result."""
     r = run(tmp_path, "host_readings.cpp", ["qsg_api.cpp", "qsg_tables.cpp"])
     assert r.returncode == 0, r.stdout
+
+
+def test_eigensolves_keep_their_pinned_memory(tmp_path):
+    """To give pinned memory back waits for all streams of the device, so it
+    is not done from solve to solve; a solve can do without."""
+    r = run(tmp_path, "host_lanczos.cpp", ["qsg_transfer_api.cpp"])
+    assert r.returncode == 0, (r.returncode, r.stdout)
