@@ -1488,9 +1488,11 @@ hipError_t launch_chunk_fused(const BatchPlan& slots, const uint32_t* ctr, uint3
     const size_t lds = (size_t)f.lds_words * sizeof(uint64_t);
     if (lds) {
         if (lds > 48 * 1024) {
+            // always the most that any context needs: the limit belongs to the
+            // kernel, and another thread's context may be about to launch
             hipError_t e = hipFuncSetAttribute((const void*)k_chunk_fused<true>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)lds);
+                                               (int)(kFusedLdsWords * sizeof(uint64_t)));
             if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL(k_chunk_fused<true>, dim3(slots.n_blocks), dim3(f.threads), lds, s,
