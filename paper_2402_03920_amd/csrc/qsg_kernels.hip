@@ -312,9 +312,14 @@ __device__ __forceinline__ Word load_word(const GroupDev& G, const uint64_t* __r
 // of masks: 3089 vector instructions a wave of eight words and 5.6 waves a
 // SIMD, now 2432 and 7.5, 783 -> 621 us a pass on 2 x 48 slots of 24 x 24 x
 // 2048.  (Handlers that also hold the comparison, 64 bytes each, took 3 %
-// longer: more instruction fetches.)  `entry`: byte offset of the handler from the instruction after
-// s_getpc (the host stores it per slot and level, see level_entry); masked
-// so that no value can leave the handlers.
+// longer: more instruction fetches.)  `entry`: byte offset of the handler from
+// the instruction after s_getpc, as the host stores it per slot and level
+// (level_entry); nothing else may be stored there.  The mask keeps the jump
+// within the handlers and the three instructions before them, where offsets 0,
+// 4 and 8 would jump for ever: a table that was never set is not run (the
+// host refuses sweeps before every ladder is set).  (An offset that lands on
+// a handler whatever the entry costs two more scalar instructions a Philox
+// block, 1 to 2 % on small launches.)
 __device__ __forceinline__ uint64_t threshold_plane(uint32_t entry, const Word& r) {
     static_assert(kHandlerBytes == 32 && kHandlerSkip == 12, "handlers below are laid out so");
     uint32_t T_lo, T_hi;

@@ -30,3 +30,10 @@ def test_eigensolves_keep_their_pinned_memory(tmp_path):
     is not done from solve to solve; a solve can do without."""
     r = run(tmp_path, "host_lanczos.cpp", ["qsg_transfer_api.cpp"])
     assert r.returncode == 0, (r.returncode, r.stdout)
+
+
+def test_level_entries_are_handlers(tmp_path):
+    """The colour pass jumps to the offsets of a slot's level entries: the
+    host builds none but starts of handlers, and runs no slot without."""
+    r = run(tmp_path, "host_ladders.cpp", ["qsg_api.cpp", "qsg_tables.cpp"])
+    assert r.returncode == 0, (r.returncode, r.stdout)
