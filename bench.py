@@ -8,8 +8,9 @@ chunk over every sample: 10 sweeps (red + blue pass each), the
 energy/overlap pass, the PT step and the exchange pass.
 
 Prints one JSON line.  value = picoseconds per spin-update of the batched
-path (one launch per pass over all samples, replayed as a HIP graph, the
-faster of the per-pass and fused forms; colour-pass schedules tuned first:
+path (one launch per pass over all samples, replayed as a HIP graph, or the
+fused form if it is faster or, on small slots, the only one; colour-pass
+schedules tuned first:
 one walk depth for the ensemble, a split per shape class);
 plain_ps_per_spin_update is the same work launched per sample, at the walk
 depth best for per-sample launches.  The other
@@ -240,11 +241,11 @@ def main():
         torch.cuda.synchronize()
         return a.elapsed_time(b) / 1e3
 
-    # the two batched forms of a PT chunk, both replayed as a HIP graph: one
-    # launch per colour pass over every group, or one fused launch for all the
-    # sweeps of the chunk (a block per slot); the faster one is the value
+    # the batched forms of a PT chunk, replayed as a HIP graph: one launch per
+    # colour pass over every group, or one fused launch for all the sweeps of
+    # the chunk (a block per slot; the only form where every slot is small);
+    # the faster one is the value
     form, flags, probe = autotune.pick_form(ens)
-    forms = autotune.FORMS
     print(f"[bench] warmup {args.warmup} steps", file=sys.stderr, flush=True)
     ens.sweep(pe * args.warmup, flags)
     torch.cuda.synchronize()
@@ -253,26 +254,32 @@ def main():
     sec = timed(lambda: ens.sweep(pe * args.steps, flags))
     wall = time.perf_counter() - t0
     ps_batched = sec / (pe * args.steps * upd_per_sweep) * 1e12
-    other = [n for n in forms if n != form][0]
-    sec_other = timed(lambda: ens.sweep(pe * args.plain_steps, forms[other]))
-    ps_other = sec_other / (pe * args.plain_steps * upd_per_sweep) * 1e12
+    others = {}
+    for name, fl in autotune.forms(ens).items():
+        if name != form:
+            sec_o = timed(lambda: ens.sweep(pe * args.plain_steps, fl))
+            others[f"{name}_ps_per_spin_update"] = round(
+                sec_o / (pe * args.plain_steps * upd_per_sweep) * 1e12, 5)
+
+    # dominant kernel: the batched colour pass; average launch duration from
+    # events around sweeps without PT (two pass launches + one tiny counter
+    # update per sweep), on the stream the kernels run on.  The fused form has
+    # no launch per pass: a chunk's time over its passes, the PT step included.
+    n_k = 2 * pe
+    if form == "fused":
+        pass_s = sec / (2 * pe * args.steps)
+    else:
+        sec_k = timed(lambda: ens.sweep(n_k, qsg.QSG_BATCHED | qsg.QSG_NO_PT))
+        pass_s = sec_k / (2 * n_k)
 
     # per-sample launches: their own walk depth (they fill the chip one group
-    # at a time), then back to the batched schedules
+    # at a time)
     plain_tile, _ = autotune.pick_plain_tile(ens, schedules)
     print(f"[bench] timing {args.plain_steps} plain steps (walk depth {plain_tile})",
           file=sys.stderr, flush=True)
     sec_plain = timed(lambda: ens.sweep(pe * args.plain_steps, qsg.QSG_PLAIN))
     ps_plain = sec_plain / (pe * args.plain_steps * upd_per_sweep) * 1e12
-    for i, g in enumerate(ens.groups):
-        ens.set_schedule(i, *schedules.get(autotune.shape_key(g), autotune.DEFAULT))
 
-    # dominant kernel: the batched colour pass; average launch duration from
-    # events around sweeps without PT (two pass launches + one tiny counter
-    # update per sweep), on the stream the kernels run on
-    n_k = 2 * pe
-    sec_k = timed(lambda: ens.sweep(n_k, qsg.QSG_BATCHED | qsg.QSG_NO_PT))
-    pass_s = sec_k / (2 * n_k)
     words_per_pass = words_per_sweep / 2
     blocks = required_blocks_per_word()
     ops_per_pass = words_per_pass * blocks * INSTR_PER_PHILOX_BLOCK
@@ -281,7 +288,7 @@ def main():
     physics = summarize(wl, ens)
     ens.close()
     ceiling = philox_ceiling()
-    traffic = measured_traffic(args.workload)
+    traffic = measured_traffic(args.workload) if form == "per-pass" else None
 
     result = {
         "metric": "ps/spin-update (1 GPU) batched vs plain",
@@ -304,7 +311,7 @@ def main():
             "form_ms_per_chunk": {k: round(v * 1e3, 4) for k, v in probe.items()},
             "schedules": schedules,
         },
-        f"{other}_ps_per_spin_update": round(ps_other, 5),
+        **others,
         "plain_ps_per_spin_update": round(ps_plain, 5),
         "plain_tau_tile": plain_tile,
         "batched_speedup_vs_plain": round(ps_plain / ps_batched, 4),
@@ -312,7 +319,8 @@ def main():
         "wall_s_timed_region": round(wall, 4),
         "roofline": {
             "bound": "alu",
-            "kernel": "k_half_sweep_batched",
+            "kernel": "k_half_sweep_batched" if form == "per-pass" else
+                      "k_chunk_fused and the PT step's kernels (per colour pass of the chunk)",
             "achieved": round(achieved, 4),
             "peak": round(PEAK_VALU_TOPS, 4),
             "unit": "T VALU lane-instructions/s",

@@ -129,8 +129,8 @@ typedef struct {
 #define QSG_PLAIN 0u    /* one launch per group and pass (per-sample launches) */
 #define QSG_BATCHED 1u  /* one launch per pass over every group                */
 #define QSG_GRAPH 2u    /* with QSG_BATCHED: replay a captured HIP graph (with
-                           the fused chunk where no slot has more than 2560
-                           words)                                              */
+                           the fused chunk, as QSG_FUSED, where no slot has
+                           more than QSG_FUSED_GRAPH_WORDS words)              */
 #define QSG_NO_PT 4u    /* skip the PT steps that fall due                     */
 #define QSG_FUSED 8u    /* with QSG_BATCHED: the sweeps of a whole PT chunk in
                            one launch, one block per slot (small slots from LDS);
@@ -138,6 +138,8 @@ typedef struct {
                            then replaces a launch per colour pass); a slot of
                            many thousand words runs serially in its one block,
                            slower than the per-pass form                     */
+
+#define QSG_FUSED_GRAPH_WORDS 2560u
 
 /* qsg_measure selectors (one at a time) */
 #define QSG_M_ENERGY 1u    /* int32 [G][N][64][2]: (Bsp, Bt) recomputed now      */

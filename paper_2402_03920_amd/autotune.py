@@ -33,6 +33,9 @@ run.
 
 `pick_form` makes the other, ensemble-wide choice: whether a PT chunk runs
 as one launch per colour pass or as one fused launch for all its sweeps.
+Where every slot is small there is no choice: a graph then holds the fused
+launch either way, and the colour-pass schedules serve only per-sample
+launches and the sweeps outside whole chunks.
 `pick_plain_tile` chooses the depth of per-sample launches, which fill the
 chip one group at a time.
 """
@@ -212,16 +215,24 @@ FORMS = {"per-pass": qsg.QSG_BATCHED | qsg.QSG_GRAPH,
          "fused": qsg.QSG_BATCHED | qsg.QSG_GRAPH | qsg.QSG_FUSED}
 
 
+def forms(ens) -> Dict[str, int]:
+    """The forms a PT chunk of this ensemble can take: the fused one alone if
+    every slot has at most QSG_FUSED_GRAPH_WORDS words."""
+    if all(g.L * g.L * g.L_tau <= qsg.QSG_FUSED_GRAPH_WORDS for g in ens.groups):
+        return {"fused": FORMS["fused"]}
+    return dict(FORMS)
+
+
 def pick_form(ens, chunks: int = 2, repeats: int = 3):
-    """The faster batched form of a PT chunk for this ensemble, both replayed
-    as HIP graphs: one launch per colour pass over every group, or one fused
-    launch per chunk (a block per slot).  Returns (name, flags, seconds per
-    chunk of each form).  Both forms give the same trajectory; timing them
-    advances the ensemble."""
+    """The faster batched form of a PT chunk for this ensemble, of those it
+    can take (forms), replayed as HIP graphs: one launch per colour pass over
+    every group, or one fused launch per chunk (a block per slot).  Returns
+    (name, flags, seconds per chunk of each form).  All forms give the same
+    trajectory; timing them advances the ensemble."""
     timed = _timer(ens.stream)
     pe = ens.cfg.pt_every
     times = {}
-    for name, fl in FORMS.items():
+    for name, fl in forms(ens).items():
         ens.sweep(pe, fl)  # capture + warm
         times[name] = _median([timed(lambda: ens.sweep(pe * chunks, fl)) / chunks
                                for _ in range(repeats)])

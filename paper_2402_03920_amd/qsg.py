@@ -31,6 +31,7 @@ QSG_BATCHED = 1
 QSG_GRAPH = 2
 QSG_NO_PT = 4
 QSG_FUSED = 8
+QSG_FUSED_GRAPH_WORDS = 2560
 
 QSG_M_ENERGY = 1
 QSG_M_OVERLAP = 2
