@@ -284,11 +284,11 @@ constexpr int kEnergyBlock = 256;
 // transposes that cost as much as 16 planes, so the deepest that leaves the
 // chip enough waves.  Tiles need not divide Ltau (their sizes differ by one
 // plane): where they had to, 3 M words at Ltau = 90 (walks of 2 planes) took
-// 75 us instead of 15.  Measured at depths 4 / 8 / 16 / 32 / 64 (us): 6.3 /
-// 6.6 / 7.1 / 12 / 12 on 33 k words, 8.0 / 7.3 / 8.8 / 13 / 16 on 324 k,
-// 14 / 9.8 / 9.0 / 13 / 18 on 1 M, 27 / 14 / 11 / 14 / 20 on 2 M, 48 / 28 /
-// 23 / 21 / 25 on 5 M, 510 / 278 / 200 / 183 / 182 on 67 M and 360 / 291 /
-// 257 (depths 16 / 32 / 64) on 113 M.
+// 75 us instead of 15.  Measured after exchange passes, at depths 4 / 8 / 16 /
+// 32 / 64 (us): 6.3 / 6.6 / 7.1 / 12 / 12 on 33 k words, 8.0 / 7.3 / 8.8 / 13 /
+// 16 on 324 k, 14 / 9.8 / 9.0 / 13 / 18 on 1 M, 27 / 14 / 11 / 14 / 20 on 2 M,
+// 48 / 28 / 23 / 21 / 25 on 5 M, 510 / 278 / 200 / 183 / 182 on 67 M and 360 /
+// 291 / 257 (depths 16 / 32 / 64) on 113 M.
 inline EnergyWalks energy_walks(uint32_t Ltau, uint64_t words) {
     const uint32_t depth = words >= (1ull << 26)   ? kEnergyLong
                            : words >= (1ull << 22) ? 32

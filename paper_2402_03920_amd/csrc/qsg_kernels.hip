@@ -884,9 +884,10 @@ __device__ __forceinline__ uint32_t lane_total(const LaneCounter<NH>& c) {
 // short tile's step planes-1 lies in the tile above it (the last tile is
 // never short), so it is read like any other and masked out.
 //
-// What bounds it: on a full chip the reads of the spins (182 us on 67 M
-// words, 3.0 TB/s; 257 us on 113 M, 3.5 TB/s: a third fewer instructions in
-// the adds changed neither); on few words the transposes at the end of every
+// What bounds it: on a full chip the reads of the spins (67 M words take 160
+// us after the colour passes of a chunk and 182 after an exchange pass, 3.4
+// and 2.9 TB/s; 113 M after an exchange pass 257 us, 3.5 TB/s: a third fewer
+// instructions in the adds changed neither); on few words the transposes at the end of every
 // wave (16 to 22 of them, as many instructions as 16 planes) against too few
 // waves: energy_walks picks the depth.
 constexpr int kEnergyBatch = 4;

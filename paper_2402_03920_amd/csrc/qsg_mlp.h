@@ -17,7 +17,8 @@ constexpr int kMlpParams = kMlpIn * kMlpHidden + kMlpHidden + 2 * (kMlpHidden * 
                            kMlpHidden * kMlpOut + kMlpOut;  // 38048
 
 // Forward workspace (floats): per hidden layer l = 0..2 the pre-activation
-// and the activation, each [B][128], then the output pre-activation [B][32].
+// and the activation, each [B][128].  (The size it is asked for in has room
+// for the outputs [B][32] behind them, which the pass does not use.)
 __host__ __device__ inline size_t mlp_ws_pre(int l, int B) {
     return (size_t)(2 * l) * B * kMlpHidden;
 }

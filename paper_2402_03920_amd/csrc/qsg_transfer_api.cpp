@@ -211,7 +211,9 @@ void correlations_of(uint32_t L, double pairs, double weighted, double quadruple
     out[2] = V + weighted;
 }
 
-// Sets of two or four sites: the workspace sizes allow for a table of them.
+// Sets of two or four sites.  The workspaces are asked for in the sizes that
+// whole transforms and a table of these sets need: programs keep buffers by
+// them.  The pruned transform uses a fifth of it at L = 5.
 size_t corr_entries(uint32_t L) {
     const size_t V = (size_t)L * L;
     return V * (V - 1) / 2 + V * (V - 1) * (V - 2) * (V - 3) / 24;
@@ -416,7 +418,12 @@ qsg_status qsg_tm_correlations_lt(uint32_t L, const double* d_even, const double
     double h[qsg::kCorrSums];
     TM_HIP(hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, s));
     TM_HIP(hipStreamSynchronize(s));
-    // R = a R_e + b R_o: R^2 from the sums of R_e^2, R_e R_o and R_o^2
+    // R = a R_e + b R_o: R^2 from the sums of R_e^2, R_e R_o and R_o^2.  The
+    // terms may cancel, but not to less than a fraction of themselves: over
+    // all ordered pairs (for Q4 pairs of pairs) R_e, R_o and R are positive
+    // semidefinite and R - a R_e = b R_o, so a^2 Tr R_e^2 <= Tr R^2, and with
+    // R_o likewise.  (Errors against 80 bits are those of squares taken length
+    // by length, 1 to 4 times 2^-53, also for states whose mixture is uniform.)
     for (uint32_t i = 0; i < n; ++i) {
         const double b = w_odd[i], a = 1.0 - b;
         double m[3];
