@@ -254,12 +254,6 @@ def main():
     sec = timed(lambda: ens.sweep(pe * args.steps, flags))
     wall = time.perf_counter() - t0
     ps_batched = sec / (pe * args.steps * upd_per_sweep) * 1e12
-    others = {}
-    for name, fl in autotune.forms(ens).items():
-        if name != form:
-            sec_o = timed(lambda: ens.sweep(pe * args.plain_steps, fl))
-            others[f"{name}_ps_per_spin_update"] = round(
-                sec_o / (pe * args.plain_steps * upd_per_sweep) * 1e12, 5)
 
     # dominant kernel: the batched colour pass; average launch duration from
     # events around sweeps without PT (two pass launches + one tiny counter
@@ -271,6 +265,13 @@ def main():
     else:
         sec_k = timed(lambda: ens.sweep(n_k, qsg.QSG_BATCHED | qsg.QSG_NO_PT))
         pass_s = sec_k / (2 * n_k)
+
+    others = {}
+    for name, fl in autotune.forms(ens).items():
+        if name != form:
+            sec_o = timed(lambda: ens.sweep(pe * args.plain_steps, fl))
+            others[f"{name}_ps_per_spin_update"] = round(
+                sec_o / (pe * args.plain_steps * upd_per_sweep) * 1e12, 5)
 
     # per-sample launches: their own walk depth (they fill the chip one group
     # at a time)
