@@ -179,7 +179,8 @@ qsg_status make_layout(const qsg_group_desc* d, uint32_t n, const qsg_run_config
         const uint32_t V = d[i].L * d[i].L * d[i].L_tau;
         energy_blocks += (uint64_t)d[i].n_gamma *
                          qsg::energy_blocks_per_slot(d[i].L * d[i].L,
-                                                     qsg::energy_walks(d[i].L_tau, total_words).tiles);
+                                                     qsg::energy_walks(d[i].L * d[i].L, d[i].L_tau,
+                                                                       total_words).tiles);
         swap_blocks += qsg::swap_blocks(V);
     }
     if (total_blocks >= (1ull << 31) || energy_blocks >= (1ull << 31) ||
@@ -561,7 +562,7 @@ qsg_status qsg_create(const qsg_group_desc* groups, uint32_t n_groups, const qsg
         g.div_plane = qsg::make_divisor(d.L * d.L);
         g.div_row = qsg::make_divisor(d.L);
         set_tile(g, cfg->tau_tile ? cfg->tau_tile : qsg::default_tile(total_words));
-        g.ewalk = qsg::energy_walks(d.L_tau, total_words);
+        g.ewalk = qsg::energy_walks(d.L * d.L, d.L_tau, total_words);
         c->energy_planes = std::max(c->energy_planes, g.ewalk.planes);
         g.sw_cap = swap_cap_of(d);
         g.log_cap = cfg->swaplog_cap;

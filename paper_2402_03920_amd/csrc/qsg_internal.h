@@ -280,26 +280,45 @@ inline uint32_t tile_for(uint32_t Ltau, uint32_t cap) {
 constexpr int kEnergyShort = 16;
 constexpr int kEnergyLong = 64;
 constexpr int kEnergyBlock = 256;
-// Depth of the walks of a launch over `words` words: every wave ends with
-// transposes that cost as much as 16 planes, so the deepest that leaves the
-// chip enough waves.  Tiles need not divide Ltau (their sizes differ by one
-// plane): where they had to, 3 M words at Ltau = 90 (walks of 2 planes) took
-// 75 us instead of 15.  Measured after exchange passes, at depths 4 / 8 / 16 /
-// 32 / 64 (us): 6.3 / 6.6 / 7.1 / 12 / 12 on 33 k words, 8.0 / 7.3 / 8.8 / 13 /
-// 16 on 324 k, 14 / 9.8 / 9.0 / 13 / 18 on 1 M, 27 / 14 / 11 / 14 / 20 on 2 M,
-// 48 / 28 / 23 / 21 / 25 on 5 M, 510 / 278 / 200 / 183 / 182 on 67 M and 360 /
-// 291 / 257 (depths 16 / 32 / 64) on 113 M.
-inline EnergyWalks energy_walks(uint32_t Ltau, uint64_t words) {
-    const uint32_t depth = words >= (1ull << 26)   ? kEnergyLong
-                           : words >= (1ull << 22) ? 32
-                           : words >= 750000       ? 16
-                           : words >= (1ull << 18) ? 8
-                                                   : 4;
+inline EnergyWalks walks_of_depth(uint32_t Ltau, uint32_t depth) {
     EnergyWalks w;
     w.tiles = (Ltau + depth - 1) / depth;
     w.planes = (Ltau + w.tiles - 1) / w.tiles;
     w.n_short = w.tiles * w.planes - Ltau;
     return w;
+}
+// The loads of the next batch of four planes run ahead only on walks of whole
+// pairs of batches.
+__host__ __device__ inline bool walks_ahead(const EnergyWalks& w) {
+    return w.planes % 8 == 0 && w.n_short == 0;
+}
+// Depth of the walks of a launch over `words` words in slots of P columns:
+// every wave ends with transposes that cost as much as 16 planes, so the
+// deepest that leaves the chip enough waves.  Tiles need not divide Ltau
+// (their sizes differ by one plane): where they had to, 3 M words at Ltau = 90
+// (walks of 2 planes) took 75 us instead of 15.  Measured after exchange
+// passes, at depths 4 / 8 / 16 / 32 / 64 (us): 6.3 / 6.7 / 7.4 / 11 / 12 on 33 k
+// words, 8.0 / 7.3 / 8.8 / 13 / 16 on 324 k, 14 / 9.2 / 8.6 / 11 / 16 on 1 M, 21 /
+// 13 / 10 / 11 / 16 on 2 M, 46 / 28 / 22 / 20 / 24 on 5 M, 510 / 278 / 200 / 183 /
+// 182 on 67 M and 360 / 291 / 257 (depths 16 / 32 / 64) on 113 M.  Two things
+// ask for deeper walks:
+// - All waves of a slot add to the same 160 counters, one after the other: 94 /
+//   50 / 29 / 21 / 19 us on one slot of 1.2 M words, whose waves number 4608 at
+//   depth 4 and 288 at 64; 81 / 44 / 22 / 18 / 17 on six slots of 0.5 M.
+// - From 6.5 M words on, 64 planes read ahead beat 32: 22.8 / 21.8 us (depths 32
+//   / 64) on 6.6 M, 31 / 28 on 13 M, 61 / 50 on 25 M; not so where the walks
+//   are ragged (30 / 38 on 7.8 M at Ltau = 94).
+inline EnergyWalks energy_walks(uint32_t P, uint32_t Ltau, uint64_t words) {
+    uint32_t depth = words >= (1ull << 26)   ? kEnergyLong
+                     : words >= (1ull << 22) ? 32
+                     : words >= 750000       ? 16
+                     : words >= (1ull << 18) ? 8
+                                             : 4;
+    const uint32_t slot_waves = words >= (1ull << 21) ? 128 : 256;
+    while (depth < (uint32_t)kEnergyLong && P * walks_of_depth(Ltau, depth).tiles > 64 * slot_waves)
+        depth *= 2;
+    if (words >= 6500000 && walks_ahead(walks_of_depth(Ltau, kEnergyLong))) depth = kEnergyLong;
+    return walks_of_depth(Ltau, depth);
 }
 hipError_t launch_pt_batched(const GroupDev* groups, uint32_t n_groups, const uint32_t* ctr,
                              hipStream_t s);

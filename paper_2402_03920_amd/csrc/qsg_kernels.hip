@@ -887,9 +887,10 @@ __device__ __forceinline__ uint32_t lane_total(const LaneCounter<NH>& c) {
 // What bounds it: on a full chip the reads of the spins (67 M words take 160
 // us after the colour passes of a chunk and 182 after an exchange pass, 3.4
 // and 2.9 TB/s; 113 M after an exchange pass 257 us, 3.5 TB/s: a third fewer
-// instructions in the adds changed neither); on few words the transposes at the end of every
-// wave (16 to 22 of them, as many instructions as 16 planes) against too few
-// waves: energy_walks picks the depth.
+// instructions in the adds changed neither); on few words the transposes at
+// the end of every wave (16 to 22 of them, as many instructions as 16 planes)
+// against too few waves, and where few slots are large the waves' atomics on
+// one set of counters: energy_walks picks the depth.
 constexpr int kEnergyBatch = 4;
 
 struct EnergyBatch {
@@ -971,7 +972,8 @@ __device__ __forceinline__ void energy_walk(const GroupDev& G, uint32_t g, uint3
         };
         EnergyBatch b0, b1;
         uint64_t ct0, cq0, ct1, cq1;
-        if (planes % (2 * kEnergyBatch) == 0 && W.n_short == 0) {
+        static_assert(2 * kEnergyBatch == 8, "walks_ahead");
+        if (walks_ahead(W)) {
             // two batch buffers used in turn (no copies between them); the
             // last fetch re-reads the top plane and is not counted
             fetch(0, b0);
@@ -1434,7 +1436,7 @@ hipError_t launch_half_sweep(const GroupDev& g, uint32_t colour, const uint32_t*
     return hipGetLastError();
 }
 hipError_t launch_energy(const GroupDev& g, int32_t* cnt, hipStream_t s) {
-    const EnergyWalks w = energy_walks(g.Ltau, (uint64_t)g.N * g.V);
+    const EnergyWalks w = energy_walks(g.L * g.L, g.Ltau, (uint64_t)g.N * g.V);
     const dim3 grid(energy_blocks_per_slot(g.L * g.L, w.tiles), g.N), block(kEnergyBlock);
     if (w.planes <= (uint32_t)kEnergyShort)
         hipLaunchKernelGGL(k_energy<kEnergyShort>, grid, block, 0, s, g, cnt, w);

@@ -37,3 +37,9 @@ def test_level_entries_are_handlers(tmp_path):
     host builds none but starts of handlers, and runs no slot without."""
     r = run(tmp_path, "host_ladders.cpp", ["qsg_api.cpp", "qsg_tables.cpp"])
     assert r.returncode == 0, (r.returncode, r.stdout)
+
+
+def test_energy_walk_depths(tmp_path):
+    """Few large slots get deep walks: their waves add to the same counters."""
+    r = run(tmp_path, "host_energy_walks.cpp", [])
+    assert r.returncode == 0, (r.returncode, r.stdout)
