@@ -1,5 +1,6 @@
-"""The ladder network's kernels on unusual values: results equal those of the
-formulas taken one sample (or one logit) after the other."""
+"""The ladder network's kernels on unusual values and on batches where loss and
+decode give a sample one thread: results equal those of the formulas taken one
+sample (or one logit) after the other."""
 import numpy as np
 import pytest
 
@@ -82,3 +83,41 @@ def test_an_infinite_weight_reaches_the_gradients_it_meets(B, bf16):
     got = _kind(grads.cpu().numpy())
     assert np.array_equal(got, _kind(want)), np.nonzero(got != _kind(want))[0][:8]
     assert np.any(_kind(want) == 2)
+
+
+def _large_batch(B):
+    rng = np.random.default_rng(B)
+    z = rng.normal(scale=2.0, size=(B, 32)).astype(np.float32)
+    t = rng.random((B, 31)) + 0.02
+    t[::5, 3:9] = 0.0
+    t = (t / t.sum(axis=1, keepdims=True)).astype(np.float32)
+    z[1, 4], z[2, 0], t[3, 2], z[4, :31] = np.nan, np.inf, np.nan, -np.inf
+    lo = rng.uniform(0.5, 2.0, B)
+    hi = lo * np.where(np.arange(B) % 7 == 0, 0.5, rng.uniform(1.0, 3.0, B))
+    lo[5], hi[6] = np.nan, np.nan
+    return z, t, rng.normal(size=B).astype(np.float32), lo, hi
+
+
+def _loss(z, t, log_l):
+    dz, loss = torch.empty((len(z), 32), device="cuda"), torch.empty(len(z), device="cuda")
+    qsg.qsg_mlp_loss(*(torch.tensor(a, device="cuda") for a in (z, t, log_l)), dz, loss)
+    return loss.cpu().numpy(), dz.cpu().numpy()
+
+
+@pytest.mark.parametrize("B", [8193, 16384 + 63])
+def test_loss_and_decode_of_large_batches_are_those_of_their_parts(B):
+    """8192 samples are the most that take 32 threads each.  Losses and
+    ladders of a batch are those of its halves bit for bit; the gradients too,
+    up to the rounding of 1/B and of its product (2^-24 each)."""
+    print(f"[mlp] B={B}", flush=True)
+    z, t, log_l, lo, hi = _large_batch(B)
+    loss, dz = _loss(z, t, log_l)
+    lad = _decode(z, lo, hi)
+    cuts = [(i, min(i + 4096, B)) for i in range(0, B, 4096)]
+    parts = [_loss(z[i:j], t[i:j], log_l[i:j]) for i, j in cuts]
+    assert np.array_equal(loss, np.concatenate([p[0] for p in parts]), equal_nan=True)
+    scaled = np.concatenate([p[1].astype(np.float64) * (j - i) / B for p, (i, j) in zip(parts, cuts)])
+    assert np.array_equal(np.isnan(dz), np.isnan(scaled))
+    assert np.nanmax(np.abs(dz - scaled) / np.maximum(np.abs(scaled), 1e-30)) < 4 * 2.0 ** -24
+    assert np.array_equal(lad, np.concatenate([_decode(z[i:j], lo[i:j], hi[i:j]) for i, j in cuts]),
+                          equal_nan=True)
