@@ -36,7 +36,6 @@ namespace qsg {
 namespace {
 
 constexpr int kOvWaves = 4;   // waves per block
-constexpr int kOvGroups = 2;  // groups of kPlanes slices per wave
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -175,7 +174,8 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int L>
+// kGroups: groups of kPlanes slices per wave.
+template <int L, int kGroups>
 __global__ void __launch_bounds__(64 * kOvWaves)
 k_tau_overlaps(const uint64_t* __restrict__ spins, uint32_t Ltau, TauList taus,
                int64_t* __restrict__ out) {
@@ -183,7 +183,7 @@ k_tau_overlaps(const uint64_t* __restrict__ spins, uint32_t Ltau, TauList taus,
     constexpr int X = L <= 16 ? 16 : 32;   // lanes per slice
     constexpr int kPlanes = 64 / X;        // slices per wave
     constexpr int NP = planes_for(L);
-    constexpr uint32_t kPerBlock = kOvWaves * kOvGroups * kPlanes;
+    constexpr uint32_t kPerBlock = kOvWaves * kGroups * kPlanes;
     // q of the wave's slices (rows padded: a lane then reads its row without
     // bank conflicts); at the end the accumulators
     constexpr int kQ = kPlanes * L * (L + 1), kU = (2 * X * X + 1) / 2;
@@ -206,7 +206,7 @@ k_tau_overlaps(const uint64_t* __restrict__ spins, uint32_t Ltau, TauList taus,
     int64_t s2 = 0, s4 = 0;
     int32_t ones = 0, slices = 0;  // sites with q = -1 of this replica; slices counted
 #pragma unroll 1
-    for (uint32_t k = 0; k < kOvGroups; ++k) {
+    for (uint32_t k = 0; k < kGroups; ++k) {
         const uint32_t first = blockIdx.x * kPerBlock + (k * kOvWaves + w) * kPlanes;
         if (first >= Ltau) break;
         const uint32_t tau1 = first + plane;
@@ -298,14 +298,30 @@ k_tau_overlaps(const uint64_t* __restrict__ spins, uint32_t Ltau, TauList taus,
     }
 }
 
+template <int L, int kGroups>
+hipError_t launch_groups(const uint64_t* slot_spins, uint32_t n_slots, uint32_t Ltau,
+                         const TauList& taus, int64_t* out, hipStream_t s) {
+    constexpr uint32_t kPerBlock = kOvWaves * kGroups * (L <= 16 ? 4 : 2);
+    const dim3 grid((Ltau + kPerBlock - 1) / kPerBlock, taus.n, n_slots);
+    hipLaunchKernelGGL((k_tau_overlaps<L, kGroups>), grid, dim3(64 * kOvWaves), 0, s, slot_spins, Ltau,
+                       taus, out);
+    return hipGetLastError();
+}
+
+// A wave takes two groups of slices before its block adds to the output, and
+// four where the planes are so small that adding is most of the work and the
+// blocks of two groups fill the chip several times (L = 2: 142 -> 85 us on 16384
+// blocks, 10.2 -> 9.0 on 896, but 4.5 -> 7.2 on 64; L = 4: 120 -> 92 on 16384,
+// 20.3 -> 17.3 on 2048; a lane per replica took 131, 9.5, 4.6, 107 and 19.5).
 template <int L>
 hipError_t launch_width(const uint64_t* slot_spins, uint32_t n_slots, uint32_t Ltau,
                         const TauList& taus, int64_t* out, hipStream_t s) {
-    constexpr uint32_t kPerBlock = kOvWaves * kOvGroups * (L <= 16 ? 4 : 2);
-    const dim3 grid((Ltau + kPerBlock - 1) / kPerBlock, taus.n, n_slots);
-    hipLaunchKernelGGL(k_tau_overlaps<L>, grid, dim3(64 * kOvWaves), 0, s, slot_spins, Ltau, taus,
-                       out);
-    return hipGetLastError();
+    if constexpr (L <= 4) {
+        const uint64_t blocks = (uint64_t)((Ltau + 31) / 32) * taus.n * n_slots;
+        if (blocks >= (L == 2 ? 512 : 2048))
+            return launch_groups<L, 4>(slot_spins, n_slots, Ltau, taus, out, s);
+    }
+    return launch_groups<L, 2>(slot_spins, n_slots, Ltau, taus, out, s);
 }
 
 }  // namespace
