@@ -1274,9 +1274,9 @@ k_swap_apply_batched(const BatchPlan plan, const Advance adv) {
 }
 
 // ---------------------------------------------------------------------------
-// Readings: every group's region into one packed buffer in pinned host
-// memory, so that an ensemble costs one launch and one wait instead of one
-// copy per group: energies, sums and exchange counts of 64 groups of 32 slots
+// Readings: the groups' regions into one packed buffer in pinned host memory,
+// so that a MiB of them costs one launch and one wait instead of one copy per
+// group: energies, sums and exchange counts of 64 groups of 32 slots
 // took 4.5 ms that way and take 1.  Bound by launch and bus latency, on
 // megabytes by the bus.
 // ---------------------------------------------------------------------------
